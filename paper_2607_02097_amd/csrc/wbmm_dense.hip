@@ -1,32 +1,17 @@
 // Cached-matrix (dense) form of WBMM for any window w_h x w_w with
 // d = w_h w_w <= 256 (Alg. 1 with the matrix built once, eq. index_select):
 //   build:    M_c[i, j] = T[c, I(i, j)]                    (matrix per channel)
-//   forward:  Y_window = X_window M_c, or X_window M_c^T   (input gradient)
 //   gradient: dM_c = sum over windows of X_window^T dY_window   (float32)
 //   bin:      dT[c, k] = sum of dM_c[i, j] over I(i, j) = k (fixed order)
 // Positions are row-major inside a window, p = h * w_w + x.  M is an
 // arbitrary dense matrix here (the table form's Toeplitz structure is not
 // used), so rectangular windows, fused matrices and any cached M share one
 // path.  The kernels are generic over the window (runtime sizes) and
-// instantiated once per dtype.
+// instantiated once per dtype.  The products X_window M_c and X_window M_c^T
+// are the general kernels' (wbmm_gen.h).
 #include "wbmm_kernels.h"
 
 namespace wbmm {
-
-constexpr int kDenseMaxD = 256;
-
-template <class Tag>
-struct DenseCfg {
-  static constexpr int WAVES = Tag::W16 ? 4 : 2;       // 16 windows per wave
-  static constexpr int TW = 16 * WAVES;                // windows per workgroup
-  static constexpr int NC = Tag::W16 ? 32 : 16;        // output positions per chunk
-  static constexpr int KMAX = kDenseMaxD;              // padded K bound
-  static constexpr int LDSX = Tag::W16 ? KMAX + 8 : KMAX + 4;  // row pitch (elements)
-  static constexpr int OW = NC + (Tag::W16 ? 8 : 4);   // output tile pitch
-  static constexpr int SMAX = KMAX / Tag::KS;          // K steps bound
-  static constexpr size_t LDS = (size_t)(TW + NC) * LDSX * Tag::ES + (size_t)TW * OW * Tag::ES;
-  static_assert(LDS <= 65536, "dense workgroup above 64 KB of LDS");
-};
 
 struct DenseArgs {
   int64_t B, C, H, W;
@@ -63,106 +48,6 @@ __global__ __launch_bounds__(256) void dense_build_kernel(const typename Tag::S 
     const int i = r / d, j = r - (r / d) * d;
     const int hi = i / ww, xi = i - hi * ww, ho = j / ww, xo = j - ho * ww;
     m[e] = t[c * k2 + (hi - ho + wh - 1) * k1 + (xi - xo + ww - 1)];
-  }
-}
-
-// Y = X M (TRANS: X M^T) per window.  One workgroup = (channel, TW windows);
-// the windows' rows land window-major in LDS, each wave keeps the A
-// fragments of its 16 windows in registers, and the output positions run in
-// chunks of NC: the chunk's columns of M (stored output-major, so that a B
-// fragment is one 16-byte read) are staged, multiplied, and the results
-// stored.
-template <class Tag, bool TRANS>
-__global__ __launch_bounds__(256) void dense_fwd_kernel(const typename Tag::S *__restrict__ x,
-                                                        const typename Tag::S *__restrict__ m,
-                                                        typename Tag::S *__restrict__ y, DenseArgs a) {
-  typedef typename Tag::S S;
-  typedef typename Tag::Frag Frag;
-  typedef DenseCfg<Tag> G;
-  constexpr int NT_ = G::NC / 16;
-  extern __shared__ __align__(16) unsigned char smem[];
-  S *Xt = reinterpret_cast<S *>(smem);
-  S *Mt = Xt + G::TW * G::LDSX;
-  S *Ot = Mt + G::NC * G::LDSX;
-
-  const int tid = threadIdx.x;
-  const int nthr = 64 * G::WAVES;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, ln = lane & 15;
-  const int64_t c = blockIdx.x / a.tiles_per_ch;
-  const int64_t n0 = (int64_t)(blockIdx.x - c * a.tiles_per_ch) * G::TW;
-  const int d = a.d, kp = a.kp;
-  const S *mc = m + c * (int64_t)d * d;
-
-  // ---- the windows' rows, window-major (zero beyond d and in the padding)
-  for (int e = tid; e < G::TW * kp; e += nthr) {
-    const int v = e / kp, p = e - (e / kp) * kp;
-    S val = (S)0;
-    if (p < d && n0 + v < a.N) {
-      const int64_t o = dense_offset(a, c, n0 + v, p);
-      if (o >= 0) val = x[o];
-    }
-    Xt[v * G::LDSX + p] = val;
-  }
-  __syncthreads();
-  const int S_ = kp / Tag::KS;
-  Frag af[G::SMAX];
-  if constexpr (Tag::W16) {
-#pragma unroll
-    for (int s = 0; s < G::SMAX; ++s)
-      if (s < S_) af[s] = *reinterpret_cast<const Frag *>(&Xt[(16 * wave + ln) * G::LDSX + 32 * s + 8 * g]);
-  } else {
-#pragma unroll
-    for (int s = 0; s < G::SMAX; ++s)
-      if (s < S_) af[s] = Xt[(16 * wave + ln) * G::LDSX + 4 * s + g];
-  }
-
-  for (int j0 = 0; j0 < d; j0 += G::NC) {
-    // ---- columns j0 .. j0+NC of M (rows of M^T), output-major
-    if (!TRANS) {
-      for (int e = tid; e < G::NC * kp; e += nthr) {
-        const int k = e / G::NC, nn = e - (e / G::NC) * G::NC;
-        Mt[nn * G::LDSX + k] = (k < d && j0 + nn < d) ? mc[(int64_t)k * d + j0 + nn] : (S)0;
-      }
-    } else {
-      for (int e = tid; e < G::NC * kp; e += nthr) {
-        const int nn = e / kp, k = e - (e / kp) * kp;
-        Mt[nn * G::LDSX + k] = (k < d && j0 + nn < d) ? mc[(int64_t)(j0 + nn) * d + k] : (S)0;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < NT_; ++t) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (Tag::W16) {
-#pragma unroll
-        for (int s = 0; s < G::SMAX; ++s)
-          if (s < S_)
-            acc = mma<Tag>(af[s], *reinterpret_cast<const Frag *>(&Mt[(16 * t + ln) * G::LDSX + 32 * s + 8 * g]), acc);
-        const uint32_t lo = pack2<Tag>(acc[0], acc[1]), hi = pack2<Tag>(acc[2], acc[3]);
-        S *o = Ot + (16 * wave + 4 * g) * G::OW + 16 * t + ln;
-        o[0] = (S)(lo & 0xffffu);
-        o[G::OW] = (S)(lo >> 16);
-        o[2 * G::OW] = (S)(hi & 0xffffu);
-        o[3 * G::OW] = (S)(hi >> 16);
-      } else {
-#pragma unroll
-        for (int s = 0; s < G::SMAX; ++s)
-          if (s < S_) acc = mma<Tag>(af[s], Mt[(16 * t + ln) * G::LDSX + 4 * s + g], acc);
-        S *o = Ot + (16 * wave + 4 * g) * G::OW + 16 * t + ln;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[r * G::OW] = acc[r];
-      }
-    }
-    __syncthreads();
-    for (int e = tid; e < G::TW * G::NC; e += nthr) {
-      const int v = e / G::NC, nn = e - (e / G::NC) * G::NC;
-      if (j0 + nn < d && n0 + v < a.N) {
-        const int64_t o = dense_offset(a, c, n0 + v, j0 + nn);
-        if (o >= 0) y[o] = Ot[v * G::OW + nn];
-      }
-    }
-    __syncthreads();
   }
 }
 
@@ -284,21 +169,6 @@ static hipError_t run_dense_build(const void *t, void *m, int64_t C, int wh, int
 }
 
 template <class Tag>
-static hipError_t run_dense_fwd(const void *x, const void *m, void *y, const Geom &g, int wh, int ww, bool trans,
-                                hipStream_t st) {
-  typedef DenseCfg<Tag> G;
-  DenseArgs a = dense_args(g, wh, ww, Tag::KS);
-  a.tiles_per_ch = (int)((a.N + G::TW - 1) / G::TW);
-  const dim3 grid((unsigned)(g.C * a.tiles_per_ch)), block(64 * G::WAVES);
-  typedef typename Tag::S S;
-  if (trans)
-    dense_fwd_kernel<Tag, true><<<grid, block, G::LDS, st>>>((const S *)x, (const S *)m, (S *)y, a);
-  else
-    dense_fwd_kernel<Tag, false><<<grid, block, G::LDS, st>>>((const S *)x, (const S *)m, (S *)y, a);
-  return hipGetLastError();
-}
-
-template <class Tag>
 static hipError_t run_dense_dm(const void *x, const void *dy, float *dm, const Geom &g, int wh, int ww,
                                hipStream_t st) {
   typedef DenseDmCfg<Tag> G;
@@ -315,16 +185,6 @@ hipError_t launch_dense_build(Dt dt, const void *t, void *m, int64_t C, int wh, 
     case Dt::F32: return run_dense_build<TagF32>(t, m, C, wh, ww, st);
     case Dt::BF16: return run_dense_build<TagBF16>(t, m, C, wh, ww, st);
     case Dt::F16: return run_dense_build<TagF16>(t, m, C, wh, ww, st);
-  }
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_dense_forward(Dt dt, const void *x, const void *m, void *y, const Geom &g, int wh, int ww,
-                                bool trans, hipStream_t st) {
-  switch (dt) {
-    case Dt::F32: return run_dense_fwd<TagF32>(x, m, y, g, wh, ww, trans, st);
-    case Dt::BF16: return run_dense_fwd<TagBF16>(x, m, y, g, wh, ww, trans, st);
-    case Dt::F16: return run_dense_fwd<TagF16>(x, m, y, g, wh, ww, trans, st);
   }
   return hipErrorInvalidValue;
 }

@@ -83,4 +83,15 @@ size_t dtable_workspace_bytes(Dt dt, const Geom &g) {
   return (size_t)p.slabs * (size_t)g.C * (size_t)(k1 * k1) * sizeof(float);
 }
 
+hipError_t launch_dense_forward(Dt dt, const void *x, const void *m, void *y, const Geom &g, int wh, int ww,
+                                bool trans, hipStream_t stream) {
+  const int src = trans ? 3 : 2;
+  switch (dt) {
+    case Dt::F32: return GenEntry<TagF32>::forward(x, m, y, g, wh, ww, src, stream);
+    case Dt::BF16: return GenEntry<TagBF16>::forward(x, m, y, g, wh, ww, src, stream);
+    case Dt::F16: return GenEntry<TagF16>::forward(x, m, y, g, wh, ww, src, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
 }  // namespace wbmm

@@ -1,0 +1,828 @@
+// General WBMM kernels for gfx950: any map, any w_h x w_w window (sides up to
+// 16), coefficients from the table or from a materialised matrix, float32 and
+// 16-bit.  They serve what the fixed-layout kernels of wbmm_kernels.h do not:
+// maps the windows do not tile, odd image widths, rectangular windows, cached
+// matrices, and float32.
+//
+// Shape of the work
+// -----------------
+// Window positions are row padded (RP = 8 or 16 columns per window row), as in
+// wbmm_kernels.h.  One 8-wave workgroup runs consecutive stages of one
+// channel; a stage is CW windows whose rows number 512, so that each thread
+// moves exactly one window row: thread t moves row t / CW of window t % CW,
+// and the lanes of a wave touch consecutive pieces of one image row.  Rows are
+// read with unaligned 16-byte loads and masked (columns past the window or the
+// image are zero), so there is no per-element path for odd widths or cut
+// windows, except for the rows within 16 elements of the tensor's end.
+//
+// The coefficients (M^T fragments) are read once per workgroup into registers:
+// wave T holds those of output positions 32 T .. 32 T + 31 for every K step,
+// and the stages stream past them.
+#pragma once
+
+#include <type_traits>
+
+#include "wbmm_kernels.h"
+
+namespace wbmm {
+
+constexpr int kGenWaves = 8;
+constexpr int kGenThreads = 64 * kGenWaves;
+
+// Where the coefficients come from: the table (forward, or read back to
+// front for the input gradient), or a matrix [C, d, d] (forward, or
+// transposed).
+enum GenSrc { kSrcTable = 0, kSrcTableRev = 1, kSrcMat = 2, kSrcMatT = 3 };
+
+// Division of n < 2^31 by a constant d >= 1: (n m) >> sh with
+// sh = 31 + ceil(log2 d) and m = floor(2^sh / d) + 1, exact since
+// m d - 2^sh is at most d <= 2^(sh - 31).
+struct FastDiv {
+  uint32_t m;
+  int sh;
+};
+__host__ inline FastDiv fast_div(uint32_t d) {
+  int l = 0;
+  while (((uint64_t)1 << l) < d) ++l;
+  return FastDiv{(uint32_t)((((uint64_t)1 << (31 + l)) / d) + 1), 31 + l};
+}
+__device__ __attribute__((always_inline)) inline uint32_t div_by(uint32_t n, FastDiv f) {
+  return (uint32_t)(((uint64_t)n * f.m) >> f.sh);
+}
+
+struct GenArgs {
+  int64_t C, H, W;
+  int64_t hw, chw;   // H W, C H W
+  int64_t numel;     // elements of one [B,C,H,W] tensor
+  uint32_t NW, NHW;  // windows per map row, per image
+  FastDiv dnw, dnhw;
+  uint32_t N;        // windows per channel (below 2^31)
+  int wh, ww;
+  int stages;        // per channel
+  int spw;           // stages per workgroup
+  int tiles_per_ch;  // workgroups per channel
+  int src;           // GenSrc
+  int lgg;           // log2 of the windows of a row that neighbouring lanes take
+};
+
+__host__ __device__ constexpr int pow2_up(int v) { return v <= 1 ? 1 : v <= 2 ? 2 : v <= 4 ? 4 : v <= 8 ? 8 : 16; }
+
+// S: K steps of 32 padded positions (rows_up(wh) = 32 S / RP).
+template <class Tag, int RP, int S>
+struct GenCfg {
+  static constexpr int KP = 32 * S;                  // padded positions
+  static constexpr int KR = KP / RP;                 // padded rows
+  static constexpr int KRP = 32 * pow2_up(S) / RP;   // row slots per window
+  static constexpr int CW = kGenThreads / KRP;       // windows per stage
+  static constexpr int SUBS = CW / 16;
+  static constexpr int NT = 2 * S;                   // 16-wide position tiles
+  static constexpr int NPL = Tag::W16 ? 1 : 3;       // 16-bit planes of a value
+  static constexpr int LDSW = KP + 8;                // pitch of a plane (elements)
+  static constexpr int PLANE = CW * LDSW * 2;        // bytes
+  static constexpr int XB = NPL * PLANE;             // one stage of one tensor
+  static constexpr int OP = Tag::W16 ? KP + 8 : KP + 4;  // result pitch (elements)
+  static constexpr int OB = CW * OP * Tag::ES;
+  static constexpr int NG = kGenWaves / S;           // wave groups sharing a stage's sub-tiles
+  static constexpr int SPW = cdiv(SUBS, NG);         // sub-tiles of a wave per stage
+  static_assert(SUBS % NG == 0, "whole sub-tiles per wave");
+  static constexpr int ND = RP * Tag::ES / 4;        // dwords of a padded row
+  // Toeplitz blocks of the table: dh = -(KR - 1) .. KR - 1
+  static constexpr int NBLK = 2 * KR - 1;
+  static constexpr int TBB = NBLK * RP * RP * 2;     // bytes of one plane
+  static constexpr int CKB = 32 * LDSW * 2;          // a chunk of 32 matrix rows
+  static_assert(NPL * TBB <= XB, "blocks within one stage buffer");
+};
+
+// Window (of the stage) and row that a thread moves: neighbouring lanes take
+// the same row of 2^lgg neighbouring windows, then the next rows of the same
+// windows, so that a wave's rows lie together in memory: with few windows per
+// map row (2^lgg is the largest power of two not above that), the rows of one
+// image follow each other.
+template <class G>
+__device__ __attribute__((always_inline)) inline int gen_slot_window(const GenArgs &a, int t) {
+  return (t / G::KRP >> a.lgg << a.lgg) | (t & ((1 << a.lgg) - 1));
+}
+template <class G>
+__device__ __attribute__((always_inline)) inline int gen_slot_row(const GenArgs &a, int t) {
+  return (t >> a.lgg) & (G::KRP - 1);
+}
+
+struct GRow {
+  int64_t eoff;  // first element of the row
+  int cols;      // its elements inside window and image, 0: none
+};
+
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4))) __attribute__((aligned(2)));
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2))) __attribute__((aligned(2)));
+typedef uint32_t u32u __attribute__((aligned(2)));
+
+// Row hi of window n of channel c.
+__device__ __attribute__((always_inline)) inline GRow gen_row(const GenArgs &a, int64_t c, uint32_t n, int hi) {
+  GRow r;
+  r.eoff = 0;
+  r.cols = 0;
+  if (n >= a.N || hi >= a.wh) return r;
+  const uint32_t b = div_by(n, a.dnhw), rem = n - b * a.NHW;
+  const uint32_t wy = div_by(rem, a.dnw), wx = rem - wy * a.NW;
+  const int h = (int)wy * a.wh + hi, x0 = (int)wx * a.ww;
+  const int cw = (int)a.W - x0;
+  r.cols = h < (int)a.H ? (cw < a.ww ? cw : a.ww) : 0;
+  r.eoff = (int64_t)b * a.chw + c * a.hw + (int64_t)h * a.W + x0;
+  return r;
+}
+
+// Sixteen zero elements for the rows that do not exist.
+__device__ const uint32_t gen_zero[16] = {};
+
+// RP elements from the row's start (the ones past its end belong to the
+// tensor; gen_mask clears them).  Every lane loads, with no branch around the
+// loads, so that a wait for them counts exactly and leaves later loads in
+// flight: rows that do not exist load zeros, rows within RP elements of the
+// tensor's end its last RP elements (gen_tail moves them down).  The tensor
+// holds at least RP elements.
+template <class Tag, int RP>
+__device__ __attribute__((always_inline)) inline void gen_load(int64_t numel, const typename Tag::S *x, const GRow &r,
+                                                               uint32_t (&d)[RP * Tag::ES / 4]) {
+  typedef const __attribute__((address_space(1))) u32x4u *GP;
+  const int64_t last = numel - RP;
+  const int64_t e = r.eoff < last ? r.eoff : last;
+  const uint64_t p = r.cols > 0 ? reinterpret_cast<uint64_t>(x + e) : reinterpret_cast<uint64_t>(gen_zero);
+#pragma unroll
+  for (int i = 0; i < RP * Tag::ES / 4; i += 4) {
+    const u32x4u u = *reinterpret_cast<GP>(p + 4 * i);
+    d[i] = u.x; d[i + 1] = u.y; d[i + 2] = u.z; d[i + 3] = u.w;
+  }
+}
+
+// A row within RP elements of the tensor's end: its elements moved down to
+// the row's start.
+template <class Tag, int RP>
+__device__ __attribute__((always_inline)) inline void gen_tail(int64_t numel, const GRow &r,
+                                                               uint32_t (&d)[RP * Tag::ES / 4]) {
+  constexpr int ND = RP * Tag::ES / 4;
+  const int64_t over = r.eoff + RP - numel;
+  if (r.cols > 0 && over > 0) {
+#pragma unroll 1
+    for (int k = (int)over; k > 0; --k) {
+#pragma unroll
+      for (int i = 0; i < ND; ++i) {
+        const uint32_t up = i + 1 < ND ? d[i + 1] : 0u;
+        d[i] = Tag::W16 ? __builtin_amdgcn_alignbit(up, d[i], 16) : up;
+      }
+    }
+  }
+}
+
+// Zero past the row's columns (apart from the loads, so that the wait for
+// them comes where the row is used).
+template <class Tag, int RP>
+__device__ __attribute__((always_inline)) inline void gen_mask(int cols, uint32_t (&d)[RP * Tag::ES / 4]) {
+#pragma unroll
+  for (int i = 0; i < RP * Tag::ES / 4; ++i) {
+    if constexpr (Tag::W16) d[i] = cols > 2 * i + 1 ? d[i] : (cols > 2 * i ? (d[i] & 0xffffu) : 0u);
+    else d[i] = cols > i ? d[i] : 0u;
+  }
+}
+
+// The first cols elements of a padded row -> y (cols <= RP; unaligned).
+template <class Tag, int RP>
+__device__ __attribute__((always_inline)) inline void gen_store(typename Tag::S *y, const GRow &r,
+                                                                uint32_t (&d)[RP * Tag::ES / 4]) {
+  constexpr int ND = RP * Tag::ES / 4;
+  char *p = reinterpret_cast<char *>(y + r.eoff);
+  const int nb = r.cols * Tag::ES;  // bytes
+  // whole 16-byte pieces first, then the rest by the bits of its length
+  const int full = nb >> 4;
+  uint32_t t[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < ND / 4; ++i) {
+    if (i < full)
+      *reinterpret_cast<u32x4u *>(p + 16 * i) = u32x4u{d[4 * i], d[4 * i + 1], d[4 * i + 2], d[4 * i + 3]};
+    if (i == full) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) t[k] = d[4 * i + k];
+    }
+  }
+  p += 16 * full;
+  if (nb & 8) {
+    *reinterpret_cast<u32x2u *>(p) = u32x2u{t[0], t[1]};
+    p += 8;
+    t[0] = t[2];
+    t[1] = t[3];
+  }
+  if (nb & 4) {
+    *reinterpret_cast<u32u *>(p) = t[0];
+    p += 4;
+    t[0] = t[1];
+  }
+  if constexpr (Tag::ES == 2) {
+    if (nb & 2) *reinterpret_cast<u16 *>(p) = (u16)(t[0] & 0xffffu);
+  }
+}
+
+// float32 on the bf16 matrix cores
+// --------------------------------
+// A float32 value is the exact sum of three bf16 values, hi + mid + lo, each
+// the nearest bf16 to what is left (8 + 8 + 8 significant bits).  A product of
+// two values is taken as the six partial products of weight 2^-16 and above,
+//   hi hi + (hi mid + mid hi) + (mid mid + hi lo + lo hi),
+// every one exact in float32, the first summed in one accumulator and the
+// others in a second one: what is left out is below 2^-24 of the product.  The
+// bf16 rate is sixteen times the float32 matrix rate, six products cost 3/8 of
+// a float32 one.  Ranges where a part would overflow or vanish (and
+// infinities and NaN) take float32 products instead: a row is "far" when its
+// largest magnitude is at least 2^60, or not zero and below 2^-96.
+constexpr uint32_t kFarHi = (127u + 60u) << 23, kFarLo = (127u - 96u) << 23;
+constexpr uint32_t kFarLoCoef = (127u - 60u) << 23;
+
+// Two values -> the dwords of their three planes.
+__device__ __attribute__((always_inline)) inline void split3(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
+  h = pack2<TagBF16>(a, b);
+  const float ra = a - __builtin_bit_cast(float, h << 16), rb = b - __builtin_bit_cast(float, h & 0xffff0000u);
+  m = pack2<TagBF16>(ra, rb);
+  const float sa = ra - __builtin_bit_cast(float, m << 16), sb = rb - __builtin_bit_cast(float, m & 0xffff0000u);
+  l = pack2<TagBF16>(sa, sb);
+}
+
+// A padded row -> LDS (window-major planes); float32: returns whether the row
+// is far.
+template <class Tag, int RP, int S>
+__device__ __attribute__((always_inline)) inline bool gen_write(unsigned char *xb, int v, int hi,
+                                                                const uint32_t (&d)[RP * Tag::ES / 4]) {
+  typedef GenCfg<Tag, RP, S> G;
+  unsigned char *p = xb + (v * G::LDSW + hi * RP) * 2;
+  bool far = false;
+  if constexpr (Tag::W16) {
+#pragma unroll
+    for (int i = 0; i < G::ND; i += 4)
+      *reinterpret_cast<uint4 *>(p + 4 * i) = make_uint4(d[i], d[i + 1], d[i + 2], d[i + 3]);
+  } else {
+    uint32_t mx = 0;
+#pragma unroll
+    for (int i = 0; i < G::ND; ++i) {
+      const uint32_t m = d[i] & 0x7fffffffu;
+      mx = m > mx ? m : mx;
+    }
+    far = mx >= kFarHi || (mx != 0 && mx < kFarLo);
+#pragma unroll
+    for (int i = 0; i < RP; i += 8) {
+      uint32_t h[4], m[4], l[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        split3(__builtin_bit_cast(float, d[i + 2 * k]), __builtin_bit_cast(float, d[i + 2 * k + 1]), h[k], m[k], l[k]);
+      *reinterpret_cast<uint4 *>(p + 2 * i) = make_uint4(h[0], h[1], h[2], h[3]);
+      *reinterpret_cast<uint4 *>(p + G::PLANE + 2 * i) = make_uint4(m[0], m[1], m[2], m[3]);
+      *reinterpret_cast<uint4 *>(p + 2 * G::PLANE + 2 * i) = make_uint4(l[0], l[1], l[2], l[3]);
+    }
+  }
+  return far;
+}
+
+typedef u16x8 GFrag;
+
+__device__ __attribute__((always_inline)) inline f32x4 mma_bf16(GFrag a, GFrag b, f32x4 c) { return mma<TagBF16>(a, b, c); }
+
+// Coefficient of input position (hi, xi) and output position (ho, xo), both
+// inside the window, in global memory.
+template <class Tag>
+__device__ __attribute__((always_inline)) inline int64_t gen_coef(const GenArgs &a, int64_t c, int hi, int xi, int ho,
+                                                                  int xo) {
+  const int K1 = 2 * a.ww - 1, K2 = K1 * (2 * a.wh - 1), d = a.wh * a.ww;
+  if (a.src <= kSrcTableRev) {
+    const int k = (hi - ho + a.wh - 1) * K1 + xi - xo + a.ww - 1;
+    return c * K2 + (a.src == kSrcTableRev ? K2 - 1 - k : k);
+  }
+  const int i = hi * a.ww + xi, j = ho * a.ww + xo;
+  return c * d * d + (a.src == kSrcMat ? i * d + j : j * d + i);
+}
+
+// ---- coefficients from the table
+// Toeplitz blocks in LDS, block dh = hi - ho from -(KR - 1) to KR - 1 as
+// [x_out][x_in] (zero past the window), from the table copy Ts (reversed for
+// the input gradient): a fragment is then one 16-byte read at a per-lane
+// base plus a constant.  float32: three planes, the lowest at tblow.  Returns
+// the largest magnitude the thread saw (float32).
+template <class Tag, int RP, int S>
+__device__ __attribute__((always_inline)) inline uint32_t gen_build_tb(const GenArgs &a, const typename Tag::S *Ts,
+                                                                       unsigned char *tb, unsigned char *tblow,
+                                                                       int tid) {
+  typedef GenCfg<Tag, RP, S> G;
+  constexpr int CPR = RP / 8;  // 8-element chunks per block row
+  const int K1 = 2 * a.ww - 1;
+  uint32_t mx = 0;
+  for (int ch = tid; ch < G::NBLK * RP * CPR; ch += kGenThreads) {
+    const int row = ch / CPR, xi0 = (ch % CPR) * 8;
+    const int dh = row / RP - (G::KR - 1), xo = row % RP;
+    const bool ok = dh > -a.wh && dh < a.wh && xo < a.ww;
+    const int base = ok ? (dh + a.wh - 1) * K1 + xi0 - xo + a.ww - 1 : 0;
+    const int nv = ok ? a.ww - xi0 : 0;  // columns inside the window
+    const int off = (row * RP + xi0) * 2;
+    unsigned char *p = tb + off;
+    if constexpr (Tag::W16) {
+      const uint32_t *q = reinterpret_cast<const uint32_t *>(Ts) + (base >> 1);
+      const uint32_t sh = (uint32_t)(base & 1) * 16u;
+      uint32_t d[5], u[4];
+#pragma unroll
+      for (int i = 0; i < 5; ++i) d[i] = q[i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t w = __builtin_amdgcn_alignbit(d[i + 1], d[i], sh);
+        u[i] = nv > 2 * i + 1 ? w : nv > 2 * i ? (w & 0xffffu) : 0u;
+      }
+      *reinterpret_cast<uint4 *>(p) = make_uint4(u[0], u[1], u[2], u[3]);
+    } else {
+      uint32_t h[4], m[4], l[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float f0 = nv > 2 * k ? Ts[base + 2 * k] : 0.f, f1 = nv > 2 * k + 1 ? Ts[base + 2 * k + 1] : 0.f;
+        const uint32_t m0 = __builtin_bit_cast(uint32_t, f0) & 0x7fffffffu, m1 = __builtin_bit_cast(uint32_t, f1) & 0x7fffffffu;
+        mx = m0 > mx ? m0 : mx;
+        mx = m1 > mx ? m1 : mx;
+        split3(f0, f1, h[k], m[k], l[k]);
+      }
+      *reinterpret_cast<uint4 *>(p) = make_uint4(h[0], h[1], h[2], h[3]);
+      *reinterpret_cast<uint4 *>(p + G::TBB) = make_uint4(m[0], m[1], m[2], m[3]);
+      *reinterpret_cast<uint4 *>(tblow + off) = make_uint4(l[0], l[1], l[2], l[3]);
+    }
+  }
+  return mx;
+}
+
+// Byte offset in the blocks of lane's part of the fragment of tile pair T at
+// tile 0, K step 0, and the step from there to tile h, K step s.
+template <class Tag, int RP, int S>
+__device__ __attribute__((always_inline)) inline int gen_tb_lane(int T, int lane) {
+  const int g = lane >> 4, ln = lane & 15;
+  const int hl = 8 * g / RP, xi0 = 8 * g % RP;  // row within the K step, first column
+  const int ol = ln / RP, xo = ln % RP;         // row within the output tile, column
+  return (((hl - ol - T * (32 / RP) + GenCfg<Tag, RP, S>::KR - 1) * RP + xo) * RP + xi0) * 2;
+}
+template <int RP>
+__host__ __device__ constexpr int gen_tb_step(int h, int s) { return (s * (32 / RP) - h * (16 / RP)) * RP * RP * 2; }
+
+// This wave's fragments from the blocks: out positions 32 T + 16 h .. + 15
+// (h = 0, 1), K step s.  Rows past the window are zero coefficients; output
+// positions past it are not stored and may hold anything.
+template <class Tag, int RP, int S, int NPR>
+__device__ __attribute__((always_inline)) inline void gen_frags_tb(const GenArgs &a, const unsigned char *tb, int T,
+                                                                   int lane, GFrag (&fr)[NPR][2][S]) {
+  typedef GenCfg<Tag, RP, S> G;
+  const int g = lane >> 4;
+  const int hl = 8 * g / RP;  // row within the K step
+  const unsigned char *base = tb + gen_tb_lane<Tag, RP, S>(T, lane);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int p = 0; p < NPR; ++p) {
+        fr[p][h][s] = *reinterpret_cast<const GFrag *>(base + p * G::TBB + gen_tb_step<RP>(h, s));
+        if (s == S - 1 && (S - 1) * (32 / RP) + hl >= a.wh) fr[p][h][s] = GFrag{0, 0, 0, 0, 0, 0, 0, 0};
+      }
+}
+
+// ---- coefficients from a matrix, 16-bit
+// Position-major fragment (16 columns x 8 rows per lane group) of a row-major
+// LDS tile: lane (g, i) receives column 16 t + i of rows 8 g .. 8 g + 7, by
+// two transposing reads.
+template <int LDSW>
+__device__ __attribute__((always_inline)) inline GFrag gen_tr_frag(const unsigned char *tile, int t, int lane) {
+  const int g = lane >> 4, r = (lane >> 2) & 3, q = lane & 3;
+  const int e0 = (8 * g + r) * LDSW + 16 * t + 4 * q;
+  const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)(tile + 2 * e0));
+  const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)(tile + 2 * (e0 + 4 * LDSW)));
+  return __builtin_bit_cast(GFrag, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// The matrix goes through LDS in chunks of 32 padded rows (rows and columns
+// padded as window positions, pads zero), a few chunks at a time, one window
+// row of one matrix row per thread.  M: chunk s holds K step s of every
+// output position, read with transposing reads; M^T: chunk T holds all of
+// wave T's fragments, read as they lie.  (Gathering the fragments from global
+// memory took most of the kernel: B128 C256 28x28, 14 x 14 windows, bf16.)
+template <class Tag, int RP, int S, int ROOM, bool TRANS>
+__device__ __attribute__((always_inline)) inline void gen_frags_mat16(const GenArgs &a, const u16 *coef, int64_t c,
+                                                                      int T, int tid, unsigned char *lds,
+                                                                      GFrag (&fr)[1][2][S]) {
+  typedef GenCfg<Tag, RP, S> G;
+  constexpr int CKB = G::CKB;
+  constexpr int NCK = ROOM / CKB < S ? ROOM / CKB : S;  // chunks at a time
+  static_assert(NCK >= 1 && 32 * G::KR <= kGenThreads, "one row per thread and chunk");
+  const int lane = tid & 63, g = lane >> 4, ln = lane & 15;
+  const int d = a.wh * a.ww;
+  const int64_t numel = a.C * d * d;
+  const int kk = tid / G::KR, ho = tid - kk * G::KR;  // padded row of the chunk, window row of its columns
+  auto row = [&](int ck) __attribute__((always_inline)) -> GRow {
+    const int hi = ck * (32 / RP) + kk / RP, xi = kk % RP;
+    GRow r;
+    r.cols = ck < S && kk < 32 && hi < a.wh && xi < a.ww && ho < a.wh ? a.ww : 0;
+    r.eoff = c * d * d + (int64_t)(hi * a.ww + xi) * d + ho * a.ww;
+    return r;
+  };
+  uint32_t v[NCK][G::ND];
+#pragma unroll
+  for (int q = 0; q < NCK; ++q) gen_load<Tag, RP>(numel, coef, row(q), v[q]);
+#pragma unroll
+  for (int c0 = 0; c0 < S; c0 += NCK) {
+#pragma unroll
+    for (int q = 0; q < NCK; ++q) {
+      const GRow r = row(c0 + q);
+      gen_tail<Tag, RP>(numel, r, v[q]);
+      gen_mask<Tag, RP>(r.cols, v[q]);
+      if (kk < 32) {
+        unsigned char *p = lds + q * CKB + (kk * G::LDSW + ho * RP) * 2;
+#pragma unroll
+        for (int i = 0; i < G::ND; i += 4)
+          *reinterpret_cast<uint4 *>(p + 4 * i) = make_uint4(v[q][i], v[q][i + 1], v[q][i + 2], v[q][i + 3]);
+      }
+    }
+    __syncthreads();
+    if (c0 + NCK < S) {
+#pragma unroll
+      for (int q = 0; q < NCK; ++q) gen_load<Tag, RP>(numel, coef, row(c0 + NCK + q), v[q]);
+    }
+    if constexpr (TRANS) {
+      const int q = T - c0;
+      if (q >= 0 && q < NCK) {
+        const unsigned char *t = lds + q * CKB + (ln * G::LDSW + 8 * g) * 2;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int s = 0; s < S; ++s) fr[0][h][s] = *reinterpret_cast<const GFrag *>(t + 32 * h * G::LDSW + 64 * s);
+      }
+    } else {
+#pragma unroll
+      for (int s = c0; s < (c0 + NCK < S ? c0 + NCK : S); ++s)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) fr[0][h][s] = gen_tr_frag<G::LDSW>(lds + (s - c0) * CKB, 2 * T + h, lane);
+    }
+    __syncthreads();
+  }
+}
+
+// ---- coefficients from a matrix, float32: gathered from global memory
+template <int RP, int S>
+__device__ __attribute__((always_inline)) inline void gen_frags_mat32(const GenArgs &a, const float *coef, int64_t c,
+                                                                      int T, int lane, GFrag (&fr)[3][2][S],
+                                                                      uint32_t &mx) {
+  const int g = lane >> 4, ln = lane & 15;
+  const int d = a.wh * a.ww;
+  const float *cm = coef + c * d * d;
+  // the eight columns of a fragment, the same for every K step and tile:
+  // masks of the ones inside the window, and their offsets from the first
+  const int xi0 = 8 * g % RP;
+  uint32_t cmask[8];
+  int eoff[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const bool in = xi0 + e < a.ww;
+    eoff[e] = in ? e * (a.src == kSrcMat ? d : 1) : 0;
+    cmask[e] = in ? ~0u : 0u;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int j = 32 * T + 16 * h + ln;
+    const int ho = j / RP, xo = j % RP;
+    const int j0 = ho * a.ww + xo;
+    const bool jok = ho < a.wh && xo < a.ww;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int hi = (32 * s + 8 * g) / RP;
+      const bool ok = jok && hi < a.wh && xi0 < a.ww;
+      const uint32_t okm = ok ? ~0u : 0u;
+      const int i0 = hi * a.ww + xi0;
+      const int base = !ok ? 0 : a.src == kSrcMat ? i0 * d + j0 : j0 * d + i0;
+      float v[8];
+      uint32_t hh[4], mm[4], ll[4];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        uint32_t u = __builtin_bit_cast(uint32_t, cm[(uint32_t)(base + eoff[e])]) & cmask[e] & okm;
+        // (the finished value, not its parts, is what stays in registers)
+        asm volatile("" : "+v"(u));
+        v[e] = __builtin_bit_cast(float, u);
+        mx = (u & 0x7fffffffu) > mx ? (u & 0x7fffffffu) : mx;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) split3(v[2 * k], v[2 * k + 1], hh[k], mm[k], ll[k]);
+      fr[0][h][s] = __builtin_bit_cast(GFrag, make_uint4(hh[0], hh[1], hh[2], hh[3]));
+      fr[1][h][s] = __builtin_bit_cast(GFrag, make_uint4(mm[0], mm[1], mm[2], mm[3]));
+      fr[2][h][s] = __builtin_bit_cast(GFrag, make_uint4(ll[0], ll[1], ll[2], ll[3]));
+      // a few fragments' loads in flight at a time: all of them at once
+      // would not fit the registers
+      if (s % 4 == 3 || s + 1 == S) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// float32 products of one sub-tile straight from global memory (stages with
+// far rows, far coefficients): slow, and the same for every shape.
+template <int RP, int S>
+__device__ __attribute__((always_inline)) inline f32x4 gen_far_tile(const GenArgs &a, const float *x, const float *coef, int64_t c,
+                                                        uint32_t n, int j, int g) {
+  const int ho = j / RP, xo = j % RP;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int s = 0; s < 8 * S; ++s) {
+    const int k = 4 * s + g;
+    const int hi = k / RP, xi = k % RP;
+    float bv = 0.f, av = 0.f;
+    if (hi < a.wh && xi < a.ww && ho < a.wh && xo < a.ww) bv = coef[gen_coef<TagF32>(a, c, hi, xi, ho, xo)];
+    const GRow r = gen_row(a, c, n, hi);
+    if (xi < r.cols) av = x[r.eoff + xi];
+    acc = mma<TagF32>(bv, av, acc);
+  }
+  return acc;
+}
+
+// Registers and LDS of the forward kernel (MAT: coefficients from a matrix).
+template <class Tag, int RP, int S, bool MAT>
+struct GenFwd {
+  typedef GenCfg<Tag, RP, S> G;
+  // float32 fragments: the lowest plane (one product in six) stays in LDS as
+  // Toeplitz blocks where all three would not leave registers for the rows in
+  // flight
+  static constexpr bool LOW = !Tag::W16 && !MAT && S >= 6;
+  static constexpr int NPR = LOW ? 2 : G::NPL;          // planes in registers
+  static constexpr bool TIGHT = !Tag::W16 && MAT && S >= 5;  // registers short
+  static constexpr int AHEAD = TIGHT ? 2 : 3;           // stages from a row's load to its use, + 1
+  static constexpr int FIX = (LOW ? G::TBB : 0) + 32;   // blocks, flags
+  static constexpr int NOB = 2 * G::XB + 2 * G::OB + FIX <= 160 * 1024 ? 2 : 1;  // result buffers
+  static constexpr int LOW_OFF = 2 * G::XB + NOB * G::OB;
+  static constexpr int FLAG_OFF = LOW_OFF + (LOW ? G::TBB : 0);
+  // 16-bit matrices: LDS for as many chunks as there are, one workgroup per
+  // compute unit
+  static constexpr int MROOM = (160 * 1024 - G::XB) / G::CKB * G::CKB;
+  static constexpr int MEND = G::XB + (MROOM < S * G::CKB ? MROOM : S * G::CKB);
+  static constexpr size_t LDS = Tag::W16 && MAT && MEND > FLAG_OFF + 32 ? (size_t)MEND : (size_t)FLAG_OFF + 32;
+  static constexpr int WGS = Tag::W16 && LDS <= 80 * 1024 ? 2 : 1;  // workgroups per compute unit
+};
+
+// Y = X M per window.  Stage s is multiplied while stage s + 1 (in registers)
+// goes to the other LDS buffer, stage s + 3 is loaded and the rows of stage
+// s - 1 are stored: one barrier per stage.
+//
+// What bounds it: 16-bit, memory while it streams (about 5 TB/s of the 7 a
+// copy reaches) and, at the sizes of a layer, the prologue (2.6 us of launch,
+// 4 to 5 until the first stage is multiplied); float32, the matrix cores, six
+// products for one, at the 1.9 GHz this load runs at.  Measured (us, before:
+// the kernels these replaced): bf16 matrix B128 C256 28x28 14 x 14 468 -> 33;
+// bf16 table w = 14 B8 C96 100x167 40 -> 19; float32 table w = 14 B128 C256
+// 56x56 788 -> 298 (135 TFLOP/s of useful work; the float32 matrix cores peak at 153).
+// The two waves of a SIMD in opposite order (float32): 368 -> 305.
+template <class Tag, int RP, int S, bool MAT>
+__global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) void gen_fwd_kernel(
+    const typename Tag::S *__restrict__ x, const typename Tag::S *__restrict__ coef, typename Tag::S *__restrict__ y,
+    GenArgs a) {
+  typedef typename Tag::S E;
+  typedef GenCfg<Tag, RP, S> G;
+  typedef GenFwd<Tag, RP, S, MAT> F;
+  constexpr bool DEEP = F::AHEAD == 3;  // two stages of rows in flight
+  constexpr bool TWO = F::NOB == 2;
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned char *xbuf = smem, *obuf = smem + 2 * G::XB;
+  int *flag = reinterpret_cast<int *>(smem + F::FLAG_OFF);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, ln = lane & 15;
+  const uint32_t bid = die_major(blockIdx.x, gridDim.x);
+  const int64_t c = bid / (uint32_t)a.tiles_per_ch;
+  const int s0 = (int)(bid - (uint32_t)c * (uint32_t)a.tiles_per_ch) * a.spw;
+  const int nst = a.stages - s0 < a.spw ? a.stages - s0 : a.spw;
+  const uint32_t n0 = (uint32_t)s0 * G::CW;
+  const int v = gen_slot_window<G>(a, tid), hi = gen_slot_row<G>(a, tid);
+
+  // this thread's row of stage s (none past the last stage)
+  auto row = [&](int s) __attribute__((always_inline)) -> GRow { return s < nst ? gen_row(a, c, n0 + s * G::CW + v, hi) : GRow{0, 0}; };
+
+  // ---- stages 0 and 1 in flight, the table -> LDS, this wave's fragments
+  // (the table first, ahead of the rows: two entries per thread, K2 <= 961)
+  const int K2 = (2 * a.ww - 1) * (2 * a.wh - 1);
+  E tv[2] = {(E)0, (E)0};
+  if constexpr (!MAT) {
+    const E *tc = coef + c * K2;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = tid + i * kGenThreads < K2 ? tid + i * kGenThreads : K2 - 1;
+      tv[i] = tc[a.src == kSrcTableRev ? K2 - 1 - k : k];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  uint32_t d0[G::ND], d1[G::ND];
+  gen_load<Tag, RP>(a.numel, x, row(0), d0);
+  if constexpr (DEEP) gen_load<Tag, RP>(a.numel, x, row(1), d1);
+  __builtin_amdgcn_sched_barrier(0);
+  E *Ts = reinterpret_cast<E *>(obuf);
+  if constexpr (!MAT) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = tid + i * kGenThreads;
+      if (k < K2 + 10) Ts[k] = k < K2 ? tv[i] : (E)0;
+    }
+  }
+  if (tid < 5) flag[tid] = -1;
+  __syncthreads();
+  const int T = wave % S, sg = wave / S;  // tile pair, sub-tile group
+  GFrag fr[F::NPR][2][S];
+  uint32_t cmx = 0;  // largest coefficient magnitude seen (float32)
+  if constexpr (MAT) {
+    constexpr int ROOM = (int)F::LDS - G::XB;
+    if constexpr (Tag::W16) {
+      if (a.src == kSrcMat) gen_frags_mat16<Tag, RP, S, ROOM, false>(a, coef, c, T, tid, xbuf + G::XB, fr);
+      else gen_frags_mat16<Tag, RP, S, ROOM, true>(a, coef, c, T, tid, xbuf + G::XB, fr);
+    } else
+      gen_frags_mat32<RP, S>(a, coef, c, T, lane, fr, cmx);
+  } else {
+    cmx = gen_build_tb<Tag, RP, S>(a, Ts, xbuf + G::XB, F::LOW ? smem + F::LOW_OFF : xbuf + G::XB + 2 * G::TBB, tid);
+  }
+  if constexpr (!Tag::W16) {
+    // far coefficients: a huge one, or none of normal size though not all
+    // are zero
+    if (__any(cmx >= kFarHi) && lane == 0) flag[2] = 1;
+    if (__any(cmx != 0) && lane == 0) flag[3] = 1;
+    if (__any(cmx >= kFarLoCoef) && lane == 0) flag[4] = 1;
+  }
+  __syncthreads();
+  if constexpr (!MAT) gen_frags_tb<Tag, RP, S>(a, xbuf + G::XB, T, lane, fr);
+  bool cfar = false;
+  if constexpr (!Tag::W16) cfar = flag[2] > 0 || (flag[3] > 0 && flag[4] < 0);
+  auto write = [&](int s, uint32_t (&d)[G::ND]) __attribute__((always_inline)) {
+    const GRow r = row(s);
+    gen_tail<Tag, RP>(a.numel, r, d);
+    gen_mask<Tag, RP>(r.cols, d);
+#pragma unroll
+    for (int i = 0; i < G::ND; ++i) asm volatile("" : "+v"(d[i]));  // (the rows arrive here, on every path)
+    if (hi < G::KR) {
+      if (gen_write<Tag, RP, S>(xbuf + (s & 1) * G::XB, v, hi, d)) flag[s & 1] = s;
+    }
+  };
+  write(0, d0);
+  if constexpr (DEEP) {
+    gen_load<Tag, RP>(a.numel, x, row(2), d0);
+  } else {
+    gen_load<Tag, RP>(a.numel, x, row(1), d1);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  __syncthreads();
+
+  auto store = [&](int s) __attribute__((always_inline)) {
+    const GRow r = row(s);
+    if (r.cols > 0) {
+      const unsigned char *ob = obuf + (TWO ? (s & 1) * G::OB : 0) + (v * G::OP + hi * RP) * Tag::ES;
+      uint32_t o[G::ND];
+#pragma unroll
+      for (int i = 0; i < G::ND; i += 4) {
+        const uint4 u = *reinterpret_cast<const uint4 *>(ob + 4 * i);
+        o[i] = u.x; o[i + 1] = u.y; o[i + 2] = u.z; o[i + 3] = u.w;
+      }
+      gen_store<Tag, RP>(y, r, o);
+    }
+  };
+  // products of stage s: this wave's tile pair of its sub-tiles sg + i NG
+  const unsigned char *lowp = smem + F::LOW_OFF + gen_tb_lane<Tag, RP, S>(T, lane);
+  auto compute = [&](int s) __attribute__((always_inline)) {
+    const unsigned char *xs = xbuf + (s & 1) * G::XB;
+    unsigned char *os = obuf + (TWO ? (s & 1) * G::OB : 0);
+    if (sg >= G::NG) return;
+    bool far = false;
+    if constexpr (!Tag::W16) far = cfar || __builtin_amdgcn_readfirstlane(flag[s & 1]) == s;
+    constexpr int NJ = Tag::W16 ? G::SPW : 1;  // sub-tiles at a time
+#pragma unroll 1
+    for (int i0 = 0; i0 < G::SPW; i0 += NJ) {
+      const int u0 = sg + i0 * G::NG;
+      const unsigned char *xp = xs + ((16 * u0 + ln) * G::LDSW + 8 * g) * 2;
+      constexpr int US = 16 * G::NG * G::LDSW * 2;  // bytes from one of its sub-tiles to the next
+      f32x4 acc[NJ][2];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[j][0] = acc[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (Tag::W16) {
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            const GFrag xf = *reinterpret_cast<const GFrag *>(xp + j * US + 64 * k);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc[j][h] = mma<Tag>(fr[0][h][k], xf, acc[j][h]);
+          }
+        }
+      } else {
+        if (far) {
+          const uint32_t n = n0 + s * G::CW + 16 * u0 + ln;
+          acc[0][0] = gen_far_tile<RP, S>(a, x, coef, c, n, 32 * T + ln, g);
+          acc[0][1] = gen_far_tile<RP, S>(a, x, coef, c, n, 32 * T + 16 + ln, g);
+        } else {
+          // three sums per tile: hi hi, then the partial products of weight
+          // 2^-8 (mb) and 2^-16 (lb); the operands of step k + 1 are read
+          // while step k is multiplied
+          f32x4 mb[2], lb[2];
+          mb[0] = mb[1] = lb[0] = lb[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+          struct Ops {
+            GFrag xh, xm, xl, fl[2];
+          } op[2];
+          auto fetch = [&](int k, Ops &o) __attribute__((always_inline)) {
+            o.xh = *reinterpret_cast<const GFrag *>(xp + 64 * k);
+            o.xm = *reinterpret_cast<const GFrag *>(xp + G::PLANE + 64 * k);
+            o.xl = *reinterpret_cast<const GFrag *>(xp + 2 * G::PLANE + 64 * k);
+            if constexpr (F::LOW) {
+#pragma unroll
+              for (int h = 0; h < 2; ++h) o.fl[h] = *reinterpret_cast<const GFrag *>(lowp + gen_tb_step<RP>(h, k));
+            }
+          };
+          fetch(0, op[0]);
+#pragma unroll
+          for (int k = 0; k < S; ++k) {
+            const Ops &o = op[k & 1];
+            if (k + 1 < S) fetch(k + 1, op[(k + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            GFrag fl[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              if constexpr (F::LOW) {
+                fl[h] = o.fl[h];
+                if (k == S - 1 && (S - 1) * (32 / RP) + 8 * g / RP >= a.wh) fl[h] = GFrag{0, 0, 0, 0, 0, 0, 0, 0};
+              } else {
+                fl[h] = fr[2][h][k];
+              }
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc[0][h] = mma_bf16(fr[0][h][k], o.xh, acc[0][h]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) mb[h] = mma_bf16(fr[1][h][k], o.xh, mb[h]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) lb[h] = mma_bf16(fl[h], o.xh, lb[h]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) mb[h] = mma_bf16(fr[0][h][k], o.xm, mb[h]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) lb[h] = mma_bf16(fr[1][h][k], o.xm, lb[h]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) lb[h] = mma_bf16(fr[0][h][k], o.xl, lb[h]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[0][h][e] += mb[h][e] + lb[h][e];
+        }
+      }
+      // window ln of the sub-tile, positions 32 T + 16 h + 4 g .. + 3
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        E *o = reinterpret_cast<E *>(os) + (16 * (u0 + j * G::NG) + ln) * G::OP + 32 * T + 4 * g;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f32x4 v4 = acc[j][h];
+          if constexpr (Tag::W16)
+            *reinterpret_cast<uint2 *>(o + 16 * h) = uint2{pack2<Tag>(v4[0], v4[1]), pack2<Tag>(v4[2], v4[3])};
+          else
+            *reinterpret_cast<float4 *>(o + 16 * h) = float4{v4[0], v4[1], v4[2], v4[3]};
+        }
+      }
+    }
+  };
+  // stage s + 1 from d to LDS, stage s + AHEAD into d, the previous stage's
+  // rows out
+  auto move = [&](int s, uint32_t (&d)[G::ND]) __attribute__((always_inline)) {
+    // (also past the last stage, with zeros: no branch, see gen_load)
+    write(s + 1, d);
+    // (the stores before the loads: the next wait for rows, which counts the
+    // loads behind them only, then leaves those in flight)
+    if constexpr (TWO) {
+      if (s > 0) store(s - 1);
+    }
+    gen_load<Tag, RP>(a.numel, x, row(s + F::AHEAD), d);
+  };
+  // float32 (one workgroup per compute unit): the second wave of each SIMD
+  // takes a stage's copies before its products, the first one after, so that
+  // the copies' vector instructions run beside the other wave's products
+  // (two loops, not a branch inside one: the waits for rows stay exact)
+  auto stage = [&](auto early, int s, uint32_t (&da)[G::ND], uint32_t (&db)[G::ND]) __attribute__((always_inline)) {
+    compute(s);
+    if constexpr (!early.value) move(s, da);
+    __syncthreads();
+    if constexpr (!TWO) {
+      store(s);
+      __syncthreads();
+    }
+    if constexpr (early.value) move(s + 1, db);
+  };
+  auto run = [&](auto early) __attribute__((always_inline)) {
+    if constexpr (early.value) move(0, d1);
+    if constexpr (DEEP) {
+      for (int s = 0; s < nst; s += 2) {
+        stage(early, s, d1, d0);
+        if (s + 1 >= nst) break;
+        stage(early, s + 1, d0, d1);
+      }
+    } else {
+      for (int s = 0; s < nst; ++s) stage(early, s, d1, d1);
+    }
+  };
+  if (!Tag::W16 && wave >= kGenWaves / 2) {
+    run(std::true_type{});
+    // (the last move stored the last stage's rows)
+    return;
+  }
+  run(std::false_type{});
+  if constexpr (TWO) store(nst - 1);
+}
+
+}  // namespace wbmm

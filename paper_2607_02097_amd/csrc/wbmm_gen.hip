@@ -1,0 +1,134 @@
+// One instantiation unit of the general kernels (wbmm_gen.h): one dtype,
+// every row pitch and K-step count.
+// Compiled with -DWBMM_INST_TAG=<TagF32|TagBF16|TagF16>.
+#include "wbmm_gen.h"
+
+namespace wbmm {
+
+// Workgroups per channel: consecutive stages of one channel per workgroup,
+// as many workgroups as the chip holds at a time (slots) or a few rounds of
+// them, whichever leaves the fewest stages in a row; a workgroup's prologue
+// (coefficients, first rows) costs about ov stages.
+static void gen_plan(int64_t C, int64_t stages, int64_t slots, double ov, int64_t max_parts, int *spw, int *parts) {
+  double best = 1e300;
+  int64_t bp = 1;
+  for (int64_t p = 1; p <= stages && p <= max_parts; ++p) {
+    const int64_t per = cdiv64(stages, p);
+    const int64_t rounds = cdiv64(C * cdiv64(stages, per), slots);
+    const double cost = (double)rounds * ((double)per + ov);
+    if (cost < best - 1e-9) {
+      best = cost;
+      bp = p;
+    }
+    if (C * p > 8 * slots) break;
+  }
+  const int64_t per = cdiv64(stages, bp);
+  *spw = (int)per;
+  *parts = (int)cdiv64(stages, per);
+}
+
+static GenArgs gen_args(const Geom &g, int wh, int ww) {
+  GenArgs a;
+  a.C = g.C; a.H = g.H; a.W = g.W;
+  a.hw = g.H * g.W;
+  a.chw = g.C * a.hw;
+  a.numel = g.B * a.chw;
+  const int64_t nh = cdiv64(g.H, wh), nw = cdiv64(g.W, ww);
+  a.NW = (uint32_t)nw;
+  a.NHW = (uint32_t)(nh * nw);
+  a.dnw = fast_div(a.NW);
+  a.dnhw = fast_div(a.NHW);
+  a.N = (uint32_t)(g.B * nh * nw);
+  a.wh = wh; a.ww = ww;
+  a.stages = 0; a.spw = 0; a.tiles_per_ch = 0; a.src = 0; a.lgg = 0;
+  return a;
+}
+
+template <class Tag, int RP, int S>
+static hipError_t gen_fwd(const void *x, const void *coef, void *y, const Geom &g, int wh, int ww, int src,
+                          hipStream_t st) {
+  typedef typename Tag::S E;
+  typedef GenCfg<Tag, RP, S> G;
+  GenArgs a = gen_args(g, wh, ww);
+  a.src = src;
+  a.stages = (int)cdiv64(a.N, G::CW);
+  a.lgg = 0;
+  while ((2 << a.lgg) <= (int64_t)a.NW && (2 << a.lgg) <= G::CW) ++a.lgg;
+  const int ncu = compute_units();
+  const int wgs = src >= kSrcMat ? GenFwd<Tag, RP, S, true>::WGS : GenFwd<Tag, RP, S, false>::WGS;
+  gen_plan(g.C, a.stages, (int64_t)(ncu > 0 ? ncu : 256) * wgs, 1.5, 1 << 20, &a.spw, &a.tiles_per_ch);
+  const dim3 grid((unsigned)(g.C * a.tiles_per_ch)), block(kGenThreads);
+  constexpr size_t ltab = GenFwd<Tag, RP, S, false>::LDS, lmat = GenFwd<Tag, RP, S, true>::LDS;
+  static_assert(ltab <= 160 * 1024 && lmat <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
+  if (src >= kSrcMat)
+    gen_fwd_kernel<Tag, RP, S, true><<<grid, block, lmat, st>>>((const E *)x, (const E *)coef, (E *)y, a);
+  else
+    gen_fwd_kernel<Tag, RP, S, false><<<grid, block, ltab, st>>>((const E *)x, (const E *)coef, (E *)y, a);
+  return hipGetLastError();
+}
+
+// Tensors or matrices of fewer than 16 elements, shorter than the row loads
+// of the general kernels: one thread per output.
+template <class Tag>
+__global__ __launch_bounds__(256) void gen_small_kernel(const typename Tag::S *__restrict__ x,
+                                                        const typename Tag::S *__restrict__ coef,
+                                                        typename Tag::S *__restrict__ y, GenArgs a) {
+  for (int64_t e = blockIdx.x * 256LL + threadIdx.x; e < a.numel; e += (int64_t)gridDim.x * 256) {
+    const int64_t gx = e % a.W, gy = e / a.W % a.H, c = e / a.hw % a.C;
+    const int64_t wy = gy / a.wh, wx = gx / a.ww;
+    const typename Tag::S *plane = x + e / a.hw * a.hw;
+    float s = 0.f;
+    for (int hi = 0; hi < a.wh && wy * a.wh + hi < a.H; ++hi)
+      for (int xi = 0; xi < a.ww && wx * a.ww + xi < a.W; ++xi) {
+        const typename Tag::S m = coef[gen_coef<Tag>(a, c, hi, xi, (int)(gy - wy * a.wh), (int)(gx - wx * a.ww))];
+        const typename Tag::S v = plane[(wy * a.wh + hi) * a.W + wx * a.ww + xi];
+        if constexpr (Tag::W16) s += to_f32<Tag>(v) * to_f32<Tag>(m);
+        else s += v * m;
+      }
+    if constexpr (Tag::W16) y[e] = (u16)(pack2<Tag>(s, 0.f) & 0xffffu);
+    else y[e] = s;
+  }
+}
+
+template <class Tag>
+static hipError_t run_gen_fwd(const void *x, const void *coef, void *y, const Geom &g, int wh, int ww, int src,
+                              hipStream_t st) {
+  const int64_t d = (int64_t)wh * ww;
+  GenArgs a = gen_args(g, wh, ww);
+  if (a.numel < 16 || (src >= kSrcMat && g.C * d * d < 16)) {
+    typedef typename Tag::S E;
+    a.src = src;
+    const int64_t blocks = cdiv64(a.numel, 256);
+    gen_small_kernel<Tag><<<dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st>>>(
+        (const E *)x, (const E *)coef, (E *)y, a);
+    return hipGetLastError();
+  }
+  if (ww <= 8) {
+    switch ((wh + 3) / 4) {
+      case 1: return gen_fwd<Tag, 8, 1>(x, coef, y, g, wh, ww, src, st);
+      case 2: return gen_fwd<Tag, 8, 2>(x, coef, y, g, wh, ww, src, st);
+      case 3: return gen_fwd<Tag, 8, 3>(x, coef, y, g, wh, ww, src, st);
+      case 4: return gen_fwd<Tag, 8, 4>(x, coef, y, g, wh, ww, src, st);
+    }
+  } else {
+    switch ((wh + 1) / 2) {
+      case 1: return gen_fwd<Tag, 16, 1>(x, coef, y, g, wh, ww, src, st);
+      case 2: return gen_fwd<Tag, 16, 2>(x, coef, y, g, wh, ww, src, st);
+      case 3: return gen_fwd<Tag, 16, 3>(x, coef, y, g, wh, ww, src, st);
+      case 4: return gen_fwd<Tag, 16, 4>(x, coef, y, g, wh, ww, src, st);
+      case 5: return gen_fwd<Tag, 16, 5>(x, coef, y, g, wh, ww, src, st);
+      case 6: return gen_fwd<Tag, 16, 6>(x, coef, y, g, wh, ww, src, st);
+      case 7: return gen_fwd<Tag, 16, 7>(x, coef, y, g, wh, ww, src, st);
+      case 8: return gen_fwd<Tag, 16, 8>(x, coef, y, g, wh, ww, src, st);
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
+template <>
+hipError_t GenEntry<WBMM_INST_TAG>::forward(const void *x, const void *coef, void *y, const Geom &g, int wh, int ww,
+                                            int src, hipStream_t st) {
+  return run_gen_fwd<WBMM_INST_TAG>(x, coef, y, g, wh, ww, src, st);
+}
+
+}  // namespace wbmm

@@ -83,6 +83,18 @@ hipError_t launch_dense_backward_matrix(Dt dt, const void *x, const void *dy, fl
 hipError_t launch_dense_bin(const float *dm, float *dtable, int64_t C, int wh, int ww,
                             hipStream_t stream);
 
+// General kernels (wbmm_gen.hip): y = x M per w_h x w_w window, the
+// coefficients from the table (src 0, or 1: read back to front) or from a
+// matrix [C, d, d] (2, or 3: transposed).  g.w is unused.
+struct TagF32;
+struct TagBF16;
+struct TagF16;
+template <class Tag>
+struct GenEntry {
+  static hipError_t forward(const void *x, const void *coef, void *y, const Geom &g, int wh, int ww, int src,
+                            hipStream_t stream);
+};
+
 // Per-(dtype, window) entry points, defined by the wbmm_inst.hip
 // translation units and collected into tables by wbmm_dispatch.cpp.
 typedef hipError_t (*FwdFn)(const void *, const void *, void *, const Geom &, bool, hipStream_t);

@@ -56,6 +56,8 @@
 // rows), and four copy waves bring the next stages in, with one workgroup
 // barrier per stage.  Otherwise a
 // four-wave workgroup per (channel, slab) runs the same products in turn.
+// Float32 windows of 9 and more, and 16-bit maps that the windows do not
+// tile, take the general kernels of wbmm_gen.h instead (kGenWindow, gen_map).
 // The hierarchical form (global window 2 wl plus local wl sub-windows) adds
 // local-block products to the forward and input gradient and splits the
 // table-gradient accumulators by row halves to bin both tables in one pass.
@@ -2732,8 +2734,8 @@ static bool img_layout(const Geom &g, const void *x, const void *y, ImgArgs &ia)
 }
 
 template <class Tag, int WIN>
-static hipError_t run_forward(const void *x, const void *t, void *y, const Geom &g, bool rev,
-                              hipStream_t st) {
+static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const Geom &g, bool rev,
+                                    hipStream_t st) {
   typedef typename Tag::S S;
   KArgs a = make_args(g);
   a.tile = pick_fwd_tile<Tag, WIN>(g);
@@ -2774,6 +2776,42 @@ static hipError_t run_forward(const void *x, const void *t, void *y, const Geom 
   else
     wbmm_fwd_kernel<Tag, WIN, false><<<grid, dim3(kFwdThreads), lds, st>>>((const S *)x, (const S *)t, nullptr, (S *)y, a);
   return hipGetLastError();
+}
+
+// Which forwards and input gradients (plain form) the general kernels of
+// wbmm_gen.h take:
+// * float32 windows of 9 and more, every map: the products as bf16 parts
+//   against the float32 matrix products of the row kernel, one table read per
+//   product (w = 14, us: B1 C8 28x28 33.2 -> 8.9, B64 C192 28x28 99 -> 40, B128
+//   C256 56x56 788 -> 305; w = 10: 14.6 -> 7.9, B64 C192 20x20 30.9 -> 30.6, B32
+//   C256 37x53 112 -> 76).  Below 9 the row kernel has less padding and wins
+//   (w = 5: 58 against 69 at B32 C256 37x53, 3.9 against 5.2 at B1 C8 20x20).
+//   By the window alone, so that the fused backward's dX, which takes the
+//   same kernel, equals wbmm_backward_input bit for bit.
+// * 16-bit windows of 7 and more on maps they do not tile: the row kernel
+//   reads cut and odd rows element by element (w = 14, B8 C96 100x167 40.3 ->
+//   19.4 us, B1 C64 75x100 8.0 -> 5.2; w = 7 23.9 -> 18.4 and 4.7 -> 4.1).  On
+//   maps they tile its whole-row copies are shorter (B128 C384 14x14 11.0
+//   against 14.5), and for w = 5 the two are equal.  The same products in
+//   the same order: the same bits.  (The general kernel needs a tensor of 16
+//   elements.)
+template <class Tag, int WIN>
+constexpr bool kGenWindow = !Tag::W16 && rp_of(WIN) == 16;
+
+template <class Tag, int WIN>
+static bool gen_map(const Geom &g) {
+  return Tag::W16 && WIN >= 7 && (g.H % WIN != 0 || g.W % WIN != 0) && g.B * g.C * g.H * g.W >= 16;
+}
+
+template <class Tag, int WIN>
+static hipError_t run_forward(const void *x, const void *t, void *y, const Geom &g, bool rev,
+                              hipStream_t st) {
+  if constexpr (kGenWindow<Tag, WIN>) {
+    return GenEntry<Tag>::forward(x, t, y, g, WIN, WIN, rev ? 1 : 0, st);
+  } else {
+    if (gen_map<Tag, WIN>(g)) return GenEntry<Tag>::forward(x, t, y, g, WIN, WIN, rev ? 1 : 0, st);
+    return run_forward_fixed<Tag, WIN>(x, t, y, g, rev, st);
+  }
 }
 
 // Hierarchical form, window WIN = 2 wl: y = x M_fused per window (both tables
@@ -2954,8 +2992,8 @@ static hipError_t run_dtable(const void *x, const void *dy, float *dt, void *ws,
 }
 
 template <class Tag, int WIN>
-static hipError_t run_backward(const void *x, const void *dy, const void *t, void *dx, float *dt, void *ws,
-                               const Geom &g, hipStream_t st) {
+static hipError_t run_backward_fused(const void *x, const void *dy, const void *t, void *dx, float *dt, void *ws,
+                                     const Geom &g, hipStream_t st) {
   typedef typename Tag::S S;
   KArgs a = make_args(g);
   const DtPlan p = plan_dt<Tag, WIN>(g);
@@ -2998,6 +3036,19 @@ static hipError_t run_backward(const void *x, const void *dy, const void *t, voi
   wbmm_bwd_kernel<Tag, WIN, false><<<grid, dim3(kThreads), lds, st>>>((const S *)x, (const S *)dy, (const S *)t,
                                                                       (S *)dx, dt, part, a);
   return sum_slabs(part, dt, g.C * table_len<WIN>(), nullptr, nullptr, 0, p.slabs, st);
+}
+
+template <class Tag, int WIN>
+static hipError_t run_backward(const void *x, const void *dy, const void *t, void *dx, float *dt, void *ws,
+                               const Geom &g, hipStream_t st) {
+  if constexpr (kGenWindow<Tag, WIN>) {
+    // dY is read twice, which costs less than the fused kernels' float32
+    // products (w = 14, B128 C192 28x28: 279 us fused, 184 as two launches)
+    const hipError_t e = run_forward<Tag, WIN>(dy, t, dx, g, true, st);
+    return e != hipSuccess ? e : run_dtable<Tag, WIN>(x, dy, dt, ws, g, st);
+  } else {
+    return run_backward_fused<Tag, WIN>(x, dy, t, dx, dt, ws, g, st);
+  }
 }
 
 // Hierarchical form (global window WIN = 2 wl): one channel-stream pass when

@@ -1,0 +1,151 @@
+"""GPU tests of the general kernels (any map, rectangular windows, cached
+matrices, float32 as bf16 parts) against plain float64 torch, at the edges of
+their stages, tiles and row loads."""
+import pytest
+import torch
+
+from helpers import TORCH_DTYPE
+from paper_2607_02097_amd import binding as W
+
+pytestmark = pytest.mark.gpu
+
+# One rounding of the result (half an ulp: 2^-9, 2^-12) plus the float32 sums
+# of at most 256 products: |error| <= half ulp |y| + 256 2^-24 sum |x m|, taken
+# relative to sum |x m| per output, with a factor of two in hand.  float32:
+# what the six partial products leave out is below 2^-24 of each product.
+REL = {"f32": 2.0 ** -16, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}
+# and half the spacing of the smallest values (float16's subnormals, 2^-24)
+ABS = {"f32": 0.0, "bf16": 0.0, "f16": 2.0 ** -25}
+
+
+def windows(v, wh, ww):
+    B, C, H, Wd = v.shape
+    v = torch.nn.functional.pad(v, (0, -Wd % ww, 0, -H % wh))
+    nh, nw = v.shape[2] // wh, v.shape[3] // ww
+    return v.reshape(B, C, nh, wh, nw, ww).permute(1, 0, 2, 4, 3, 5).reshape(C, B * nh * nw, wh * ww)
+
+
+def unwindows(v, shape, wh, ww):
+    B, C, H, Wd = shape
+    nh, nw = -(-H // wh), -(-Wd // ww)
+    v = v.reshape(C, B, nh, nw, wh, ww).permute(1, 0, 2, 4, 3, 5)
+    return v.reshape(B, C, nh * wh, nw * ww)[:, :, :H, :Wd]
+
+
+def index(wh, ww):
+    p = torch.arange(wh * ww)
+    h, x = p // ww, p % ww
+    return (h[:, None] - h[None] + wh - 1) * (2 * ww - 1) + x[:, None] - x[None] + ww - 1
+
+
+def data(B, C, H, Wd, wh, ww, dtype, seed):
+    g = torch.Generator().manual_seed(seed)
+    td = TORCH_DTYPE[dtype]
+    x = torch.randn((B, C, H, Wd), generator=g).to(td)
+    t = (0.02 * torch.randn((C, (2 * wh - 1) * (2 * ww - 1)), generator=g)).to(td)
+    return x, t
+
+
+def check(got, x, m, wh, ww, dtype, label):
+    """got against x m per window, each output relative to its sum |x m|."""
+    xw = windows(x.double(), wh, ww)
+    want = unwindows(xw @ m, x.shape, wh, ww)
+    scale = unwindows(xw.abs() @ m.abs(), x.shape, wh, ww)
+    err = (got.double().cpu() - want).abs()
+    worst = float(((err - ABS[dtype]) / (scale + 1e-30)).max())
+    print(label, "worst %.2e" % worst, flush=True)
+    assert worst <= REL[dtype], label
+
+
+# K steps 1..8 of both row pitches, their remainders, one stage and several
+WINDOWS = [(1, 1), (1, 16), (2, 9), (3, 8), (4, 7), (5, 16), (7, 14), (8, 8), (9, 3), (10, 9), (12, 12), (13, 8),
+           (14, 7), (14, 14), (15, 15), (16, 16)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("win", WINDOWS, ids=lambda w: "%dx%d" % w)
+def test_matrix_and_table_products(win, dtype):
+    """Dense forward and transposed product with an arbitrary matrix, and the
+    rectangular-window forms with the matrix built from a table: maps smaller
+    than a window, cut windows, odd widths, several stages."""
+    wh, ww = win
+    for B, C, H, Wd in ((1, 2, max(wh - 1, 4), ww + 1), (3, 3, 2 * wh + 1, 3 * ww - 1), (2, 1, 6 * wh, 11 * ww)):
+        x, t = data(B, C, H, Wd, wh, ww, dtype, seed=wh * 31 + ww)
+        g = torch.Generator().manual_seed(5)
+        m = (0.1 * torch.randn((C, wh * ww, wh * ww), generator=g)).to(TORCH_DTYPE[dtype])
+        xd, md, td = x.cuda(), m.cuda(), t.cuda()
+        label = "%s %s %s" % (dtype, win, (B, C, H, Wd))
+        check(W.wbmm_dense_forward(xd, md, wh, ww), x, m.double(), wh, ww, dtype, "dense " + label)
+        check(W.wbmm_dense_backward_input(xd, md, wh, ww), x, m.double().transpose(1, 2), wh, ww, dtype,
+              "dense^T " + label)
+        mt = t.double()[:, index(wh, ww)]
+        check(W.wbmm_rect_forward(xd, td, wh, ww), x, mt, wh, ww, dtype, "rect " + label)
+        check(W.wbmm_rect_backward_input(xd, td, wh, ww), x, mt.transpose(1, 2), wh, ww, dtype, "rect^T " + label)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (1, 3, 1, 5), (1, 1, 3, 5), (2, 2, 2, 2), (1, 1, 4, 4)],
+                         ids=lambda s: "B%dC%dH%dW%d" % s)
+def test_tensors_shorter_than_a_row_load(shape, dtype):
+    """Fewer than, and exactly, the sixteen elements that a row load takes, in
+    the map and (windows of one to three positions) in the matrix."""
+    B, C, H, Wd = shape
+    for w in (2, 7, 14):
+        x, t = data(B, C, H, Wd, w, w, dtype, seed=w)
+        m = t.double()[:, index(w, w)]
+        check(W.wbmm_forward(x.cuda(), t.cuda(), w), x, m, w, w, dtype, "fwd %s %s w%d" % (dtype, shape, w))
+        check(W.wbmm_rect_forward(x.cuda(), t.cuda(), w, w), x, m, w, w, dtype, "rect %s %s w%d" % (dtype, shape, w))
+    for C in (1, 3, 15, 16):
+        for wh, ww in ((1, 1), (1, 3), (2, 1)):
+            x, t = data(2, C, 9, 20, wh, ww, dtype, seed=C)
+            m = t.double()[:, index(wh, ww)]
+            check(W.wbmm_rect_forward(x.cuda(), t.cuda(), wh, ww), x, m, wh, ww, dtype, "small matrix %d %dx%d" % (C, wh, ww))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("w", [7, 8, 9, 13, 14, 16])
+def test_cut_maps_equal_padded_maps(w, dtype):
+    """A map cut inside its last windows takes the general kernel, the same
+    map padded with zeros to whole windows the fixed-layout kernels: the same
+    products in the same order, so the same bits."""
+    B, C, nh, nw = 2, 3, 4, 4
+    H, Wd = nh * w - 1, nw * w - 3
+    x, t = data(B, C, H, Wd, w, w, dtype, seed=w)
+    xd, td = x.cuda(), t.cuda()
+    xp = torch.nn.functional.pad(xd, (0, nw * w - Wd, 0, nh * w - H)).contiguous()
+    for f in (W.wbmm_forward, W.wbmm_backward_input):
+        assert torch.equal(f(xd, td, w), f(xp, td, w)[:, :, :H, :Wd])
+
+
+@pytest.mark.parametrize("w", [9, 14, 16])
+def test_float32_range(w):
+    """float32 rows and tables outside the range of the bf16 parts take
+    float32 products: infinities and NaN reach exactly the outputs of their
+    window, huge, tiny and denormal values keep float32's precision, and a
+    zero table or zero rows give zeros."""
+    B, C, H, Wd = 3, 2, 2 * w, 3 * w
+    x, t = data(B, C, H, Wd, w, w, "f32", seed=w)
+    m = t.double()[:, index(w, w)]
+    for s in (2.0 ** 70, 2.0 ** -100, 2.0 ** -120):
+        xs = x * s
+        check(W.wbmm_forward(xs.cuda(), t.cuda(), w) / s, xs / s, m, w, w, "f32", "x scaled by %g" % s)
+    for s in (2.0 ** 66, 2.0 ** -70):
+        check(W.wbmm_forward(x.cuda(), (t * s).cuda(), w) / s, x, m, w, w, "f32", "table scaled by %g" % s)
+    # a few rows far out of range beside ordinary ones
+    xm = x.clone()
+    xm[1, 0, 3] *= 2.0 ** 80
+    xm[2, 1, w + 1] *= 2.0 ** -110
+    check(W.wbmm_forward(xm.cuda(), t.cuda(), w), xm, m, w, w, "f32", "mixed rows")
+    for bad in (float("inf"), float("-inf"), float("nan")):
+        xb = x.clone()
+        xb[1, 1, w + 2, 5] = bad
+        y = W.wbmm_forward(xb.cuda(), t.cuda(), w).cpu()
+        hit = torch.zeros_like(xb, dtype=torch.bool)
+        hit[1, 1, w:2 * w, 0:w] = True
+        assert not torch.isfinite(y[hit]).any() and torch.isfinite(y[~hit]).all()
+        if bad != bad:
+            assert torch.isnan(y[hit]).all()
+        else:
+            assert torch.isinf(y[hit]).all()
+    assert not W.wbmm_forward(torch.zeros_like(x).cuda(), t.cuda(), w).any()
+    assert not W.wbmm_forward(x.cuda(), torch.zeros_like(t).cuda(), w).any()
