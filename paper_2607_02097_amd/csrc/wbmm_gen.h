@@ -174,13 +174,30 @@ __device__ __attribute__((always_inline)) inline void gen_tail(int64_t numel, co
 }
 
 // Zero past the row's columns (apart from the loads, so that the wait for
-// them comes where the row is used).
+// them comes where the row is used): masks for 0 .. RP columns in LDS, since
+// comparing every column costs five instructions a dword.
 template <class Tag, int RP>
-__device__ __attribute__((always_inline)) inline void gen_mask(int cols, uint32_t (&d)[RP * Tag::ES / 4]) {
+__host__ __device__ constexpr int gen_mask_bytes() { return (RP + 1) * RP * Tag::ES; }
+
+template <class Tag, int RP>
+__device__ __attribute__((always_inline)) inline void gen_mask_table(uint32_t *tab, int tid) {
+  constexpr int ND = RP * Tag::ES / 4;
+  static_assert((RP + 1) * ND <= kGenThreads, "one entry per thread");
+  const int cols = tid / ND, i = tid % ND;
+  if (cols <= RP) {
+    if constexpr (Tag::W16) tab[tid] = cols > 2 * i + 1 ? ~0u : cols > 2 * i ? 0xffffu : 0u;
+    else tab[tid] = cols > i ? ~0u : 0u;
+  }
+}
+
+template <class Tag, int RP>
+__device__ __attribute__((always_inline)) inline void gen_mask(const uint32_t *tab, int cols,
+                                                               uint32_t (&d)[RP * Tag::ES / 4]) {
+  constexpr int ND = RP * Tag::ES / 4;
 #pragma unroll
-  for (int i = 0; i < RP * Tag::ES / 4; ++i) {
-    if constexpr (Tag::W16) d[i] = cols > 2 * i + 1 ? d[i] : (cols > 2 * i ? (d[i] & 0xffffu) : 0u);
-    else d[i] = cols > i ? d[i] : 0u;
+  for (int i = 0; i < ND; i += 4) {
+    const uint4 m = *reinterpret_cast<const uint4 *>(tab + cols * ND + i);
+    d[i] &= m.x; d[i + 1] &= m.y; d[i + 2] &= m.z; d[i + 3] &= m.w;
   }
 }
 
@@ -402,7 +419,8 @@ __device__ __attribute__((always_inline)) inline GFrag gen_tr_frag(const unsigne
 // memory took most of the kernel: B128 C256 28x28, 14 x 14 windows, bf16.)
 template <class Tag, int RP, int S, int ROOM, bool TRANS>
 __device__ __attribute__((always_inline)) inline void gen_frags_mat16(const GenArgs &a, const u16 *coef, int64_t c,
-                                                                      int T, int tid, unsigned char *lds,
+                                                                      int T, int tid, const uint32_t *masks,
+                                                                      unsigned char *lds,
                                                                       GFrag (&fr)[1][2][S]) {
   typedef GenCfg<Tag, RP, S> G;
   constexpr int CKB = G::CKB;
@@ -428,7 +446,7 @@ __device__ __attribute__((always_inline)) inline void gen_frags_mat16(const GenA
     for (int q = 0; q < NCK; ++q) {
       const GRow r = row(c0 + q);
       gen_tail<Tag, RP>(numel, r, v[q]);
-      gen_mask<Tag, RP>(r.cols, v[q]);
+      gen_mask<Tag, RP>(masks, r.cols, v[q]);
       if (kk < 32) {
         unsigned char *p = lds + q * CKB + (kk * G::LDSW + ho * RP) * 2;
 #pragma unroll
@@ -545,15 +563,16 @@ struct GenFwd {
   static constexpr int NPR = LOW ? 2 : G::NPL;          // planes in registers
   static constexpr bool TIGHT = !Tag::W16 && MAT && S >= 5;  // registers short
   static constexpr int AHEAD = TIGHT ? 2 : 3;           // stages from a row's load to its use, + 1
-  static constexpr int FIX = (LOW ? G::TBB : 0) + 32;   // blocks, flags
+  static constexpr int FIX = (LOW ? G::TBB : 0) + gen_mask_bytes<Tag, RP>() + 32;  // blocks, masks, flags
   static constexpr int NOB = 2 * G::XB + 2 * G::OB + FIX <= 160 * 1024 ? 2 : 1;  // result buffers
-  static constexpr int LOW_OFF = 2 * G::XB + NOB * G::OB;
-  static constexpr int FLAG_OFF = LOW_OFF + (LOW ? G::TBB : 0);
+  static constexpr int MROOM = (160 * 1024 - FIX - G::XB) / G::CKB * G::CKB;
+  static constexpr int MEND = Tag::W16 && MAT ? G::XB + (MROOM < S * G::CKB ? MROOM : S * G::CKB) : 0;
   // 16-bit matrices: LDS for as many chunks as there are, one workgroup per
   // compute unit
-  static constexpr int MROOM = (160 * 1024 - G::XB) / G::CKB * G::CKB;
-  static constexpr int MEND = G::XB + (MROOM < S * G::CKB ? MROOM : S * G::CKB);
-  static constexpr size_t LDS = Tag::W16 && MAT && MEND > FLAG_OFF + 32 ? (size_t)MEND : (size_t)FLAG_OFF + 32;
+  static constexpr int LOW_OFF = 2 * G::XB + NOB * G::OB > MEND ? 2 * G::XB + NOB * G::OB : MEND;
+  static constexpr int MASK_OFF = LOW_OFF + (LOW ? G::TBB : 0);
+  static constexpr int FLAG_OFF = MASK_OFF + gen_mask_bytes<Tag, RP>();
+  static constexpr size_t LDS = (size_t)FLAG_OFF + 32;
   static constexpr int WGS = Tag::W16 && LDS <= 80 * 1024 ? 2 : 1;  // workgroups per compute unit
 };
 
@@ -581,6 +600,7 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char *xbuf = smem, *obuf = smem + 2 * G::XB;
   int *flag = reinterpret_cast<int *>(smem + F::FLAG_OFF);
+  uint32_t *masks = reinterpret_cast<uint32_t *>(smem + F::MASK_OFF);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, ln = lane & 15;
@@ -620,15 +640,16 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
     }
   }
   if (tid < 5) flag[tid] = -1;
+  gen_mask_table<Tag, RP>(masks, tid);
   __syncthreads();
   const int T = wave % S, sg = wave / S;  // tile pair, sub-tile group
   GFrag fr[F::NPR][2][S];
   uint32_t cmx = 0;  // largest coefficient magnitude seen (float32)
   if constexpr (MAT) {
-    constexpr int ROOM = (int)F::LDS - G::XB;
+    constexpr int ROOM = F::LOW_OFF - G::XB;
     if constexpr (Tag::W16) {
-      if (a.src == kSrcMat) gen_frags_mat16<Tag, RP, S, ROOM, false>(a, coef, c, T, tid, xbuf + G::XB, fr);
-      else gen_frags_mat16<Tag, RP, S, ROOM, true>(a, coef, c, T, tid, xbuf + G::XB, fr);
+      if (a.src == kSrcMat) gen_frags_mat16<Tag, RP, S, ROOM, false>(a, coef, c, T, tid, masks, xbuf + G::XB, fr);
+      else gen_frags_mat16<Tag, RP, S, ROOM, true>(a, coef, c, T, tid, masks, xbuf + G::XB, fr);
     } else
       gen_frags_mat32<RP, S>(a, coef, c, T, lane, fr, cmx);
   } else {
@@ -648,7 +669,7 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
   auto write = [&](int s, uint32_t (&d)[G::ND]) __attribute__((always_inline)) {
     const GRow r = row(s);
     gen_tail<Tag, RP>(a.numel, r, d);
-    gen_mask<Tag, RP>(r.cols, d);
+    gen_mask<Tag, RP>(masks, r.cols, d);
 #pragma unroll
     for (int i = 0; i < G::ND; ++i) asm volatile("" : "+v"(d[i]));  // (the rows arrive here, on every path)
     if (hi < G::KR) {
@@ -823,6 +844,360 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
   }
   run(std::false_type{});
   if constexpr (TWO) store(nst - 1);
+}
+
+// ---------------------------------------------------- table gradient
+// dT = the sums of X^T dY over windows along equal offsets.  K = windows: the
+// position-major fragments of x and dy come from transposing reads of their
+// window-major stages.  Wave (ph, pg) multiplies input tiles ph S .. + S - 1
+// with a quarter of the output tiles; products of tile pairs with equal
+// difference share an accumulator (S + NPO - 1 of them), so a wave reads
+// S + NPO fragments for S NPO products.  At the end every wave sums the
+// diagonals of its accumulators, and the waves' sums are added in order.
+//
+// DX (16-bit): the fused backward.  The same stages feed the input gradient
+// dY M^T as in the forward kernel (wave T holds the reversed table's
+// fragments of output positions 32 T .. + 31), so dY is read once and x, dy and
+// dx move in one launch; the rows of dX are stored a stage later.  Stages,
+// accumulators and sums are the same with and without DX, and the products of
+// dX those of the forward kernel: the same bits either way.
+//
+// What bounds it: 16-bit, memory and the copies' vector instructions (one
+// 8-wave workgroup per compute unit, two stages of rows in flight, row
+// addresses kept from load to store, columns masked from a table in LDS:
+// B8 C96 100x167 w = 14 fused 38 -> 35 us, B64 C96 56x56 w = 7 33 -> 29; as
+// separate launches 40 and 36, the four-wave kernels 69 and 46); float32, the
+// matrix cores and the splitting of the rows, which one LDS buffer per stage
+// leaves beside no products (B128 C192 28x28 w = 14: 85 us, float32 products
+// 122).
+template <class Tag, int RP, int S, bool DX>
+struct GenDt {
+  typedef GenCfg<Tag, RP, S> G;
+  static_assert(!DX || Tag::W16, "fused backward: 16-bit");
+  static constexpr int NPO = cdiv(G::NT, 4);       // output tiles of a wave (at most)
+  static constexpr int NR = S + NPO - 1;           // accumulators: i - q + NPO - 1
+  static constexpr int KST = G::CW / 32;           // K steps per stage
+  static constexpr int NBUF = Tag::W16 ? 2 : 1;    // stages in LDS
+  // float32: the smaller partial products in sums of their own where the
+  // registers allow
+  static constexpr bool LOWACC = !Tag::W16 && S <= 6;
+  static constexpr int STAGE = 2 * G::XB;          // x and dy
+  static constexpr int R = 16 / RP;                // window rows per tile
+  static constexpr int NBIN = R * R * 2 * RP;      // diagonals of a tile's R x R blocks, padded
+  static constexpr int BT = 4;                     // tiles binned at a time
+  static constexpr int SCR = kGenWaves * BT * kBinTile * 4;
+  static constexpr int BINS = kGenWaves * NR * NBIN * 4;
+  static constexpr int O_OFF = NBUF * STAGE;       // two result buffers
+  static constexpr int END = O_OFF + (DX ? 2 * G::OB : 0);
+  static constexpr int MASK_OFF = END > SCR + BINS ? END : SCR + BINS;
+  static constexpr int FLAG_OFF = MASK_OFF + gen_mask_bytes<Tag, RP>();
+  static constexpr size_t LDS = (size_t)FLAG_OFF + 16;
+};
+
+// First output tile of wave (ph, pg): quarters rounded down for one half of
+// the input tiles and up for the other, so that the two waves of a SIMD (pg
+// equal) have the same work together.
+template <int NT>
+__device__ __attribute__((always_inline)) inline int gen_dt_cut(int ph, int pg) {
+  return (NT * pg + (ph ? 3 : 0)) >> 2;
+}
+
+template <class Tag, int RP, int S, bool DX>
+__global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
+    const typename Tag::S *__restrict__ x, const typename Tag::S *__restrict__ dy,
+    const typename Tag::S *__restrict__ tab, typename Tag::S *__restrict__ dxo, float *__restrict__ out, GenArgs a) {
+  typedef GenCfg<Tag, RP, S> G;
+  typedef GenDt<Tag, RP, S, DX> D;
+  constexpr int NPO = D::NPO, NR = D::NR;
+  extern __shared__ __align__(16) unsigned char smem[];
+  int *flag = reinterpret_cast<int *>(smem + D::FLAG_OFF);
+  uint32_t *masks = reinterpret_cast<uint32_t *>(smem + D::MASK_OFF);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, ln = lane & 15;
+  const uint32_t bid = die_major(blockIdx.x, gridDim.x);
+  const int64_t c = bid / (uint32_t)a.tiles_per_ch;
+  const int slab = (int)(bid - (uint32_t)c * (uint32_t)a.tiles_per_ch);
+  const int s0 = slab * a.spw;
+  const int nst = a.stages - s0 < a.spw ? a.stages - s0 : a.spw;
+  const uint32_t n0 = (uint32_t)s0 * G::CW;
+  const int v = gen_slot_window<G>(a, tid), hi = gen_slot_row<G>(a, tid);
+  const int ph = wave >> 2, pg = wave & 3;
+  const int po0 = gen_dt_cut<G::NT>(ph, pg), npo = gen_dt_cut<G::NT>(ph, pg + 1) - po0;
+
+  auto row = [&](int s) __attribute__((always_inline)) -> GRow {
+    return s < nst ? gen_row(a, c, n0 + s * G::CW + v, hi) : GRow{0, 0};
+  };
+  f32x4 acc[NR], lowacc[D::LOWACC ? NR : 1];
+  auto &low = [&]() -> auto & {
+    if constexpr (D::LOWACC) return lowacc;
+    else return acc;
+  }();
+#pragma unroll
+  for (int r = 0; r < NR; ++r) acc[r] = low[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // this thread's row of one stage, of x and dy
+  struct Rows {
+    GRow r;
+    uint32_t x[G::ND], g[G::ND];
+  };
+  auto load = [&](int s, Rows &d) __attribute__((always_inline)) {
+    d.r = row(s);
+    gen_load<Tag, RP>(a.numel, x, d.r, d.x);
+    gen_load<Tag, RP>(a.numel, dy, d.r, d.g);
+  };
+  auto write = [&](int s, unsigned char *st, Rows &d) __attribute__((always_inline)) {
+    gen_tail<Tag, RP>(a.numel, d.r, d.x);
+    gen_tail<Tag, RP>(a.numel, d.r, d.g);
+    gen_mask<Tag, RP>(masks, d.r.cols, d.x);
+    gen_mask<Tag, RP>(masks, d.r.cols, d.g);
+#pragma unroll
+    for (int i = 0; i < G::ND; ++i) asm volatile("" : "+v"(d.x[i]), "+v"(d.g[i]));  // (the rows arrive here, on every path)
+    if (hi < G::KR) {
+      const bool fx = gen_write<Tag, RP, S>(st, v, hi, d.x), fg = gen_write<Tag, RP, S>(st + G::XB, v, hi, d.g);
+      if (fx || fg) flag[s & 1] = s;
+    }
+  };
+  auto products = [&](int s, const unsigned char *st) __attribute__((always_inline)) {
+    if constexpr (Tag::W16) {
+#pragma unroll
+      for (int ks = 0; ks < D::KST; ++ks) {
+        const unsigned char *xt = st + ks * 32 * G::LDSW * 2, *gt = xt + G::XB;
+        GFrag bf[NPO];
+#pragma unroll
+        for (int q = 0; q < NPO; ++q) bf[q] = dt_frag16<G::LDSW>(gt, q < npo ? po0 + q : po0, lane);
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+          const GFrag af = dt_frag16<G::LDSW>(xt, ph * S + i, lane);
+#pragma unroll
+          for (int q = 0; q < NPO; ++q)
+            if (q < npo) acc[i - q + NPO - 1] = mma<Tag>(af, bf[q], acc[i - q + NPO - 1]);
+        }
+      }
+    } else if (__builtin_amdgcn_readfirstlane(flag[s & 1]) == s) {
+      // float32 products of a stage with far rows, from global memory
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+#pragma unroll 1
+        for (int q = 0; q < npo; ++q) {
+          const int i = r + q - (NPO - 1);
+          if (i < 0 || i >= S) continue;
+          const int pa = 16 * (ph * S + i) + ln, pb = 16 * (po0 + q) + ln;
+#pragma unroll 1
+          for (int w = 0; w < G::CW; w += 4) {
+            const uint32_t n = n0 + s * G::CW + w + g;
+            const GRow ra = gen_row(a, c, n, pa / RP), rb = gen_row(a, c, n, pb / RP);
+            const float av = pa % RP < ra.cols ? x[ra.eoff + pa % RP] : 0.f;
+            const float bv = pb % RP < rb.cols ? dy[rb.eoff + pb % RP] : 0.f;
+            acc[r] = mma<TagF32>(av, bv, acc[r]);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < D::KST; ++ks) {
+        const unsigned char *xt = st + ks * 32 * G::LDSW * 2, *gt = xt + G::XB;
+        GFrag bf[3][NPO], af[2][3];
+#pragma unroll
+        for (int q = 0; q < NPO; ++q)
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            bf[p][q] = dt_frag16<G::LDSW>(gt + p * G::PLANE, q < npo ? po0 + q : po0, lane);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) af[0][p] = dt_frag16<G::LDSW>(xt + p * G::PLANE, ph * S, lane);
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+          // (the next tile's fragments are read while this one is multiplied)
+          if (i + 1 < S) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p) af[(i + 1) & 1][p] = dt_frag16<G::LDSW>(xt + p * G::PLANE, ph * S + i + 1, lane);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          const GFrag(&f)[3] = af[i & 1];
+#define WBMM_DT_PART(PA, PB, ACC)                                                          \
+  _Pragma("unroll") for (int q = 0; q < NPO; ++q) if (q < npo) ACC[i - q + NPO - 1] =      \
+      mma_bf16(f[PA], bf[PB][q], ACC[i - q + NPO - 1]);
+          WBMM_DT_PART(2, 0, low)
+          WBMM_DT_PART(0, 2, low)
+          WBMM_DT_PART(1, 1, low)
+          WBMM_DT_PART(1, 0, low)
+          WBMM_DT_PART(0, 1, low)
+          WBMM_DT_PART(0, 0, acc)
+#undef WBMM_DT_PART
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+  };
+
+  // ---- input gradient: the reversed table's fragments of tile pair T, the
+  // products of stage s and the rows of a finished stage out
+  const int T = wave % S, sg = wave / S;
+  GFrag fr[1][2][DX ? S : 1];
+  unsigned char *obuf = smem + D::O_OFF;
+  auto dx_products = [&](int s, const unsigned char *st) __attribute__((always_inline)) {
+    if constexpr (DX) {
+      if (sg >= G::NG) return;
+      const unsigned char *gp = st + G::XB + ((16 * sg + ln) * G::LDSW + 8 * g) * 2;
+      typename Tag::S *o = reinterpret_cast<typename Tag::S *>(obuf + (s & 1) * G::OB) + (16 * sg + ln) * G::OP + 32 * T + 4 * g;
+#pragma unroll
+      for (int j = 0; j < G::SPW; ++j) {
+        f32x4 r[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+          const GFrag gf = *reinterpret_cast<const GFrag *>(gp + 16 * j * G::NG * G::LDSW * 2 + 64 * k);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) r[h] = mma<Tag>(fr[0][h][k], gf, r[h]);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          *reinterpret_cast<uint2 *>(o + 16 * j * G::NG * G::OP + 16 * h) =
+              uint2{pack2<Tag>(r[h][0], r[h][1]), pack2<Tag>(r[h][2], r[h][3])};
+      }
+    }
+  };
+  auto dx_store = [&](int s, const GRow &r) __attribute__((always_inline)) {
+    if constexpr (DX) {
+      if (r.cols > 0) {
+        const unsigned char *ob = obuf + (s & 1) * G::OB + (v * G::OP + hi * RP) * Tag::ES;
+        uint32_t o[G::ND];
+#pragma unroll
+        for (int i = 0; i < G::ND; i += 4) {
+          const uint4 u = *reinterpret_cast<const uint4 *>(ob + 4 * i);
+          o[i] = u.x; o[i + 1] = u.y; o[i + 2] = u.z; o[i + 3] = u.w;
+        }
+        gen_store<Tag, RP>(dxo, r, o);
+      }
+    }
+  };
+
+  const int K1 = 2 * a.ww - 1, K2 = K1 * (2 * a.wh - 1);
+  typename Tag::S tv[2] = {};
+  if constexpr (DX) {
+    // (the table first, ahead of the rows; K2 <= 961)
+    const typename Tag::S *tc = tab + c * K2;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) tv[i] = tc[K2 - 1 - (tid + i * kGenThreads < K2 ? tid + i * kGenThreads : K2 - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  Rows d0, d1;
+  load(0, d0);
+  if constexpr (D::NBUF == 2) load(1, d1);
+  __builtin_amdgcn_sched_barrier(0);
+  if (tid < 2) flag[tid] = -1;
+  gen_mask_table<Tag, RP>(masks, tid);
+  if constexpr (DX) {
+    typename Tag::S *Ts = reinterpret_cast<typename Tag::S *>(obuf);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = tid + i * kGenThreads;
+      if (k < K2 + 10) Ts[k] = k < K2 ? tv[i] : (typename Tag::S)0;
+    }
+    __syncthreads();
+    gen_build_tb<Tag, RP, S>(a, Ts, smem + D::STAGE, nullptr, tid);
+  }
+  __syncthreads();
+  if constexpr (D::NBUF == 2) {
+    if constexpr (DX) gen_frags_tb<Tag, RP, S>(a, smem + D::STAGE, T, lane, fr);
+    GRow rprev = {0, 0}, rcur = d0.r;
+    write(0, smem, d0);
+    load(2, d0);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    // stage s + 1 (in d) to LDS, the rows of stage s - 1 out, stage s + 3 into d
+    auto stage = [&](int s, Rows &d) __attribute__((always_inline)) {
+      const unsigned char *st = smem + (s & 1) * D::STAGE;
+      products(s, st);
+      dx_products(s, st);
+      const GRow rnext = d.r;
+      write(s + 1, smem + ((s + 1) & 1) * D::STAGE, d);
+      dx_store(s - 1, rprev);
+      load(s + 3, d);
+      rprev = rcur;
+      rcur = rnext;
+      __syncthreads();
+    };
+    for (int s = 0; s < nst; s += 2) {
+      stage(s, d1);
+      if (s + 1 >= nst) break;
+      stage(s + 1, d0);
+    }
+    dx_store(nst - 1, rprev);
+    if constexpr (DX) __syncthreads();  // (the scratch below reaches the result buffers)
+  } else {
+    for (int s = 0; s < nst; ++s) {
+      write(s, smem, d0);
+      __syncthreads();
+      load(s + 1, d0);
+      products(s, smem);
+      __syncthreads();
+    }
+  }
+
+  // ---- diagonals of the wave's tiles, each R x R blocks of RP x RP: a block
+  // is written skewed, element (xi, xo) at column (xo - xi) mod RP of row xi,
+  // so that column s holds diagonal dw = -s above row RP - s and RP - s below;
+  // one lane sums one column of one block (pads are zero)
+  constexpr int R = D::R;
+  float *scr = reinterpret_cast<float *>(smem) + wave * D::BT * kBinTile;
+  float *bins = reinterpret_cast<float *>(smem + D::SCR);
+  float *mine = bins + wave * NR * D::NBIN;
+#pragma unroll
+  for (int r0 = 0; r0 < NR; r0 += D::BT) {
+    wave_lds_sync();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int rr = 4 * g + e;
+      float *p = scr + rr * 17 + (ln & ~(RP - 1)) + ((ln - rr) & (RP - 1));
+#pragma unroll
+      for (int j = 0; j < D::BT; ++j) {
+        if (r0 + j >= NR) continue;
+        float t = acc[r0 + j][e];
+        if constexpr (D::LOWACC) t += low[r0 + j][e];
+        p[j * kBinTile] = t;
+      }
+    }
+    wave_lds_sync();
+    constexpr int TPT = R * R * RP;  // columns of a tile
+#pragma unroll
+    for (int k = 0; k < D::BT * TPT / 64; ++k) {
+      const int t = lane + 64 * k;
+      const int j = t / TPT, b = t % TPT / RP, sft = t % RP;  // tile, block (ra R + rb), column
+      if (r0 + j < NR) {
+        const float *p = scr + j * kBinTile + b / R * RP * 17 + b % R * RP + sft;
+        float lo = 0.f, up = 0.f;
+#pragma unroll
+        for (int xi = 0; xi < RP; ++xi) {
+          const float f = p[xi * 17];
+          const bool below = xi + sft >= RP;
+          lo += below ? 0.f : f;
+          up += below ? f : 0.f;
+        }
+        float *o = mine + (r0 + j) * D::NBIN + b * 2 * RP + RP - 1;
+        o[-sft] = lo;
+        if (sft > 0) o[RP - sft] = up;
+      }
+    }
+  }
+  __syncthreads();
+  // ---- entry (dh, dw): the waves' diagonals of the tiles P = pi - po and
+  // blocks with dh = P R + ra - rb, in wave order
+  float *o = out + ((int64_t)slab * a.C + c) * K2;
+  for (int k = tid; k < K2; k += kGenThreads) {
+    const int dh = k / K1 - (a.wh - 1), dw = k - k / K1 * K1 - (a.ww - 1);
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kGenWaves; ++w) {
+      const int base = gen_dt_cut<G::NT>(w >> 2, w & 3) - (w >> 2) * S + NPO - 1;
+#pragma unroll
+      for (int b = 0; b < R * R; ++b) {
+        const int pr = dh - (b / R - b % R);  // P R
+        if (R == 2 && (pr & 1)) continue;
+        const int r = pr / R + base;
+        if (r >= 0 && r < NR) sum += bins[(w * NR + r) * D::NBIN + b * 2 * RP + RP - 1 + dw];
+      }
+    }
+    o[k] = sum;
+  }
 }
 
 }  // namespace wbmm

@@ -44,6 +44,13 @@ static GenArgs gen_args(const Geom &g, int wh, int ww) {
   return a;
 }
 
+// Neighbouring windows whose rows neighbouring lanes move: see gen_slot_window.
+template <class G>
+static void gen_lanes(GenArgs &a) {
+  a.lgg = 0;
+  while ((2 << a.lgg) <= (int64_t)a.NW && (2 << a.lgg) <= G::CW) ++a.lgg;
+}
+
 template <class Tag, int RP, int S>
 static hipError_t gen_fwd(const void *x, const void *coef, void *y, const Geom &g, int wh, int ww, int src,
                           hipStream_t st) {
@@ -52,8 +59,7 @@ static hipError_t gen_fwd(const void *x, const void *coef, void *y, const Geom &
   GenArgs a = gen_args(g, wh, ww);
   a.src = src;
   a.stages = (int)cdiv64(a.N, G::CW);
-  a.lgg = 0;
-  while ((2 << a.lgg) <= (int64_t)a.NW && (2 << a.lgg) <= G::CW) ++a.lgg;
+  gen_lanes<G>(a);
   const int ncu = compute_units();
   const int wgs = src >= kSrcMat ? GenFwd<Tag, RP, S, true>::WGS : GenFwd<Tag, RP, S, false>::WGS;
   gen_plan(g.C, a.stages, (int64_t)(ncu > 0 ? ncu : 256) * wgs, 1.5, 1 << 20, &a.spw, &a.tiles_per_ch);
@@ -123,6 +129,67 @@ static hipError_t run_gen_fwd(const void *x, const void *coef, void *y, const Ge
     }
   }
   return hipErrorInvalidValue;
+}
+
+// Table gradient, with dx (16-bit) the fused backward: at most max_slabs
+// partial tables per channel, which the caller's workspace holds (one: dt is
+// written directly); the partials are summed by the sum kernel behind it.
+// One workgroup per compute unit is planned for, with or without dx, so that
+// both have the same slabs.
+template <class Tag, int RP, int S>
+static hipError_t gen_dt(const void *x, const void *dy, const void *t, void *dx, float *dt, float *ws, const Geom &g,
+                         int wh, int ww, int64_t max_slabs, hipStream_t st) {
+  typedef typename Tag::S E;
+  typedef GenCfg<Tag, RP, S> G;
+  GenArgs a = gen_args(g, wh, ww);
+  a.stages = (int)cdiv64(a.N, G::CW);
+  gen_lanes<G>(a);
+  const int ncu = compute_units();
+  gen_plan(g.C, a.stages, ncu > 0 ? ncu : 256, 3.0, max_slabs, &a.spw, &a.tiles_per_ch);
+  float *out = a.tiles_per_ch > 1 ? ws : dt;
+  const dim3 grid((unsigned)(g.C * a.tiles_per_ch)), block(kGenThreads);
+  constexpr size_t lds = GenDt<Tag, RP, S, false>::LDS, flds = GenDt<Tag, RP, S, Tag::W16>::LDS;
+  static_assert(lds <= 160 * 1024 && flds <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
+  if (dx)
+    gen_dt_kernel<Tag, RP, S, Tag::W16><<<grid, block, flds, st>>>((const E *)x, (const E *)dy, (const E *)t, (E *)dx,
+                                                                   out, a);
+  else
+    gen_dt_kernel<Tag, RP, S, false><<<grid, block, lds, st>>>((const E *)x, (const E *)dy, nullptr, nullptr, out, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.tiles_per_ch <= 1) return e;
+  return launch_dt_sum(ws, dt, g.C * (int64_t)(2 * wh - 1) * (2 * ww - 1), nullptr, nullptr, 0, a.tiles_per_ch, st);
+}
+
+template <class Tag>
+static hipError_t run_gen_dt(const void *x, const void *dy, const void *t, void *dx, float *dt, float *ws,
+                             const Geom &g, int wh, int ww, int64_t max_slabs, hipStream_t st) {
+  if (ww <= 8) {
+    switch ((wh + 3) / 4) {
+      case 1: return gen_dt<Tag, 8, 1>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 2: return gen_dt<Tag, 8, 2>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 3: return gen_dt<Tag, 8, 3>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 4: return gen_dt<Tag, 8, 4>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+    }
+  } else {
+    switch ((wh + 1) / 2) {
+      case 1: return gen_dt<Tag, 16, 1>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 2: return gen_dt<Tag, 16, 2>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 3: return gen_dt<Tag, 16, 3>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 4: return gen_dt<Tag, 16, 4>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 5: return gen_dt<Tag, 16, 5>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 6: return gen_dt<Tag, 16, 6>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 7: return gen_dt<Tag, 16, 7>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+      case 8: return gen_dt<Tag, 16, 8>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
+template <>
+hipError_t GenEntry<WBMM_INST_TAG>::backward(const void *x, const void *dy, const void *t, void *dx, float *dt,
+                                             void *ws, const Geom &g, int wh, int ww, int64_t max_slabs,
+                                             hipStream_t st) {
+  return run_gen_dt<WBMM_INST_TAG>(x, dy, t, dx, dt, (float *)ws, g, wh, ww, max_slabs, st);
 }
 
 template <>

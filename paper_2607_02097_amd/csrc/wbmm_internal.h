@@ -93,6 +93,11 @@ template <class Tag>
 struct GenEntry {
   static hipError_t forward(const void *x, const void *coef, void *y, const Geom &g, int wh, int ww, int src,
                             hipStream_t stream);
+  // Table gradient in at most max_slabs partial tables per channel (ws), of
+  // a tensor of at least 16 elements; with dx (16-bit) the input gradient
+  // from table t in the same pass.
+  static hipError_t backward(const void *x, const void *dy, const void *t, void *dx, float *dt, void *ws,
+                             const Geom &g, int wh, int ww, int64_t max_slabs, hipStream_t stream);
 };
 
 // Per-(dtype, window) entry points, defined by the wbmm_inst.hip

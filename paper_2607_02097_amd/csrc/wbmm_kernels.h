@@ -56,8 +56,9 @@
 // rows), and four copy waves bring the next stages in, with one workgroup
 // barrier per stage.  Otherwise a
 // four-wave workgroup per (channel, slab) runs the same products in turn.
-// Float32 windows of 9 and more, and 16-bit maps that the windows do not
-// tile, take the general kernels of wbmm_gen.h instead (kGenWindow, gen_map).
+// Float32 windows of 9 and more, and 16-bit maps without fixed-offset rows,
+// take the general kernels of wbmm_gen.h instead (kGenWindow, gen_map,
+// gen_grad).
 // The hierarchical form (global window 2 wl plus local wl sub-windows) adds
 // local-block products to the forward and input gradient and splits the
 // table-gradient accumulators by row halves to bin both tables in one pass.
@@ -2945,6 +2946,29 @@ static hipError_t sum_slabs(const float *part, float *dt, int64_t n, const float
   return launch_dt_sum(part, dt, n, part2, dt2, n2, (int)slabs, st);
 }
 
+// Which table gradients, and 16-bit fused backwards, the general kernel of
+// wbmm_gen.h takes (tiled: whether the rows have fixed offsets):
+// * float32 windows of 13 and more from 2 M elements: six products of bf16
+//   parts against float32 products (w = 14, us: B64 C192 28x28 63.6 -> 46.0, B128
+//   C192 28x28 122 -> 85, B128 C384 14x14 65 -> 52; but B1 C64 75x100 10.5
+//   against 12.6).  w = 10 has half its columns padding and gains nothing
+//   (B64 C192 20x20 38 against 36, B128 C384 10x10 33 against 38).
+// * 16-bit rows without fixed offsets (odd windows, cut maps, window counts
+//   that are no power of two, odd addresses), which the four-wave kernels
+//   address row by row and read element by element where odd: from 2 M
+//   elements at windows up to 8, from 4 M above (fused backward, us: w = 7
+//   B64 C96 56x56 47 -> 29, B64 C192 14x14 11.3 -> 9.5; w = 14 B8 C96 100x167
+//   69 -> 35; w = 5 B64 C96 40x40 41 -> 26; but w = 14 B4 C96 50x84, 1.6 M, 11.5
+//   against 12.5 and w = 9 B128 C384 9x9, 4.0 M, 17.3 against 23.9).
+// The same for the fused backward and the table gradient alone, so that they
+// agree bit for bit.
+template <class Tag, int WIN>
+static bool gen_grad(const Geom &g, bool tiled) {
+  const int64_t numel = g.B * g.C * g.H * g.W;
+  if (!Tag::W16) return WIN >= 13 && numel >= (int64_t)1 << 21;
+  return !tiled && numel >= (int64_t)1 << (rp_of(WIN) == 8 ? 21 : 22);
+}
+
 template <class Tag, int WIN>
 static hipError_t run_dtable(const void *x, const void *dy, float *dt, void *ws, const Geom &g,
                              hipStream_t st) {
@@ -2954,6 +2978,8 @@ static hipError_t run_dtable(const void *x, const void *dy, float *dt, void *ws,
   a.tile = (int)p.slab_windows;
   a.tiles_per_ch = (int)p.slabs;
   set_tiled<WIN, Tag::ES>(g, a, {x, dy});
+  if (gen_grad<Tag, WIN>(g, a.tiled != 0))
+    return GenEntry<Tag>::backward(x, dy, nullptr, nullptr, dt, ws, g, WIN, WIN, p.slabs, st);
   if constexpr (Tag::ES == 4 || WIN % 2 == 0) {
     KArgs b = a;
     if (stream_plan<Tag, WIN>(g, b, true, p.slabs)) {
@@ -3000,6 +3026,8 @@ static hipError_t run_backward_fused(const void *x, const void *dy, const void *
   a.tile = (int)p.slab_windows;
   a.tiles_per_ch = (int)p.slabs;
   set_tiled<WIN, Tag::ES>(g, a, {x, dy, dx});
+  if (Tag::W16 && gen_grad<Tag, WIN>(g, a.tiled != 0))
+    return GenEntry<Tag>::backward(x, dy, t, dx, dt, ws, g, WIN, WIN, p.slabs, st);
   if constexpr (Tag::ES == 4 || WIN % 2 == 0) {
     KArgs b = a;
     if (stream_plan<Tag, WIN>(g, b, true, p.slabs)) {
@@ -3043,7 +3071,7 @@ static hipError_t run_backward(const void *x, const void *dy, const void *t, voi
                                const Geom &g, hipStream_t st) {
   if constexpr (kGenWindow<Tag, WIN>) {
     // dY is read twice, which costs less than the fused kernels' float32
-    // products (w = 14, B128 C192 28x28: 279 us fused, 184 as two launches)
+    // products (w = 14, B128 C192 28x28: 279 us fused, 157 as two launches)
     const hipError_t e = run_forward<Tag, WIN>(dy, t, dx, g, true, st);
     return e != hipSuccess ? e : run_dtable<Tag, WIN>(x, dy, dt, ws, g, st);
   } else {

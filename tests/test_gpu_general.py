@@ -149,3 +149,67 @@ def test_float32_range(w):
             assert torch.isinf(y[hit]).all()
     assert not W.wbmm_forward(torch.zeros_like(x).cuda(), t.cuda(), w).any()
     assert not W.wbmm_forward(x.cuda(), torch.zeros_like(t).cuda(), w).any()
+
+
+# rows without fixed offsets at the sizes the general gradients take, windows
+# of every K-step count: cut maps, odd windows, window counts that are no
+# power of two, one and several slabs, more channels than compute units
+GRAD = [(24, 96, 31, 31, 3), (40, 64, 29, 31, 4), (9, 300, 28, 28, 7), (64, 40, 29, 31, 7), (16, 96, 42, 42, 8),
+        (30, 200, 27, 27, 9), (6, 64, 113, 99, 10), (2, 600, 61, 61, 12), (8, 96, 100, 61, 14), (11, 96, 84, 84, 14),
+        (3, 17, 301, 299, 15), (9, 40, 111, 109, 16)]
+
+
+def exact_gradients(x, dy, t, w):
+    idx = index(w, w).to(x.device)
+    xw, gw = windows(x.double(), w, w), windows(dy.double(), w, w)
+    m = t.double()[:, idx]
+    g = torch.bmm(xw.transpose(1, 2).contiguous(), gw.contiguous())
+    dt = torch.zeros(t.shape, dtype=torch.float64, device=x.device).index_add_(1, idx.flatten(), g.flatten(1))
+    dx = unwindows(torch.bmm(gw.contiguous(), m.transpose(1, 2).contiguous()), x.shape, w, w)
+    return dx, dt
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", GRAD, ids=lambda s: "B%dC%dH%dW%dw%d" % s)
+def test_general_gradients(shape, dtype):
+    """The fused backward equals the separate calls bit for bit and the exact
+    gradients within tolerance (dT: float32 sums of exact products, held to
+    1e-5 of the largest entry as in the parity tests)."""
+    B, C, H, Wd, w = shape
+    x, t = (v.cuda() for v in data(B, C, H, Wd, w, w, dtype, seed=w))
+    dy, _ = (v.cuda() for v in data(B, C, H, Wd, w, w, dtype, seed=w + 100))
+    dx, dt = W.wbmm_backward(x, dy, t, w)
+    assert torch.equal(dt, W.wbmm_backward_table(x, dy, w))
+    assert torch.equal(dx, W.wbmm_backward_input(dy, t, w))
+    wdx, wdt = exact_gradients(x, dy, t, w)
+    e_t = float((dt.double() - wdt).abs().max() / wdt.abs().max())
+    e_x = float((dx.double() - wdx).abs().max() / wdx.abs().max())
+    print(shape, dtype, "dt %.1e dx %.1e" % (e_t, e_x), flush=True)
+    assert e_t <= 1e-5 and e_x <= 2e-2
+
+
+@pytest.mark.parametrize("shape", [(20, 200, 27, 27, 13), (14, 192, 28, 28, 14), (10, 300, 30, 31, 15),
+                                   (3, 40, 160, 150, 16)], ids=lambda s: "B%dC%dH%dW%dw%d" % s)
+def test_general_gradients_float32(shape):
+    """As above in float32, then with rows of x or dy out of the range of the
+    bf16 parts (their stages take float32 products)."""
+    B, C, H, Wd, w = shape
+    x, t = (v.cuda() for v in data(B, C, H, Wd, w, w, "f32", seed=w))
+    dy, _ = (v.cuda() for v in data(B, C, H, Wd, w, w, "f32", seed=w + 100))
+    for case in ("plain", "huge", "tiny"):
+        if case == "huge":
+            x[1, 3, 5] *= 2.0 ** 70
+        if case == "tiny":
+            x[1, 3, 5] *= 2.0 ** -70
+            dy[0, :, :w] *= 2.0 ** -110
+        dx, dt = W.wbmm_backward(x, dy, t, w)
+        assert torch.equal(dt, W.wbmm_backward_table(x, dy, w))
+        assert torch.equal(dx, W.wbmm_backward_input(dy, t, w))
+        wdx, wdt = exact_gradients(x, dy, t, w)
+        err = (dt.double() - wdt).abs().amax(1) / wdt.abs().amax(1)  # per channel: each has its own scale
+        e_x = float((dx.double() - wdx).abs().max() / wdx.abs().max())
+        print(shape, case, "dt %.1e dx %.1e" % (float(err.max()), e_x), flush=True)
+        assert float(err.max()) <= 1e-5 and e_x <= 1e-5
+    x[0, 2, 7, 9] = float("nan")
+    _, dt = W.wbmm_backward(x, dy, t, w)
+    assert torch.isnan(dt[2]).any() and not torch.isnan(dt[:2]).any() and not torch.isnan(dt[3:]).any()
