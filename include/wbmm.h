@@ -246,6 +246,30 @@ wbmm_status wbmm_dense_backward_matrix(const void *x, const void *dy, float *dm,
 wbmm_status wbmm_bin_matrix(const float *dm, float *dtable, int64_t C, int wh,
                             int ww, void *stream);
 
+/* ---- Rectangular w_h x w_w windows (1 <= w_h, w_w <= 16) straight from the
+ * table [C,(2 w_h - 1)(2 w_w - 1)]: what wbmm_build_matrix followed by
+ * wbmm_dense_forward / wbmm_dense_backward_input, and
+ * wbmm_dense_backward_matrix followed by wbmm_bin_matrix, compute, without a
+ * matrix in memory.  Conventions as above; dtable is float32, overwritten.
+ * workspace: at least wbmm_rect_backward_table_workspace_bytes() bytes (may
+ * be NULL when that is 0), 4-byte aligned, any contents, not shared by calls
+ * that can run concurrently. */
+wbmm_status wbmm_rect_forward(const void *x, const void *table, void *y,
+                              int64_t B, int64_t C, int64_t H, int64_t W,
+                              int wh, int ww, wbmm_dtype dtype, void *stream);
+wbmm_status wbmm_rect_backward_input(const void *dy, const void *table,
+                                     void *dx, int64_t B, int64_t C, int64_t H,
+                                     int64_t W, int wh, int ww,
+                                     wbmm_dtype dtype, void *stream);
+size_t wbmm_rect_backward_table_workspace_bytes(int64_t B, int64_t C,
+                                                int64_t H, int64_t W, int wh,
+                                                int ww, wbmm_dtype dtype);
+wbmm_status wbmm_rect_backward_table(const void *x, const void *dy,
+                                     float *dtable, void *workspace,
+                                     size_t workspace_bytes, int64_t B,
+                                     int64_t C, int64_t H, int64_t W, int wh,
+                                     int ww, wbmm_dtype dtype, void *stream);
+
 /* Static description of a status code (never NULL). */
 const char *wbmm_status_string(wbmm_status s);
 

@@ -12,8 +12,8 @@ Names follow the C entry points: ``wbmm_forward``, ``wbmm_backward_input``,
 ``wbmm_hier_backward_workspace_bytes``, the cached-matrix form
 ``wbmm_build_matrix``, ``wbmm_dense_forward``, ``wbmm_dense_backward_input``,
 ``wbmm_dense_backward_matrix``, ``wbmm_bin_matrix``, and
-``wbmm_relative_index``, ``wbmm_status_string``.  ``wbmm_rect_*`` compose the
-cached-matrix calls into WBMM for rectangular windows.
+``wbmm_relative_index``, ``wbmm_status_string``.  ``wbmm_rect_*`` are WBMM for
+rectangular windows, straight from the table or with a cached matrix.
 """
 from __future__ import annotations
 
@@ -39,7 +39,9 @@ EXPORTED = ("wbmm_forward", "wbmm_backward_input", "wbmm_backward_table",
             "wbmm_hier_backward_input", "wbmm_hier_backward",
             "wbmm_hier_backward_workspace_bytes", "wbmm_build_matrix",
             "wbmm_dense_forward", "wbmm_dense_backward_input",
-            "wbmm_dense_backward_matrix", "wbmm_bin_matrix", "wbmm_status_string",
+            "wbmm_dense_backward_matrix", "wbmm_bin_matrix", "wbmm_rect_forward",
+            "wbmm_rect_backward_input", "wbmm_rect_backward_table",
+            "wbmm_rect_backward_table_workspace_bytes", "wbmm_status_string",
             "wbmm_relative_index", "wbmm_version")
 
 _lib = None
@@ -93,6 +95,14 @@ def load_library(path: str = LIB_PATH):
     lib.wbmm_dense_backward_input.restype = st
     lib.wbmm_dense_backward_matrix.argtypes = [vp, vp, vp] + dshape
     lib.wbmm_dense_backward_matrix.restype = st
+    lib.wbmm_rect_forward.argtypes = [vp, vp, vp] + dshape
+    lib.wbmm_rect_forward.restype = st
+    lib.wbmm_rect_backward_input.argtypes = [vp, vp, vp] + dshape
+    lib.wbmm_rect_backward_input.restype = st
+    lib.wbmm_rect_backward_table_workspace_bytes.argtypes = [i64, i64, i64, i64, ci, ci, ci]
+    lib.wbmm_rect_backward_table_workspace_bytes.restype = ctypes.c_size_t
+    lib.wbmm_rect_backward_table.argtypes = [vp, vp, vp, vp, ctypes.c_size_t] + dshape
+    lib.wbmm_rect_backward_table.restype = st
     lib.wbmm_bin_matrix.argtypes = [vp, vp, i64, ci, ci, vp]
     lib.wbmm_bin_matrix.restype = st
     lib.wbmm_status_string.argtypes = [st]
@@ -452,24 +462,50 @@ def wbmm_bin_matrix(dm, wh: int, ww: int, out=None, stream=None):
     return out
 
 
+def _rect_like(fn_name, src, table, wh, ww, stream):
+    _check_tensor(table, "table")
+    _check_tensor(src, "input")
+    B, C, H, W = src.shape
+    k = (2 * int(wh) - 1) * (2 * int(ww) - 1)
+    if table.dtype != src.dtype or table.device != src.device or table.shape[0] != C or table.numel() < C * k:
+        raise ValueError("table must be [C, (2wh-1)(2ww-1)] in the input's dtype and device")
+    out = torch.empty_like(src)
+    _call(fn_name, src.device, _ptr(src), _ptr(table), _ptr(out), B, C, H, W, int(wh), int(ww), _code(src.dtype),
+          _stream(src, stream))
+    return out
+
+
 def wbmm_rect_forward(x, table, wh: int, ww: int, m=None, stream=None):
-    """WBMM with wh x ww windows (table [C,(2wh-1)(2ww-1)]): the matrix is
-    built (or ``m`` reused) and applied per window."""
+    """WBMM with wh x ww windows (table [C,(2wh-1)(2ww-1)]), from the table or
+    from the matrix ``m`` built from it."""
     if m is None:
-        m = wbmm_build_matrix(table, wh, ww, stream=stream)
+        return _rect_like("wbmm_rect_forward", x, table, wh, ww, stream)
     return wbmm_dense_forward(x, m, wh, ww, stream=stream)
 
 
 def wbmm_rect_backward_input(dy, table, wh: int, ww: int, m=None, stream=None):
     if m is None:
-        m = wbmm_build_matrix(table, wh, ww, stream=stream)
+        return _rect_like("wbmm_rect_backward_input", dy, table, wh, ww, stream)
     return wbmm_dense_backward_input(dy, m, wh, ww, stream=stream)
 
 
 def wbmm_rect_backward_table(x, dy, wh: int, ww: int, stream=None):
-    """Table gradient with wh x ww windows (float32): the matrix gradient
-    folded onto the table."""
-    return wbmm_bin_matrix(wbmm_dense_backward_matrix(x, dy, wh, ww, stream=stream), wh, ww, stream=stream)
+    """Table gradient with wh x ww windows (float32
+    [C, (2wh-1)(2ww-1)])."""
+    _check_tensor(x, "x")
+    _check_tensor(dy, "dy")
+    if dy.shape != x.shape or dy.dtype != x.dtype or dy.device != x.device:
+        raise ValueError("dy must match x's shape, dtype and device")
+    B, C, H, W = x.shape
+    code = _code(x.dtype)
+    need = int(load_library().wbmm_rect_backward_table_workspace_bytes(B, C, H, W, int(wh), int(ww), code))
+    # (the workspace belongs to the stream that the call runs on)
+    with torch.cuda.stream(_torch_stream(x.device, stream)):
+        ws = torch.empty(need, dtype=torch.uint8, device=x.device)
+    out = torch.empty((C, (2 * int(wh) - 1) * (2 * int(ww) - 1)), dtype=torch.float32, device=x.device)
+    _call("wbmm_rect_backward_table", x.device, _ptr(x), _ptr(dy), _ptr(out), _ptr(ws), need, B, C, H, W, int(wh),
+          int(ww), code, _stream(x, stream))
+    return out
 
 
 def wbmm_relative_index(w: int) -> torch.Tensor:

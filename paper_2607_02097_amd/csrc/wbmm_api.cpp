@@ -344,6 +344,63 @@ wbmm_status wbmm_dense_backward_input(const void *dy, const void *m, void *dx, i
   return dense_forward_like(dy, m, dx, B, C, H, W, wh, ww, dtype, stream, true);
 }
 
+// ---- rectangular windows straight from the table
+
+static wbmm_status rect_forward_like(const void *in, const void *table, void *out, int64_t B, int64_t C, int64_t H,
+                                     int64_t W, int wh, int ww, wbmm_dtype dtype, void *stream, bool rev) {
+  Geom g;
+  int64_t bytes = 0;
+  wbmm_status s = dense_shape(B, C, H, W, wh, ww, dtype, &g, &bytes);
+  if (s != WBMM_OK) return s;
+  if (!in || !table || !out) return WBMM_ERR_INVALID_ARG;
+  const size_t es = elem_size(dtype);
+  if (!aligned(in, es) || !aligned(table, es) || !aligned(out, es)) return WBMM_ERR_INVALID_ARG;
+  const int64_t tbytes = C * (int64_t)(2 * wh - 1) * (2 * ww - 1) * (int64_t)es;
+  if (overlap(in, bytes, out, bytes) || overlap(table, tbytes, out, bytes)) return WBMM_ERR_INVALID_ARG;
+  return from_hip(wbmm::launch_rect_forward((Dt)dtype, in, table, out, g, wh, ww, rev, (hipStream_t)stream));
+}
+
+wbmm_status wbmm_rect_forward(const void *x, const void *table, void *y, int64_t B, int64_t C, int64_t H, int64_t W,
+                              int wh, int ww, wbmm_dtype dtype, void *stream) {
+  return rect_forward_like(x, table, y, B, C, H, W, wh, ww, dtype, stream, false);
+}
+
+wbmm_status wbmm_rect_backward_input(const void *dy, const void *table, void *dx, int64_t B, int64_t C, int64_t H,
+                                     int64_t W, int wh, int ww, wbmm_dtype dtype, void *stream) {
+  return rect_forward_like(dy, table, dx, B, C, H, W, wh, ww, dtype, stream, true);
+}
+
+size_t wbmm_rect_backward_table_workspace_bytes(int64_t B, int64_t C, int64_t H, int64_t W, int wh, int ww,
+                                                wbmm_dtype dtype) {
+  Geom g;
+  int64_t bytes = 0;
+  if (dense_shape(B, C, H, W, wh, ww, dtype, &g, &bytes) != WBMM_OK) return 0;
+  const int64_t slabs = wbmm::rect_max_slabs(g);
+  return slabs > 1 ? (size_t)slabs * (size_t)C * (size_t)((2 * wh - 1) * (2 * ww - 1)) * 4 : 0;
+}
+
+wbmm_status wbmm_rect_backward_table(const void *x, const void *dy, float *dtable, void *workspace,
+                                     size_t workspace_bytes, int64_t B, int64_t C, int64_t H, int64_t W, int wh,
+                                     int ww, wbmm_dtype dtype, void *stream) {
+  Geom g;
+  int64_t bytes = 0;
+  wbmm_status s = dense_shape(B, C, H, W, wh, ww, dtype, &g, &bytes);
+  if (s != WBMM_OK) return s;
+  if (!x || !dy || !dtable) return WBMM_ERR_INVALID_ARG;
+  const size_t es = elem_size(dtype);
+  if (!aligned(x, es) || !aligned(dy, es) || !aligned(dtable, 4)) return WBMM_ERR_INVALID_ARG;
+  const int64_t tbytes = C * (int64_t)(2 * wh - 1) * (2 * ww - 1) * 4;
+  if (overlap(x, bytes, dtable, tbytes) || overlap(dy, bytes, dtable, tbytes)) return WBMM_ERR_INVALID_ARG;
+  const size_t need = wbmm_rect_backward_table_workspace_bytes(B, C, H, W, wh, ww, dtype);
+  if (need > 0) {
+    if (!workspace || workspace_bytes < need || !aligned(workspace, 4)) return WBMM_ERR_INVALID_ARG;
+    if (overlap(workspace, (int64_t)need, dtable, tbytes) || overlap(workspace, (int64_t)need, x, bytes) ||
+        overlap(workspace, (int64_t)need, dy, bytes))
+      return WBMM_ERR_INVALID_ARG;
+  }
+  return from_hip(wbmm::launch_rect_dtable((Dt)dtype, x, dy, dtable, workspace, g, wh, ww, (hipStream_t)stream));
+}
+
 wbmm_status wbmm_dense_backward_matrix(const void *x, const void *dy, float *dm, int64_t B, int64_t C, int64_t H,
                                        int64_t W, int wh, int ww, wbmm_dtype dtype, void *stream) {
   Geom g;

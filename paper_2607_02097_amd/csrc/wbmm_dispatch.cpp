@@ -94,4 +94,33 @@ hipError_t launch_dense_forward(Dt dt, const void *x, const void *m, void *y, co
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_rect_forward(Dt dt, const void *x, const void *table, void *y, const Geom &g, int wh, int ww,
+                               bool reverse_table, hipStream_t stream) {
+  const int src = reverse_table ? 1 : 0;
+  switch (dt) {
+    case Dt::F32: return GenEntry<TagF32>::forward(x, table, y, g, wh, ww, src, stream);
+    case Dt::BF16: return GenEntry<TagBF16>::forward(x, table, y, g, wh, ww, src, stream);
+    case Dt::F16: return GenEntry<TagF16>::forward(x, table, y, g, wh, ww, src, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
+// As many partial tables as fill the chip a few times over, each of at least
+// one stage of 32 windows.
+int64_t rect_max_slabs(const Geom &g) {
+  const int64_t stages = (g.N + 31) / 32, fill = (1024 + g.C - 1) / g.C;
+  return fill < stages ? fill : stages;
+}
+
+hipError_t launch_rect_dtable(Dt dt, const void *x, const void *dy, float *dtable, void *workspace, const Geom &g,
+                              int wh, int ww, hipStream_t stream) {
+  const int64_t slabs = rect_max_slabs(g);
+  switch (dt) {
+    case Dt::F32: return GenEntry<TagF32>::backward(x, dy, nullptr, nullptr, dtable, workspace, g, wh, ww, slabs, stream);
+    case Dt::BF16: return GenEntry<TagBF16>::backward(x, dy, nullptr, nullptr, dtable, workspace, g, wh, ww, slabs, stream);
+    case Dt::F16: return GenEntry<TagF16>::backward(x, dy, nullptr, nullptr, dtable, workspace, g, wh, ww, slabs, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
 }  // namespace wbmm

@@ -160,9 +160,41 @@ static hipError_t gen_dt(const void *x, const void *dy, const void *t, void *dx,
   return launch_dt_sum(ws, dt, g.C * (int64_t)(2 * wh - 1) * (2 * ww - 1), nullptr, nullptr, 0, a.tiles_per_ch, st);
 }
 
+// Table gradient of a tensor of fewer than 16 elements: one thread per entry.
+template <class Tag>
+__global__ __launch_bounds__(256) void gen_small_dt_kernel(const typename Tag::S *__restrict__ x,
+                                                           const typename Tag::S *__restrict__ dy,
+                                                           float *__restrict__ dt, GenArgs a) {
+  const int64_t K1 = 2 * a.ww - 1, K2 = K1 * (2 * a.wh - 1);
+  for (int64_t e = blockIdx.x * 256LL + threadIdx.x; e < a.C * K2; e += (int64_t)gridDim.x * 256) {
+    const int64_t c = e / K2, k = e - c * K2;
+    const int64_t dh = k / K1 - (a.wh - 1), dw = k % K1 - (a.ww - 1);
+    float s = 0.f;
+    for (int64_t o = 0; o < a.numel; ++o) {  // output position o, input at offset (dh, dw) in the same window
+      const int64_t gx = o % a.W, gy = o / a.W % a.H;
+      if (o / a.hw % a.C != c) continue;
+      const int64_t hx = gx + dw, hy = gy + dh;
+      if (hx < gx / a.ww * a.ww || hx >= (gx / a.ww + 1) * a.ww || hx >= a.W) continue;
+      if (hy < gy / a.wh * a.wh || hy >= (gy / a.wh + 1) * a.wh || hy >= a.H) continue;
+      const int64_t i = o + dh * a.W + dw;
+      if constexpr (Tag::W16) s += to_f32<Tag>(x[i]) * to_f32<Tag>(dy[o]);
+      else s += x[i] * dy[o];
+    }
+    dt[e] = s;
+  }
+}
+
 template <class Tag>
 static hipError_t run_gen_dt(const void *x, const void *dy, const void *t, void *dx, float *dt, float *ws,
                              const Geom &g, int wh, int ww, int64_t max_slabs, hipStream_t st) {
+  GenArgs a = gen_args(g, wh, ww);
+  if (a.numel < 16) {
+    typedef typename Tag::S E;
+    if (dx) return hipErrorInvalidValue;
+    const int64_t blocks = cdiv64(g.C * (int64_t)(2 * wh - 1) * (2 * ww - 1), 256);
+    gen_small_dt_kernel<Tag><<<dim3((unsigned)blocks), dim3(256), 0, st>>>((const E *)x, (const E *)dy, dt, a);
+    return hipGetLastError();
+  }
   if (ww <= 8) {
     switch ((wh + 3) / 4) {
       case 1: return gen_dt<Tag, 8, 1>(x, dy, t, dx, dt, ws, g, wh, ww, max_slabs, st);

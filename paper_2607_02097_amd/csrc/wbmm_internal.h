@@ -93,12 +93,21 @@ template <class Tag>
 struct GenEntry {
   static hipError_t forward(const void *x, const void *coef, void *y, const Geom &g, int wh, int ww, int src,
                             hipStream_t stream);
-  // Table gradient in at most max_slabs partial tables per channel (ws), of
-  // a tensor of at least 16 elements; with dx (16-bit) the input gradient
-  // from table t in the same pass.
+  // Table gradient in at most max_slabs partial tables per channel (ws), with
+  // dx (16-bit, at least 16 elements) the input gradient from table t in the
+  // same pass.
   static hipError_t backward(const void *x, const void *dy, const void *t, void *dx, float *dt, void *ws,
                              const Geom &g, int wh, int ww, int64_t max_slabs, hipStream_t stream);
 };
+
+// Rectangular windows straight from the table (the general kernels): the
+// product (reverse_table: the input gradient) and the table gradient in at
+// most rect_max_slabs(g) partial tables per channel.
+int64_t rect_max_slabs(const Geom &g);
+hipError_t launch_rect_forward(Dt dt, const void *x, const void *table, void *y, const Geom &g, int wh, int ww,
+                               bool reverse_table, hipStream_t stream);
+hipError_t launch_rect_dtable(Dt dt, const void *x, const void *dy, float *dtable, void *workspace, const Geom &g,
+                              int wh, int ww, hipStream_t stream);
 
 // Per-(dtype, window) entry points, defined by the wbmm_inst.hip
 // translation units and collected into tables by wbmm_dispatch.cpp.

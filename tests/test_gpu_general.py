@@ -213,3 +213,44 @@ def test_general_gradients_float32(shape):
     x[0, 2, 7, 9] = float("nan")
     _, dt = W.wbmm_backward(x, dy, t, w)
     assert torch.isnan(dt[2]).any() and not torch.isnan(dt[:2]).any() and not torch.isnan(dt[3:]).any()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("win", WINDOWS, ids=lambda w: "%dx%d" % w)
+def test_rectangular_table_gradient(win, dtype):
+    """From the table, against float64 and against the matrix gradient folded
+    by wbmm_bin_matrix; tiny maps, cut windows, several slabs."""
+    wh, ww = win
+    for B, C, H, Wd in ((1, 1, 2, 3), (1, 2, max(wh - 1, 4), ww + 5), (3, 3, 2 * wh + 1, 3 * ww - 1),
+                        (7, 5, 6 * wh, 11 * ww)):
+        x, _ = data(B, C, H, Wd, wh, ww, dtype, seed=wh + ww)
+        dy, _ = data(B, C, H, Wd, wh, ww, dtype, seed=wh * ww)
+        xw, gw = windows(x.double(), wh, ww), windows(dy.double(), wh, ww)
+        idx = index(wh, ww).flatten()
+        want = torch.zeros((C, (2 * wh - 1) * (2 * ww - 1)), dtype=torch.float64)
+        want.index_add_(1, idx, (xw.transpose(1, 2) @ gw).flatten(1))
+        scale = torch.zeros_like(want).index_add_(1, idx, (xw.abs().transpose(1, 2) @ gw.abs()).flatten(1))
+        got = W.wbmm_rect_backward_table(x.cuda(), dy.cuda(), wh, ww)
+        fold = W.wbmm_bin_matrix(W.wbmm_dense_backward_matrix(x.cuda(), dy.cuda(), wh, ww), wh, ww)
+        # float32 sums of exact products (f32: of parts that leave out 2^-24)
+        for r in (got, fold):
+            worst = float(((r.double().cpu() - want).abs() / (scale + 1e-30)).max())
+            assert worst <= 2.0 ** -18, (win, dtype, (B, C, H, Wd), worst)
+
+
+def test_rectangular_errors_and_streams():
+    x, t = (v.cuda() for v in data(2, 3, 20, 30, 4, 9, "bf16", seed=1))
+    with pytest.raises(ValueError):
+        W.wbmm_rect_forward(x, t[:2].contiguous(), 4, 9)
+    with pytest.raises(ValueError):
+        W.wbmm_rect_forward(x, t.float(), 4, 9)
+    with pytest.raises(ValueError):
+        W.wbmm_rect_backward_table(x, x[:1].contiguous(), 4, 9)
+    with pytest.raises(W.WbmmError):
+        W.wbmm_rect_backward_table(x, x, 17, 9)
+    want = W.wbmm_rect_backward_table(x, x, 4, 9)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    got = W.wbmm_rect_backward_table(x, x, 4, 9, stream=s)
+    s.synchronize()
+    assert torch.equal(got, want)
