@@ -585,9 +585,9 @@ struct GenFwd {
 // 4 to 5 until the first stage is multiplied); float32, the matrix cores, six
 // products for one, at the 1.9 GHz this load runs at.  Measured (us, before:
 // the kernels these replaced): bf16 matrix B128 C256 28x28 14 x 14 468 -> 33;
-// bf16 table w = 14 B8 C96 100x167 40 -> 19; float32 table w = 14 B128 C256
-// 56x56 788 -> 298 (135 TFLOP/s of useful work; the float32 matrix cores peak at 153).
-// The two waves of a SIMD in opposite order (float32): 368 -> 305.
+// bf16 table w = 14 B8 C96 100x167 40 -> 19; float32 table w = 14 B1 C8
+// 28x28 33 -> 8.9.  The two waves of a SIMD in opposite order (float32,
+// B128 C256 56x56): 368 -> 305.
 template <class Tag, int RP, int S, bool MAT>
 __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) void gen_fwd_kernel(
     const typename Tag::S *__restrict__ x, const typename Tag::S *__restrict__ coef, typename Tag::S *__restrict__ y,
@@ -844,6 +844,230 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
   }
   run(std::false_type{});
   if constexpr (TWO) store(nst - 1);
+}
+
+// ---------------------------------------------- float32, many windows
+// Y = X M from the table for maps that fill the chip with 16-window units,
+// one per wave: no stages, no barriers.  A wave reads its windows' fragments
+// straight from global memory (eight consecutive columns of one window row
+// per lane and K step), splits them in registers, multiplies them by the
+// table's fragments in LDS, tile pair by tile pair, and stores four consecutive
+// columns per lane; the next unit's rows are in flight meanwhile.  Two waves
+// per SIMD, at different points of their units, keep the matrix cores busy
+// through each other's splitting, loads and stores.
+//
+// What bounds it: the matrix cores at the rate the card sustains.  B128 C256
+// 56x56, w = 14: 275 us for 316 GFLOP of partial products, 1150 TFLOP/s (a large
+// bf16 matrix product reaches 1190 to 1360 on this card, which lowers its clock under
+// it); 257 without loads and stores, 227 with the products alone.  The staged
+// kernel above: 295.
+template <int RP, int S>
+struct GenDirect {
+  typedef GenCfg<TagF32, RP, S> G;
+  // a fragment depends on 2 k - t (K step, output tile) alone: NF of them,
+  // each stored in lane order (a fragment read covers 1 KB without bank
+  // conflicts; from Toeplitz blocks half of the LDS cycles were conflicts)
+  static constexpr int NF = 4 * S - 2;
+  static constexpr int PL = NF * 1024;  // bytes of one plane
+  static constexpr int TS_OFF = 3 * PL;             // table copy, then the masks of 0 .. 8 columns, flags
+  static constexpr int MASK_OFF = TS_OFF + 4 * 976;
+  static constexpr int FLAG_OFF = MASK_OFF + 9 * 32;
+  static constexpr size_t LDS = (size_t)FLAG_OFF + 16;
+};
+
+template <int RP, int S>
+__global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float *__restrict__ x,
+                                                                    const float *__restrict__ tab,
+                                                                    float *__restrict__ y, GenArgs a) {
+  typedef GenDirect<RP, S> D;
+  constexpr int KROWS = 32 / RP;  // window rows per K step
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, ln = lane & 15;
+  const uint32_t bid = die_major(blockIdx.x, gridDim.x);
+  const int64_t c = bid / (uint32_t)a.tiles_per_ch;
+  // units of this workgroup (spw rounds of eight), this wave's every eighth
+  const int u0 = (int)(bid - (uint32_t)c * (uint32_t)a.tiles_per_ch) * a.spw * kGenWaves;
+  const int nu = (int)((a.N + 15) / 16);
+  const int u1 = nu - u0 < a.spw * kGenWaves ? nu : u0 + a.spw * kGenWaves;
+
+  // ---- the table -> LDS -> blocks
+  const int K2 = (2 * a.ww - 1) * (2 * a.wh - 1);
+  float *Ts = reinterpret_cast<float *>(smem + D::TS_OFF);
+  uint32_t *masks = reinterpret_cast<uint32_t *>(smem + D::MASK_OFF);
+  int *flag = reinterpret_cast<int *>(smem + D::FLAG_OFF);
+  const float *tc = tab + c * K2;
+  for (int k = tid; k < K2 + 10; k += kGenThreads)
+    Ts[k] = k < K2 ? tc[a.src == kSrcTableRev ? K2 - 1 - k : k] : 0.f;
+  if (tid < 72) masks[tid] = tid / 8 > tid % 8 ? ~0u : 0u;
+  if (tid < 3) flag[tid] = 0;
+  __syncthreads();
+  uint32_t cmx = 0;
+  for (int ch = tid; ch < D::NF * 64; ch += kGenThreads) {
+    const int l = ch & 63, lg = l >> 4, lo = l & 15;
+    const int dh = (ch / 64 - (2 * S - 1)) * (16 / RP) + 8 * lg / RP - lo / RP, xo = lo % RP, xi = 8 * lg % RP;
+    const bool ok = dh > -a.wh && dh < a.wh && xo < a.ww;
+    const int nv = ok ? a.ww - xi : 0;  // columns inside the window
+    const float *t = Ts + (ok ? (dh + a.wh - 1) * (2 * a.ww - 1) + xi - xo + a.ww - 1 : 0);
+    uint32_t hh[4], mm[4], ll[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float f0 = nv > 2 * k ? t[2 * k] : 0.f, f1 = nv > 2 * k + 1 ? t[2 * k + 1] : 0.f;
+      const uint32_t m0 = __builtin_bit_cast(uint32_t, f0) & 0x7fffffffu, m1 = __builtin_bit_cast(uint32_t, f1) & 0x7fffffffu;
+      cmx = m0 > cmx ? m0 : cmx;
+      cmx = m1 > cmx ? m1 : cmx;
+      split3(f0, f1, hh[k], mm[k], ll[k]);
+    }
+    unsigned char *p = smem + ch * 16;
+    *reinterpret_cast<uint4 *>(p) = make_uint4(hh[0], hh[1], hh[2], hh[3]);
+    *reinterpret_cast<uint4 *>(p + D::PL) = make_uint4(mm[0], mm[1], mm[2], mm[3]);
+    *reinterpret_cast<uint4 *>(p + 2 * D::PL) = make_uint4(ll[0], ll[1], ll[2], ll[3]);
+  }
+  if (__any(cmx >= kFarHi) && lane == 0) flag[0] = 1;
+  if (__any(cmx != 0) && lane == 0) flag[1] = 1;
+  if (__any(cmx >= kFarLoCoef) && lane == 0) flag[2] = 1;
+  __syncthreads();
+  const bool cfar = flag[0] || (flag[1] && !flag[2]);
+
+  // this lane's window of a unit: its first element, rows and columns inside
+  // the image (0 rows: no window)
+  struct Win {
+    int64_t eoff;
+    int rows, cols;
+  };
+  auto window = [&](int u) __attribute__((always_inline)) -> Win {
+    Win w = {0, 0, 0};
+    const uint32_t n = 16u * (uint32_t)u + ln;
+    const uint32_t b = div_by(n, a.dnhw), rem = n - b * a.NHW;
+    const uint32_t wy = div_by(rem, a.dnw), wx = rem - wy * a.NW;
+    const int h0 = (int)wy * a.wh, x0 = (int)wx * a.ww;
+    const bool ok = u < u1 && n < a.N;
+    w.rows = !ok ? 0 : (int)a.H - h0 < a.wh ? (int)a.H - h0 : a.wh;
+    w.cols = (int)a.W - x0 < a.ww ? (int)a.W - x0 : a.ww;
+    w.eoff = (int64_t)b * a.chw + c * a.hw + (int64_t)h0 * a.W + x0;
+    return w;
+  };
+  const int hl = 8 * g / RP, x0 = 8 * g % RP;  // row within a K step, first column
+  const int64_t last = a.numel - 8;
+  typedef const __attribute__((address_space(1))) u32x4u *GP;
+  // (every lane loads, as in gen_load)
+  auto load = [&](const Win &w, uint32_t (&raw)[S][8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int r = KROWS * s + hl;
+      int64_t e = w.eoff + (int64_t)r * a.W + x0;
+      e = e < last ? e : last;
+      const uint64_t p = r < w.rows && x0 < w.cols ? reinterpret_cast<uint64_t>(x + e) : reinterpret_cast<uint64_t>(gen_zero);
+#pragma unroll
+      for (int i = 0; i < 8; i += 4) {
+        const u32x4u u = *reinterpret_cast<GP>(p + 4 * i);
+        raw[s][i] = u.x; raw[s][i + 1] = u.y; raw[s][i + 2] = u.z; raw[s][i + 3] = u.w;
+      }
+    }
+  };
+
+  uint32_t raw[S][8];
+  Win cur = window(u0 + wave);
+  load(cur, raw);
+  const unsigned char *tb0 = smem + (2 * S - 1) * 1024 + lane * 16;
+  for (int u = u0 + wave; u < u1; u += kGenWaves) {
+    // ---- the rows of this unit -> planes; the next unit's in flight
+    GFrag xp[3][S];
+    bool far = false;
+    {
+      const int nv = cur.cols - x0 < 0 ? 0 : cur.cols - x0 > 8 ? 8 : cur.cols - x0;
+      const uint4 ma = *reinterpret_cast<const uint4 *>(masks + 8 * nv), mb = *reinterpret_cast<const uint4 *>(masks + 8 * nv + 4);
+      const uint32_t m[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int r = KROWS * s + hl;
+        const int64_t over = cur.eoff + (int64_t)r * a.W + x0 - last;
+        if (r < cur.rows && x0 < cur.cols && over > 0) {
+          // within eight elements of the tensor's end: see gen_tail
+#pragma unroll 1
+          for (int k = (int)over; k > 0; --k)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) raw[s][i] = i < 7 ? raw[s][i + 1] : 0u;
+        }
+        uint32_t mx = 0;
+        uint32_t hh[4], mm[4], ll[4];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          raw[s][i] &= m[i];
+          const uint32_t v = raw[s][i] & 0x7fffffffu;
+          mx = v > mx ? v : mx;
+        }
+        far |= mx >= kFarHi || (mx != 0 && mx < kFarLo);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          split3(__builtin_bit_cast(float, raw[s][2 * i]), __builtin_bit_cast(float, raw[s][2 * i + 1]), hh[i], mm[i], ll[i]);
+        xp[0][s] = __builtin_bit_cast(GFrag, make_uint4(hh[0], hh[1], hh[2], hh[3]));
+        xp[1][s] = __builtin_bit_cast(GFrag, make_uint4(mm[0], mm[1], mm[2], mm[3]));
+        xp[2][s] = __builtin_bit_cast(GFrag, make_uint4(ll[0], ll[1], ll[2], ll[3]));
+      }
+    }
+    far = cfar || __any(far);
+    const Win w = cur;
+    cur = window(u + kGenWaves);
+    load(cur, raw);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- output tiles 2 T, 2 T + 1
+    const unsigned char *tb = tb0;
+#pragma unroll 1
+    for (int T = 0; T < S; ++T, tb -= 2048) {
+      f32x4 acc[2], mb[2], lb[2];
+      acc[0] = acc[1] = mb[0] = mb[1] = lb[0] = lb[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (far) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[h] = gen_far_tile<RP, S>(a, x, tab, c, 16u * (uint32_t)u + ln, 32 * T + 16 * h + ln, g);
+      } else {
+        // (step, tile) by (step, tile); the blocks of the next one are read
+        // while this one is multiplied (both tiles' at once would not fit
+        // the registers)
+        GFrag op[2][3];
+        auto fetch = [&](int k, int h, GFrag (&o)[3]) __attribute__((always_inline)) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            o[p] = *reinterpret_cast<const GFrag *>(tb + p * D::PL + (2 * k - h) * 1024);
+        };
+        fetch(0, 0, op[0]);
+#pragma unroll
+        for (int q = 0; q < 2 * S; ++q) {
+          const int k = q / 2, h = q % 2;
+          const GFrag(&o)[3] = op[q & 1];
+          if (q + 1 < 2 * S) fetch((q + 1) / 2, (q + 1) % 2, op[(q + 1) & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+          lb[h] = mma_bf16(o[2], xp[0][k], lb[h]);
+          mb[h] = mma_bf16(o[1], xp[0][k], mb[h]);
+          acc[h] = mma_bf16(o[0], xp[0][k], acc[h]);
+          lb[h] = mma_bf16(o[1], xp[1][k], lb[h]);
+          mb[h] = mma_bf16(o[0], xp[1][k], mb[h]);
+          lb[h] = mma_bf16(o[0], xp[2][k], lb[h]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      // window ln, positions 32 T + 16 h + 4 g .. + 3
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int pos = 32 * T + 16 * h + 4 * g, r = pos / RP, xc = pos % RP;
+        const int nc = r < w.rows ? w.cols - xc : 0;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[h][e] + (mb[h][e] + lb[h][e]);
+        float *q = y + w.eoff + (int64_t)r * a.W + xc;
+        if (nc >= 4) {
+          *reinterpret_cast<u32x4a *>(q) = u32x4a{__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]),
+                                                  __builtin_bit_cast(uint32_t, v[2]), __builtin_bit_cast(uint32_t, v[3])};
+        } else if (nc > 0) {
+          q[0] = v[0];
+          if (nc > 1) q[1] = v[1];
+          if (nc > 2) q[2] = v[2];
+        }
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------- table gradient

@@ -63,12 +63,27 @@ static hipError_t gen_fwd(const void *x, const void *coef, void *y, const Geom &
   const int ncu = compute_units();
   const int wgs = src >= kSrcMat ? GenFwd<Tag, RP, S, true>::WGS : GenFwd<Tag, RP, S, false>::WGS;
   gen_plan(g.C, a.stages, (int64_t)(ncu > 0 ? ncu : 256) * wgs, 1.5, 1 << 20, &a.spw, &a.tiles_per_ch);
+  if constexpr (!Tag::W16) {
+    // float32 from the table: one unit of 16 windows per wave where they fill
+    // half of the chip's 2048 waves (w = 14, us: B16 C96 56x56, 1536 units, 24.8
+    // -> 22.3; B128 C256 56x56 295 -> 275; w = 9 B128 C256 36x36 187 -> 138; but
+    // B1 C64 75x100, 192 units, 10.2 against 13.7); rows of eight always (w = 7
+    // B1 C64 75x100 6.5 -> 5.7, B64 C96 56x56 48.8 -> 35.0)
+    if (src < kSrcMat && (RP == 8 || g.C * cdiv64(a.N, 16) >= 1024)) {
+      typedef GenDirect<RP, S> D;
+      a.stages = (int)cdiv64(a.N, 16 * kGenWaves);
+      gen_plan(g.C, a.stages, ncu > 0 ? ncu : 256, 1.0, 1 << 20, &a.spw, &a.tiles_per_ch);
+      gen_direct_kernel<RP, S><<<dim3((unsigned)(g.C * a.tiles_per_ch)), dim3(kGenThreads), D::LDS, st>>>(
+          (const float *)x, (const float *)coef, (float *)y, a);
+      return hipGetLastError();
+    }
+  }
   const dim3 grid((unsigned)(g.C * a.tiles_per_ch)), block(kGenThreads);
   constexpr size_t ltab = GenFwd<Tag, RP, S, false>::LDS, lmat = GenFwd<Tag, RP, S, true>::LDS;
   static_assert(ltab <= 160 * 1024 && lmat <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
   if (src >= kSrcMat)
     gen_fwd_kernel<Tag, RP, S, true><<<grid, block, lmat, st>>>((const E *)x, (const E *)coef, (E *)y, a);
-  else
+  else if constexpr (Tag::W16 || RP == 16)
     gen_fwd_kernel<Tag, RP, S, false><<<grid, block, ltab, st>>>((const E *)x, (const E *)coef, (E *)y, a);
   return hipGetLastError();
 }

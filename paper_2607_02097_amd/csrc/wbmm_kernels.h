@@ -56,8 +56,8 @@
 // rows), and four copy waves bring the next stages in, with one workgroup
 // barrier per stage.  Otherwise a
 // four-wave workgroup per (channel, slab) runs the same products in turn.
-// Float32 windows of 9 and more, and 16-bit maps without fixed-offset rows,
-// take the general kernels of wbmm_gen.h instead (kGenWindow, gen_map,
+// Float32 windows of 9 and more (smaller ones on large maps), and 16-bit maps
+// without fixed-offset rows, take the general kernels of wbmm_gen.h instead (kGenWindow, gen_map,
 // gen_grad).
 // The hierarchical form (global window 2 wl plus local wl sub-windows) adds
 // local-block products to the forward and input gradient and splits the
@@ -2783,15 +2783,19 @@ static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const
 // wbmm_gen.h take:
 // * float32 windows of 9 and more, every map: the products as bf16 parts
 //   against the float32 matrix products of the row kernel, one table read per
-//   product (w = 14, us: B1 C8 28x28 33.2 -> 8.9, B64 C192 28x28 99 -> 40, B128
-//   C256 56x56 788 -> 305; w = 10: 14.6 -> 7.9, B64 C192 20x20 30.9 -> 30.6, B32
-//   C256 37x53 112 -> 76).  Below 9 the row kernel has less padding and wins
-//   (w = 5: 58 against 69 at B32 C256 37x53, 3.9 against 5.2 at B1 C8 20x20).
-//   By the window alone, so that the fused backward's dX, which takes the
-//   same kernel, equals wbmm_backward_input bit for bit.
+//   product (us: w = 14 B1 C8 28x28 33.2 -> 8.9, B64 C192 28x28 99 -> 36, B128
+//   C256 56x56 788 -> 275; w = 10 B1 C8 20x20 14.6 -> 7.9, B64 C192 20x20 30.9
+//   -> 21.4).
+// * float32 windows of 4 to 8 from 2 M elements: without fixed-offset rows
+//   (w = 5 B64 C96 56x56 66.8 -> 54.7, w = 7 B32 C256 37x53 60 -> 33), and 7
+//   and 8 with at least two windows a row (w = 7 B64 C96 56x56 43 -> 35, w = 8
+//   B128 C192 16x16 15.6 -> 13.5).  Elsewhere the row kernel is the shorter
+//   one (w = 7 B128 C384 7x7 9.3 against 11.6, w = 5 B128 C256 20x20 33 against
+//   37).  By the shape alone, so that the fused backward's dX, which takes
+//   the same kernel, equals wbmm_backward_input bit for bit.
 // * 16-bit windows of 7 and more on maps they do not tile: the row kernel
 //   reads cut and odd rows element by element (w = 14, B8 C96 100x167 40.3 ->
-//   19.4 us, B1 C64 75x100 8.0 -> 5.2; w = 7 23.9 -> 18.4 and 4.7 -> 4.1).  On
+//   19 us, B1 C64 75x100 8.0 -> 5.0; w = 7 23.9 -> 17.6 and 4.7 -> 4.0).  On
 //   maps they tile its whole-row copies are shorter (B128 C384 14x14 11.0
 //   against 14.5), and for w = 5 the two are equal.  The same products in
 //   the same order: the same bits.  (The general kernel needs a tensor of 16
@@ -2801,7 +2805,14 @@ constexpr bool kGenWindow = !Tag::W16 && rp_of(WIN) == 16;
 
 template <class Tag, int WIN>
 static bool gen_map(const Geom &g) {
-  return Tag::W16 && WIN >= 7 && (g.H % WIN != 0 || g.W % WIN != 0) && g.B * g.C * g.H * g.W >= 16;
+  const int64_t numel = g.B * g.C * g.H * g.W;
+  if constexpr (Tag::W16) {
+    return WIN >= 7 && (g.H % WIN != 0 || g.W % WIN != 0) && numel >= 16;
+  } else {
+    KArgs a = make_args(g);
+    set_tiled<WIN, Tag::ES>(g, a, {});
+    return WIN >= 4 && numel >= (int64_t)1 << 21 && (!a.tiled || (WIN >= 7 && g.NW >= 2));
+  }
 }
 
 template <class Tag, int WIN>
@@ -2951,8 +2962,10 @@ static hipError_t sum_slabs(const float *part, float *dt, int64_t n, const float
 // * float32 windows of 13 and more from 2 M elements: six products of bf16
 //   parts against float32 products (w = 14, us: B64 C192 28x28 63.6 -> 46.0, B128
 //   C192 28x28 122 -> 85, B128 C384 14x14 65 -> 52; but B1 C64 75x100 10.5
-//   against 12.6).  w = 10 has half its columns padding and gains nothing
-//   (B64 C192 20x20 38 against 36, B128 C384 10x10 33 against 38).
+//   against 12.6), and of 7 and 8 where the forward takes them too (w = 7
+//   B128 C192 14x14 24.5 -> 18.9, B32 C256 37x53 57 -> 46).  w = 10 has half its
+//   columns padding and gains nothing (B64 C192 20x20 38 against 36, B128 C384
+//   10x10 33 against 38), nor does w = 5 (B32 C256 37x53 70 against 80).
 // * 16-bit rows without fixed offsets (odd windows, cut maps, window counts
 //   that are no power of two, odd addresses), which the four-wave kernels
 //   address row by row and read element by element where odd: from 2 M
@@ -2965,7 +2978,7 @@ static hipError_t sum_slabs(const float *part, float *dt, int64_t n, const float
 template <class Tag, int WIN>
 static bool gen_grad(const Geom &g, bool tiled) {
   const int64_t numel = g.B * g.C * g.H * g.W;
-  if (!Tag::W16) return WIN >= 13 && numel >= (int64_t)1 << 21;
+  if (!Tag::W16) return (WIN >= 13 && numel >= (int64_t)1 << 21) || ((WIN == 7 || WIN == 8) && gen_map<Tag, WIN>(g));
   return !tiled && numel >= (int64_t)1 << (rp_of(WIN) == 8 ? 21 : 22);
 }
 
@@ -3069,14 +3082,15 @@ static hipError_t run_backward_fused(const void *x, const void *dy, const void *
 template <class Tag, int WIN>
 static hipError_t run_backward(const void *x, const void *dy, const void *t, void *dx, float *dt, void *ws,
                                const Geom &g, hipStream_t st) {
-  if constexpr (kGenWindow<Tag, WIN>) {
+  if (!Tag::W16 && (kGenWindow<Tag, WIN> || gen_map<Tag, WIN>(g))) {
     // dY is read twice, which costs less than the fused kernels' float32
-    // products (w = 14, B128 C192 28x28: 279 us fused, 157 as two launches)
+    // products (w = 14, B128 C192 28x28: 279 us fused, 148 as two launches;
+    // w = 7 B32 C256 37x53 100 and 78)
     const hipError_t e = run_forward<Tag, WIN>(dy, t, dx, g, true, st);
     return e != hipSuccess ? e : run_dtable<Tag, WIN>(x, dy, dt, ws, g, st);
-  } else {
-    return run_backward_fused<Tag, WIN>(x, dy, t, dx, dt, ws, g, st);
   }
+  if constexpr (kGenWindow<Tag, WIN>) return hipErrorInvalidValue;  // (not reached)
+  else return run_backward_fused<Tag, WIN>(x, dy, t, dx, dt, ws, g, st);
 }
 
 // Hierarchical form (global window WIN = 2 wl): one channel-stream pass when

@@ -117,29 +117,33 @@ def test_cut_maps_equal_padded_maps(w, dtype):
         assert torch.equal(f(xd, td, w), f(xp, td, w)[:, :, :H, :Wd])
 
 
-@pytest.mark.parametrize("w", [9, 14, 16])
-def test_float32_range(w):
+# few channels: the staged kernel (rows of eight: the direct one); many: enough
+# 16-window units for the direct one
+@pytest.mark.parametrize("w,C", [(9, 2), (14, 2), (16, 2), (5, 2), (7, 3), (9, 1024), (12, 700), (14, 1024), (16, 600)])
+def test_float32_range(w, C):
     """float32 rows and tables outside the range of the bf16 parts take
     float32 products: infinities and NaN reach exactly the outputs of their
     window, huge, tiny and denormal values keep float32's precision, and a
     zero table or zero rows give zeros."""
-    B, C, H, Wd = 3, 2, 2 * w, 3 * w
+    B, H, Wd = 3, 2 * w, 3 * w
+    fwd = W.wbmm_forward if w > 8 else (lambda x, t, w: W.wbmm_rect_forward(x, t, w, w))
     x, t = data(B, C, H, Wd, w, w, "f32", seed=w)
     m = t.double()[:, index(w, w)]
+    check(fwd(x.cuda(), t.cuda(), w), x, m, w, w, "f32", "plain")
     for s in (2.0 ** 70, 2.0 ** -100, 2.0 ** -120):
         xs = x * s
-        check(W.wbmm_forward(xs.cuda(), t.cuda(), w) / s, xs / s, m, w, w, "f32", "x scaled by %g" % s)
+        check(fwd(xs.cuda(), t.cuda(), w) / s, xs / s, m, w, w, "f32", "x scaled by %g" % s)
     for s in (2.0 ** 66, 2.0 ** -70):
-        check(W.wbmm_forward(x.cuda(), (t * s).cuda(), w) / s, x, m, w, w, "f32", "table scaled by %g" % s)
+        check(fwd(x.cuda(), (t * s).cuda(), w) / s, x, m, w, w, "f32", "table scaled by %g" % s)
     # a few rows far out of range beside ordinary ones
     xm = x.clone()
     xm[1, 0, 3] *= 2.0 ** 80
     xm[2, 1, w + 1] *= 2.0 ** -110
-    check(W.wbmm_forward(xm.cuda(), t.cuda(), w), xm, m, w, w, "f32", "mixed rows")
+    check(fwd(xm.cuda(), t.cuda(), w), xm, m, w, w, "f32", "mixed rows")
     for bad in (float("inf"), float("-inf"), float("nan")):
         xb = x.clone()
-        xb[1, 1, w + 2, 5] = bad
-        y = W.wbmm_forward(xb.cuda(), t.cuda(), w).cpu()
+        xb[1, 1, w + 2, 3] = bad
+        y = fwd(xb.cuda(), t.cuda(), w).cpu()
         hit = torch.zeros_like(xb, dtype=torch.bool)
         hit[1, 1, w:2 * w, 0:w] = True
         assert not torch.isfinite(y[hit]).any() and torch.isfinite(y[~hit]).all()
@@ -147,8 +151,8 @@ def test_float32_range(w):
             assert torch.isnan(y[hit]).all()
         else:
             assert torch.isinf(y[hit]).all()
-    assert not W.wbmm_forward(torch.zeros_like(x).cuda(), t.cuda(), w).any()
-    assert not W.wbmm_forward(x.cuda(), torch.zeros_like(t).cuda(), w).any()
+    assert not fwd(torch.zeros_like(x).cuda(), t.cuda(), w).any()
+    assert not fwd(x.cuda(), torch.zeros_like(t).cuda(), w).any()
 
 
 # rows without fixed offsets at the sizes the general gradients take, windows
@@ -189,9 +193,10 @@ def test_general_gradients(shape, dtype):
 
 
 @pytest.mark.parametrize("shape", [(20, 200, 27, 27, 13), (14, 192, 28, 28, 14), (10, 300, 30, 31, 15),
-                                   (3, 40, 160, 150, 16)], ids=lambda s: "B%dC%dH%dW%dw%d" % s)
+                                   (3, 40, 160, 150, 16), (64, 192, 14, 14, 7), (8, 96, 61, 50, 7), (5, 60, 96, 96, 8),
+                                   (9, 96, 56, 56, 5), (30, 90, 28, 28, 9)], ids=lambda s: "B%dC%dH%dW%dw%d" % s)
 def test_general_gradients_float32(shape):
-    """As above in float32, then with rows of x or dy out of the range of the
+    """As above in float32 (and the forward), then with rows of x or dy out of the range of the
     bf16 parts (their stages take float32 products)."""
     B, C, H, Wd, w = shape
     x, t = (v.cuda() for v in data(B, C, H, Wd, w, w, "f32", seed=w))
@@ -205,6 +210,7 @@ def test_general_gradients_float32(shape):
         dx, dt = W.wbmm_backward(x, dy, t, w)
         assert torch.equal(dt, W.wbmm_backward_table(x, dy, w))
         assert torch.equal(dx, W.wbmm_backward_input(dy, t, w))
+        assert torch.equal(W.wbmm_forward(x, t, w), W.wbmm_rect_forward(x, t, w, w))
         wdx, wdt = exact_gradients(x, dy, t, w)
         err = (dt.double() - wdt).abs().amax(1) / wdt.abs().amax(1)  # per channel: each has its own scale
         e_x = float((dx.double() - wdx).abs().max() / wdx.abs().max())
