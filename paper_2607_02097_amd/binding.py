@@ -18,6 +18,7 @@ rectangular windows, straight from the table or with a cached matrix.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -120,21 +121,47 @@ def wbmm_status_string(status: int) -> str:
     return load_library().wbmm_status_string(int(status)).decode()
 
 
-def _stream(t: torch.Tensor, stream):
+# The current device and the current stream's handle, without the Python
+# objects of torch.cuda's own accessors: a small call spends more of its host
+# time on those than on its launch.
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                              lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
+def _stream(t: torch.Tensor, stream) -> int:
+    """Handle of the stream a call on t is enqueued on."""
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+        return _current_raw_stream(t.get_device())
     if isinstance(stream, torch.cuda.Stream):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
+
+
+def _alike(a: torch.Tensor, b: torch.Tensor) -> bool:
+    """Same dtype and device (both GPU tensors)."""
+    return a.dtype == b.dtype and a.get_device() == b.get_device()
 
 
 def _check_tensor(t: torch.Tensor, name: str):
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError("%s must be a GPU tensor (got %s)" % (name, t.device))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
+
+
+def _call(fn_name, index, *args):
+    """The library call, with device ``index`` current."""
+    fn = getattr(_lib if _lib is not None else load_library(), fn_name)
+    if _current_device() == index:
+        st = fn(*args)
+    else:
+        with torch.cuda.device(index):
+            st = fn(*args)
+    if st != WBMM_OK:
+        raise WbmmError(st, fn_name)
 
 
 def _code(dtype) -> int:
@@ -143,29 +170,22 @@ def _code(dtype) -> int:
     return DTYPE_CODES[dtype]
 
 
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
-
-
 def _forward_like(fn_name, src, table, w, out, stream):
     _check_tensor(src, "input")
     _check_tensor(table, "table")
     if src.dim() != 4:
         raise ValueError("input must be [B, C, H, W]")
     B, C, H, W = src.shape
-    if table.dtype != src.dtype or table.device != src.device:
+    if not _alike(table, src):
         raise ValueError("table must match the input's dtype and device")
     if out is None:
         out = torch.empty_like(src)
     else:
         _check_tensor(out, "out")
-        if out.shape != src.shape or out.dtype != src.dtype or out.device != src.device:
+        if out.shape != src.shape or not _alike(out, src):
             raise ValueError("out must match the input's shape, dtype and device")
-    with torch.cuda.device(src.device):
-        st = getattr(load_library(), fn_name)(_ptr(src), _ptr(table), _ptr(out), B, C, H, W,
-                                              int(w), _code(src.dtype), _stream(src, stream))
-    if st != WBMM_OK:
-        raise WbmmError(st, fn_name)
+    _call(fn_name, src.get_device(), src.data_ptr(), table.data_ptr(), out.data_ptr(), B, C, H, W, int(w),
+          _code(src.dtype), _stream(src, stream))
     return out
 
 
@@ -196,18 +216,28 @@ def _torch_stream(device, stream):
     return torch.cuda.ExternalStream(int(stream), device=device)
 
 
-def _cached_workspace(device, nbytes, stream, shape_key):
-    """A workspace kept per (device, stream, call shape).  The library writes
-    the partial sums it holds before reading them, so its contents on entry
-    do not matter; it is allocated on the stream the call is enqueued on."""
-    ts = _torch_stream(device, stream)
-    key = (str(device), ts.cuda_stream, shape_key)
-    ws = _WS_CACHE.get(key)
-    if ws is None:
-        with torch.cuda.stream(ts):
-            ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
-        _WS_CACHE[key] = ws
-    return ws
+@functools.lru_cache(maxsize=1024)
+def _workspace_bytes(fn_name, *dims) -> int:
+    """A workspace query of the library (a function of its arguments alone)."""
+    return int(getattr(load_library(), fn_name)(*dims))
+
+
+def _workspace_arg(x, workspace, stream, handle, need, shape_key):
+    """(pointer, bytes) of the workspace of a call on x: the caller's, or,
+    where the call needs one, a workspace kept per (device, stream, call
+    shape).  The library writes the partial sums it holds before reading them,
+    so its contents on entry do not matter; it is allocated on the stream the
+    call is enqueued on."""
+    if workspace is None:
+        if need == 0:
+            return None, 0
+        key = (x.get_device(), handle, shape_key)
+        workspace = _WS_CACHE.get(key)
+        if workspace is None:
+            with torch.cuda.stream(_torch_stream(x.device, stream)):
+                workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+            _WS_CACHE[key] = workspace
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 def new_workspace(nbytes: int, device="cuda") -> torch.Tensor:
@@ -226,7 +256,7 @@ def wbmm_backward_table(x: torch.Tensor, dy: torch.Tensor, w: int, out=None, wor
     cached per (device, stream, shape) is used."""
     _check_tensor(x, "x")
     _check_tensor(dy, "dy")
-    if dy.shape != x.shape or dy.dtype != x.dtype or dy.device != x.device:
+    if dy.shape != x.shape or not _alike(dy, x):
         raise ValueError("dy must match x's shape, dtype and device")
     B, C, H, W = x.shape
     k = (2 * int(w) - 1) ** 2
@@ -234,19 +264,14 @@ def wbmm_backward_table(x: torch.Tensor, dy: torch.Tensor, w: int, out=None, wor
         out = torch.empty((C, k), dtype=torch.float32, device=x.device)
     else:
         _check_tensor(out, "out")
-        if out.dtype != torch.float32 or out.numel() != C * k or out.device != x.device:
+        if out.dtype != torch.float32 or out.numel() != C * k or out.get_device() != x.get_device():
             raise ValueError("out must be float32 [C, (2w-1)^2] on x's device")
-    need = wbmm_backward_table_workspace_bytes(x.shape, w, x.dtype)
-    if workspace is None and need > 0:
-        workspace = _cached_workspace(x.device, need, stream, (tuple(x.shape), int(w), x.dtype))
-    ws_ptr = ctypes.c_void_p(workspace.data_ptr() if workspace is not None else 0)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    with torch.cuda.device(x.device):
-        st = load_library().wbmm_backward_table(_ptr(x), _ptr(dy), _ptr(out), ws_ptr, ws_bytes,
-                                                B, C, H, W, int(w), _code(x.dtype),
-                                                _stream(x, stream))
-    if st != WBMM_OK:
-        raise WbmmError(st, "wbmm_backward_table")
+    w, code, handle = int(w), _code(x.dtype), _stream(x, stream)
+    ws_ptr, ws_bytes = _workspace_arg(x, workspace, stream, handle,
+                                      _workspace_bytes("wbmm_backward_table_workspace_bytes", B, C, H, W, w, code),
+                                      (B, C, H, W, w, code))
+    _call("wbmm_backward_table", x.get_device(), x.data_ptr(), dy.data_ptr(), out.data_ptr(), ws_ptr, ws_bytes,
+          B, C, H, W, w, code, handle)
     return out
 
 
@@ -263,9 +288,9 @@ def wbmm_backward(x: torch.Tensor, dy: torch.Tensor, table: torch.Tensor, w: int
     _check_tensor(x, "x")
     _check_tensor(dy, "dy")
     _check_tensor(table, "table")
-    if dy.shape != x.shape or dy.dtype != x.dtype or dy.device != x.device:
+    if dy.shape != x.shape or not _alike(dy, x):
         raise ValueError("dy must match x's shape, dtype and device")
-    if table.dtype != x.dtype or table.device != x.device:
+    if not _alike(table, x):
         raise ValueError("table must match x's dtype and device")
     B, C, H, W = x.shape
     k = (2 * int(w) - 1) ** 2
@@ -273,25 +298,20 @@ def wbmm_backward(x: torch.Tensor, dy: torch.Tensor, table: torch.Tensor, w: int
         dx = torch.empty_like(x)
     else:
         _check_tensor(dx, "dx")
-        if dx.shape != x.shape or dx.dtype != x.dtype or dx.device != x.device:
+        if dx.shape != x.shape or not _alike(dx, x):
             raise ValueError("dx must match x's shape, dtype and device")
     if dtable is None:
         dtable = torch.empty((C, k), dtype=torch.float32, device=x.device)
     else:
         _check_tensor(dtable, "dtable")
-        if dtable.dtype != torch.float32 or dtable.numel() != C * k or dtable.device != x.device:
+        if dtable.dtype != torch.float32 or dtable.numel() != C * k or dtable.get_device() != x.get_device():
             raise ValueError("dtable must be float32 [C, (2w-1)^2] on x's device")
-    need = wbmm_backward_workspace_bytes(x.shape, w, x.dtype)
-    if workspace is None and need > 0:
-        workspace = _cached_workspace(x.device, need, stream, (tuple(x.shape), int(w), x.dtype))
-    ws_ptr = ctypes.c_void_p(workspace.data_ptr() if workspace is not None else 0)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    with torch.cuda.device(x.device):
-        st = load_library().wbmm_backward(_ptr(x), _ptr(dy), _ptr(table), _ptr(dx), _ptr(dtable),
-                                          ws_ptr, ws_bytes, B, C, H, W, int(w), _code(x.dtype),
-                                          _stream(x, stream))
-    if st != WBMM_OK:
-        raise WbmmError(st, "wbmm_backward")
+    w, code, handle = int(w), _code(x.dtype), _stream(x, stream)
+    ws_ptr, ws_bytes = _workspace_arg(x, workspace, stream, handle,
+                                      _workspace_bytes("wbmm_backward_workspace_bytes", B, C, H, W, w, code),
+                                      (B, C, H, W, w, code))
+    _call("wbmm_backward", x.get_device(), x.data_ptr(), dy.data_ptr(), table.data_ptr(), dx.data_ptr(),
+          dtable.data_ptr(), ws_ptr, ws_bytes, B, C, H, W, w, code, handle)
     return dx, dtable
 
 
@@ -307,11 +327,8 @@ def wbmm_backward_noalloc(x: torch.Tensor, dy: torch.Tensor, table: torch.Tensor
     if table.dtype != x.dtype or dtable.dtype != torch.float32:
         raise ValueError("table in x's dtype, dtable float32")
     B, C, H, W = x.shape
-    with torch.cuda.device(x.device):
-        st = load_library().wbmm_backward_noalloc(_ptr(x), _ptr(dy), _ptr(table), _ptr(dx), _ptr(dtable),
-                                                  B, C, H, W, int(w), _code(x.dtype), _stream(x, stream))
-    if st != WBMM_OK:
-        raise WbmmError(st, "wbmm_backward_noalloc")
+    _call("wbmm_backward_noalloc", x.get_device(), x.data_ptr(), dy.data_ptr(), table.data_ptr(), dx.data_ptr(),
+          dtable.data_ptr(), B, C, H, W, int(w), _code(x.dtype), _stream(x, stream))
     return dx, dtable
 
 
@@ -323,19 +340,16 @@ def _hier_like(fn_name, src, tg, tl, wl, out, stream):
         raise ValueError("input must be [B, C, H, W]")
     B, C, H, W = src.shape
     for t in (tg, tl):
-        if t.dtype != src.dtype or t.device != src.device:
+        if not _alike(t, src):
             raise ValueError("tables must match the input's dtype and device")
     if out is None:
         out = torch.empty_like(src)
     else:
         _check_tensor(out, "out")
-        if out.shape != src.shape or out.dtype != src.dtype or out.device != src.device:
+        if out.shape != src.shape or not _alike(out, src):
             raise ValueError("out must match the input's shape, dtype and device")
-    with torch.cuda.device(src.device):
-        st = getattr(load_library(), fn_name)(_ptr(src), _ptr(tg), _ptr(tl), _ptr(out), B, C, H, W,
-                                              int(wl), _code(src.dtype), _stream(src, stream))
-    if st != WBMM_OK:
-        raise WbmmError(st, fn_name)
+    _call(fn_name, src.get_device(), src.data_ptr(), tg.data_ptr(), tl.data_ptr(), out.data_ptr(), B, C, H, W, int(wl),
+          _code(src.dtype), _stream(src, stream))
     return out
 
 
@@ -360,34 +374,22 @@ def wbmm_hier_backward(x, dy, table_g, table_l, wl: int, workspace=None, stream=
     table gradients float32."""
     _check_tensor(x, "x")
     _check_tensor(dy, "dy")
-    if dy.shape != x.shape or dy.dtype != x.dtype or dy.device != x.device:
+    if dy.shape != x.shape or not _alike(dy, x):
         raise ValueError("dy must match x's shape, dtype and device")
     B, C, H, W = x.shape
     dx = torch.empty_like(x)
     dtg = torch.empty((C, (4 * int(wl) - 1) ** 2), dtype=torch.float32, device=x.device)
     dtl = torch.empty((C, (2 * int(wl) - 1) ** 2), dtype=torch.float32, device=x.device)
-    need = wbmm_hier_backward_workspace_bytes(x.shape, wl, x.dtype)
-    if workspace is None and need > 0:
-        workspace = _cached_workspace(x.device, need, stream, ("hier", tuple(x.shape), int(wl), x.dtype))
-    ws_ptr = ctypes.c_void_p(workspace.data_ptr() if workspace is not None else 0)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    with torch.cuda.device(x.device):
-        st = load_library().wbmm_hier_backward(_ptr(x), _ptr(dy), _ptr(table_g), _ptr(table_l), _ptr(dx),
-                                               _ptr(dtg), _ptr(dtl), ws_ptr, ws_bytes, B, C, H, W, int(wl),
-                                               _code(x.dtype), _stream(x, stream))
-    if st != WBMM_OK:
-        raise WbmmError(st, "wbmm_hier_backward")
+    wl, code, handle = int(wl), _code(x.dtype), _stream(x, stream)
+    ws_ptr, ws_bytes = _workspace_arg(x, workspace, stream, handle,
+                                      _workspace_bytes("wbmm_hier_backward_workspace_bytes", B, C, H, W, wl, code),
+                                      ("hier", B, C, H, W, wl, code))
+    _call("wbmm_hier_backward", x.get_device(), x.data_ptr(), dy.data_ptr(), table_g.data_ptr(), table_l.data_ptr(),
+          dx.data_ptr(), dtg.data_ptr(), dtl.data_ptr(), ws_ptr, ws_bytes, B, C, H, W, wl, code, handle)
     return dx, dtg, dtl
 
 
 # ------------------------------------------------ cached-matrix (dense) form
-
-def _call(fn_name, dev, *args):
-    with torch.cuda.device(dev):
-        st = getattr(load_library(), fn_name)(*args)
-    if st != WBMM_OK:
-        raise WbmmError(st, fn_name)
-
 
 def wbmm_build_matrix(table, wh: int, ww: int, out=None, stream=None):
     """M [C, d, d] (d = wh ww), M[c][i][j] = table[c][I(i, j)], in the
@@ -401,7 +403,7 @@ def wbmm_build_matrix(table, wh: int, ww: int, out=None, stream=None):
         _check_tensor(out, "out")
         if out.numel() != C * d * d or out.dtype != table.dtype or out.device != table.device:
             raise ValueError("out must be [C, d, d] in the table's dtype and device")
-    _call("wbmm_build_matrix", table.device, _ptr(table), _ptr(out), C, int(wh), int(ww), _code(table.dtype),
+    _call("wbmm_build_matrix", table.get_device(), table.data_ptr(), out.data_ptr(), C, int(wh), int(ww), _code(table.dtype),
           _stream(table, stream))
     return out
 
@@ -411,15 +413,15 @@ def _dense_like(fn_name, src, m, wh, ww, out, stream):
     _check_tensor(m, "m")
     B, C, H, W = src.shape
     d = int(wh) * int(ww)
-    if m.dtype != src.dtype or m.device != src.device or m.numel() != C * d * d:
+    if not _alike(m, src) or m.numel() != C * d * d:
         raise ValueError("m must be [C, d, d] in the input's dtype and device")
     if out is None:
         out = torch.empty_like(src)
     else:
         _check_tensor(out, "out")
-        if out.shape != src.shape or out.dtype != src.dtype or out.device != src.device:
+        if out.shape != src.shape or not _alike(out, src):
             raise ValueError("out must match the input's shape, dtype and device")
-    _call(fn_name, src.device, _ptr(src), _ptr(m), _ptr(out), B, C, H, W, int(wh), int(ww), _code(src.dtype),
+    _call(fn_name, src.get_device(), src.data_ptr(), m.data_ptr(), out.data_ptr(), B, C, H, W, int(wh), int(ww), _code(src.dtype),
           _stream(src, stream))
     return out
 
@@ -438,13 +440,13 @@ def wbmm_dense_backward_matrix(x, dy, wh: int, ww: int, out=None, stream=None):
     """dm [C, d, d] float32: sum over windows of x_window^T dy_window."""
     _check_tensor(x, "x")
     _check_tensor(dy, "dy")
-    if dy.shape != x.shape or dy.dtype != x.dtype or dy.device != x.device:
+    if dy.shape != x.shape or not _alike(dy, x):
         raise ValueError("dy must match x's shape, dtype and device")
     B, C, H, W = x.shape
     d = int(wh) * int(ww)
     if out is None:
         out = torch.empty((C, d, d), dtype=torch.float32, device=x.device)
-    _call("wbmm_dense_backward_matrix", x.device, _ptr(x), _ptr(dy), _ptr(out), B, C, H, W, int(wh), int(ww),
+    _call("wbmm_dense_backward_matrix", x.get_device(), x.data_ptr(), dy.data_ptr(), out.data_ptr(), B, C, H, W, int(wh), int(ww),
           _code(x.dtype), _stream(x, stream))
     return out
 
@@ -458,7 +460,7 @@ def wbmm_bin_matrix(dm, wh: int, ww: int, out=None, stream=None):
     k = (2 * int(wh) - 1) * (2 * int(ww) - 1)
     if out is None:
         out = torch.empty((C, k), dtype=torch.float32, device=dm.device)
-    _call("wbmm_bin_matrix", dm.device, _ptr(dm), _ptr(out), C, int(wh), int(ww), _stream(dm, stream))
+    _call("wbmm_bin_matrix", dm.get_device(), dm.data_ptr(), out.data_ptr(), C, int(wh), int(ww), _stream(dm, stream))
     return out
 
 
@@ -467,10 +469,10 @@ def _rect_like(fn_name, src, table, wh, ww, stream):
     _check_tensor(src, "input")
     B, C, H, W = src.shape
     k = (2 * int(wh) - 1) * (2 * int(ww) - 1)
-    if table.dtype != src.dtype or table.device != src.device or table.shape[0] != C or table.numel() < C * k:
+    if not _alike(table, src) or table.shape[0] != C or table.numel() < C * k:
         raise ValueError("table must be [C, (2wh-1)(2ww-1)] in the input's dtype and device")
     out = torch.empty_like(src)
-    _call(fn_name, src.device, _ptr(src), _ptr(table), _ptr(out), B, C, H, W, int(wh), int(ww), _code(src.dtype),
+    _call(fn_name, src.get_device(), src.data_ptr(), table.data_ptr(), out.data_ptr(), B, C, H, W, int(wh), int(ww), _code(src.dtype),
           _stream(src, stream))
     return out
 
@@ -494,16 +496,19 @@ def wbmm_rect_backward_table(x, dy, wh: int, ww: int, stream=None):
     [C, (2wh-1)(2ww-1)])."""
     _check_tensor(x, "x")
     _check_tensor(dy, "dy")
-    if dy.shape != x.shape or dy.dtype != x.dtype or dy.device != x.device:
+    if dy.shape != x.shape or not _alike(dy, x):
         raise ValueError("dy must match x's shape, dtype and device")
     B, C, H, W = x.shape
     code = _code(x.dtype)
-    need = int(load_library().wbmm_rect_backward_table_workspace_bytes(B, C, H, W, int(wh), int(ww), code))
+    need = _workspace_bytes("wbmm_rect_backward_table_workspace_bytes", B, C, H, W, int(wh), int(ww), code)
     # (the workspace belongs to the stream that the call runs on)
-    with torch.cuda.stream(_torch_stream(x.device, stream)):
+    if stream is None:
         ws = torch.empty(need, dtype=torch.uint8, device=x.device)
+    else:
+        with torch.cuda.stream(_torch_stream(x.device, stream)):
+            ws = torch.empty(need, dtype=torch.uint8, device=x.device)
     out = torch.empty((C, (2 * int(wh) - 1) * (2 * int(ww) - 1)), dtype=torch.float32, device=x.device)
-    _call("wbmm_rect_backward_table", x.device, _ptr(x), _ptr(dy), _ptr(out), _ptr(ws), need, B, C, H, W, int(wh),
+    _call("wbmm_rect_backward_table", x.get_device(), x.data_ptr(), dy.data_ptr(), out.data_ptr(), ws.data_ptr(), need, B, C, H, W, int(wh),
           int(ww), code, _stream(x, stream))
     return out
 
