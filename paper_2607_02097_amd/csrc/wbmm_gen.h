@@ -50,6 +50,17 @@ __device__ __attribute__((always_inline)) inline uint32_t div_by(uint32_t n, Fas
   return (uint32_t)(((uint64_t)n * f.m) >> f.sh);
 }
 
+// Workgroups of a launch, C tiles_per_ch of them: a grid dimension holds fewer
+// than 2^32 threads, so more than 2^22 workgroups go on in the second one.
+constexpr int64_t kGenGridX = (int64_t)1 << 22;
+__host__ inline dim3 gen_grid(int64_t wgs) {
+  if (wgs <= kGenGridX) return dim3((unsigned)wgs);
+  return dim3((unsigned)kGenGridX, (unsigned)((wgs + kGenGridX - 1) / kGenGridX));
+}
+__device__ __attribute__((always_inline)) inline uint32_t gen_block() {
+  return blockIdx.y * gridDim.x + die_major(blockIdx.x, gridDim.x);
+}
+
 struct GenArgs {
   int64_t C, H, W;
   int64_t hw, chw;   // H W, C H W
@@ -604,8 +615,9 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, ln = lane & 15;
-  const uint32_t bid = die_major(blockIdx.x, gridDim.x);
+  const uint32_t bid = gen_block();
   const int64_t c = bid / (uint32_t)a.tiles_per_ch;
+  if (c >= a.C) return;
   const int s0 = (int)(bid - (uint32_t)c * (uint32_t)a.tiles_per_ch) * a.spw;
   const int nst = a.stages - s0 < a.spw ? a.stages - s0 : a.spw;
   const uint32_t n0 = (uint32_t)s0 * G::CW;
@@ -885,8 +897,9 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, ln = lane & 15;
-  const uint32_t bid = die_major(blockIdx.x, gridDim.x);
+  const uint32_t bid = gen_block();
   const int64_t c = bid / (uint32_t)a.tiles_per_ch;
+  if (c >= a.C) return;
   // units of this workgroup (spw rounds of eight), this wave's every eighth
   const int u0 = (int)(bid - (uint32_t)c * (uint32_t)a.tiles_per_ch) * a.spw * kGenWaves;
   const int nu = (int)((a.N + 15) / 16);
@@ -1139,8 +1152,9 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, ln = lane & 15;
-  const uint32_t bid = die_major(blockIdx.x, gridDim.x);
+  const uint32_t bid = gen_block();
   const int64_t c = bid / (uint32_t)a.tiles_per_ch;
+  if (c >= a.C) return;
   const int slab = (int)(bid - (uint32_t)c * (uint32_t)a.tiles_per_ch);
   const int s0 = slab * a.spw;
   const int nst = a.stages - s0 < a.spw ? a.stages - s0 : a.spw;

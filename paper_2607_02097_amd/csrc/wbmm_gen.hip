@@ -73,12 +73,12 @@ static hipError_t gen_fwd(const void *x, const void *coef, void *y, const Geom &
       typedef GenDirect<RP, S> D;
       a.stages = (int)cdiv64(a.N, 16 * kGenWaves);
       gen_plan(g.C, a.stages, ncu > 0 ? ncu : 256, 1.0, 1 << 20, &a.spw, &a.tiles_per_ch);
-      gen_direct_kernel<RP, S><<<dim3((unsigned)(g.C * a.tiles_per_ch)), dim3(kGenThreads), D::LDS, st>>>(
+      gen_direct_kernel<RP, S><<<gen_grid(g.C * a.tiles_per_ch), dim3(kGenThreads), D::LDS, st>>>(
           (const float *)x, (const float *)coef, (float *)y, a);
       return hipGetLastError();
     }
   }
-  const dim3 grid((unsigned)(g.C * a.tiles_per_ch)), block(kGenThreads);
+  const dim3 grid = gen_grid(g.C * a.tiles_per_ch), block(kGenThreads);
   constexpr size_t ltab = GenFwd<Tag, RP, S, false>::LDS, lmat = GenFwd<Tag, RP, S, true>::LDS;
   static_assert(ltab <= 160 * 1024 && lmat <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
   if (src >= kSrcMat)
@@ -162,7 +162,7 @@ static hipError_t gen_dt(const void *x, const void *dy, const void *t, void *dx,
   const int ncu = compute_units();
   gen_plan(g.C, a.stages, ncu > 0 ? ncu : 256, 3.0, max_slabs, &a.spw, &a.tiles_per_ch);
   float *out = a.tiles_per_ch > 1 ? ws : dt;
-  const dim3 grid((unsigned)(g.C * a.tiles_per_ch)), block(kGenThreads);
+  const dim3 grid = gen_grid(g.C * a.tiles_per_ch), block(kGenThreads);
   constexpr size_t lds = GenDt<Tag, RP, S, false>::LDS, flds = GenDt<Tag, RP, S, Tag::W16>::LDS;
   static_assert(lds <= 160 * 1024 && flds <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
   if (dx)

@@ -260,3 +260,22 @@ def test_rectangular_errors_and_streams():
     got = W.wbmm_rect_backward_table(x, x, 4, 9, stream=s)
     s.synchronize()
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_more_channels_than_one_grid_dimension(dtype):
+    """2^23 + 5 channels of one 1 x 2 window: at 512 threads a channel more
+    than the 2^32 threads of a grid dimension.  y0 = x0 T1 + x1 T2, y1 = x0 T0
+    + x1 T1; dT = (x0 dy1, x0 dy0 + x1 dy1, x1 dy0).  Small whole numbers:
+    every result is exact."""
+    C, td = 2 ** 23 + 5, TORCH_DTYPE[dtype]
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x, dy, t = (torch.randint(-3, 4, s, generator=g, device="cuda").to(td) for s in ((1, C, 1, 2), (1, C, 1, 2), (C, 3)))
+    x0, x1, d0, d1 = x[0, :, 0, 0], x[0, :, 0, 1], dy[0, :, 0, 0], dy[0, :, 0, 1]
+    t0, t1, t2 = t.unbind(1)
+    y = W.wbmm_rect_forward(x, t, 1, 2)
+    assert torch.equal(y[0, :, 0], torch.stack([x0 * t1 + x1 * t2, x0 * t0 + x1 * t1], 1))
+    dx = W.wbmm_rect_backward_input(dy, t, 1, 2)
+    assert torch.equal(dx[0, :, 0], torch.stack([d0 * t1 + d1 * t0, d0 * t2 + d1 * t1], 1))
+    dt = W.wbmm_rect_backward_table(x, dy, 1, 2)
+    assert torch.equal(dt, torch.stack([x0 * d1, x0 * d0 + x1 * d1, x1 * d0], 1).float())
