@@ -58,23 +58,23 @@ def parse():
 # on (sha256 of the kernel header's code without comments and blank lines);
 # otherwise reported as null.
 TRAFFIC = {
-    ("bf16_b128_c384_14_w14", "bwd"): {"source": "c5c88ade4f762eae", "bytes": 60216951},
-    ("bf16_b128_c384_14_w14", "dt"): {"source": "c5c88ade4f762eae", "bytes": 40341241},
-    ("bf16_b128_c384_14_w14", "dx"): {"source": "c5c88ade4f762eae", "bytes": 39186822},
-    ("bf16_b128_c384_14_w14", "fwd"): {"source": "c5c88ade4f762eae", "bytes": 39195548},
-    ("bf16_b16_c64_112_hier7", "hbwd"): {"source": "c5c88ade4f762eae", "bytes": 79881986},
-    ("bf16_b16_c64_112_hier7", "hfwd"): {"source": "c5c88ade4f762eae", "bytes": 51712583},
-    ("bf16_b16_c64_112_w14", "bwd"): {"source": "c5c88ade4f762eae", "bytes": 78627980},
-    ("bf16_b16_c64_112_w14", "dt"): {"source": "c5c88ade4f762eae", "bytes": 52797942},
-    ("bf16_b16_c64_112_w14", "dx"): {"source": "c5c88ade4f762eae", "bytes": 51593424},
-    ("bf16_b16_c64_112_w14", "fwd"): {"source": "c5c88ade4f762eae", "bytes": 51586736},
-    ("bf16_b64_c192_28_hier7", "hbwd"): {"source": "c5c88ade4f762eae", "bytes": 60621653},
-    ("bf16_b64_c192_28_hier7", "hfwd"): {"source": "c5c88ade4f762eae", "bytes": 40013008},
-    ("bf16_b64_c192_28_w14", "bwd"): {"source": "c5c88ade4f762eae", "bytes": 59373612},
-    ("bf16_b64_c192_28_w14", "dt"): {"source": "c5c88ade4f762eae", "bytes": 39781561},
-    ("bf16_b64_c192_28_w14", "dx"): {"source": "c5c88ade4f762eae", "bytes": 39369981},
-    ("bf16_b64_c192_28_w14", "fwd"): {"source": "c5c88ade4f762eae", "bytes": 39392765},
-    ("bf16_b64_c96_56_w7", "fwd"): {"source": "c5c88ade4f762eae", "bytes": 77247279},
+    ("bf16_b128_c384_14_w14", "bwd"): {"source": "f5b382451a5f9b02", "bytes": 60217239},
+    ("bf16_b128_c384_14_w14", "dt"): {"source": "f5b382451a5f9b02", "bytes": 40341305},
+    ("bf16_b128_c384_14_w14", "dx"): {"source": "f5b382451a5f9b02", "bytes": 39188486},
+    ("bf16_b128_c384_14_w14", "fwd"): {"source": "f5b382451a5f9b02", "bytes": 39195004},
+    ("bf16_b16_c64_112_hier7", "hbwd"): {"source": "f5b382451a5f9b02", "bytes": 79881123},
+    ("bf16_b16_c64_112_hier7", "hfwd"): {"source": "f5b382451a5f9b02", "bytes": 51754503},
+    ("bf16_b16_c64_112_w14", "bwd"): {"source": "f5b382451a5f9b02", "bytes": 78628076},
+    ("bf16_b16_c64_112_w14", "dt"): {"source": "f5b382451a5f9b02", "bytes": 52797814},
+    ("bf16_b16_c64_112_w14", "dx"): {"source": "f5b382451a5f9b02", "bytes": 51581392},
+    ("bf16_b16_c64_112_w14", "fwd"): {"source": "f5b382451a5f9b02", "bytes": 51625840},
+    ("bf16_b64_c192_28_hier7", "hbwd"): {"source": "f5b382451a5f9b02", "bytes": 60623187},
+    ("bf16_b64_c192_28_hier7", "hfwd"): {"source": "f5b382451a5f9b02", "bytes": 39816000},
+    ("bf16_b64_c192_28_w14", "bwd"): {"source": "f5b382451a5f9b02", "bytes": 59373740},
+    ("bf16_b64_c192_28_w14", "dt"): {"source": "f5b382451a5f9b02", "bytes": 39781689},
+    ("bf16_b64_c192_28_w14", "dx"): {"source": "f5b382451a5f9b02", "bytes": 39369181},
+    ("bf16_b64_c192_28_w14", "fwd"): {"source": "f5b382451a5f9b02", "bytes": 39392045},
+    ("bf16_b64_c96_56_w7", "fwd"): {"source": "f5b382451a5f9b02", "bytes": 77242669},
 }
 
 
