@@ -29,7 +29,10 @@
  *   H x W (Sec. 3.4.1, "Handling Arbitrary Input Sizes").
  * - 16-bit inputs are multiplied on the matrix cores with float32
  *   accumulation; every output element is rounded once (nearest-even) from
- *   its float32 sum.  float32 inputs use float32 matrix-core products.
+ *   its float32 sum.  float32 inputs are multiplied at float32 precision,
+ *   with float32 products or as three bfloat16 parts whose partial products
+ *   reach 2^-24 of each product; values outside the parts' range, infinities
+ *   and NaN take float32 products.
  * - Work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
  *   default stream).  Calls are asynchronous: nothing is synchronised, and the
  *   caller must keep every buffer alive until the stream has passed the work.
@@ -52,7 +55,7 @@ extern "C" {
 #endif
 
 typedef enum {
-  WBMM_F32 = 0,  /* float32 storage and float32 products          */
+  WBMM_F32 = 0,  /* float32 storage and precision                  */
   WBMM_BF16 = 1, /* bfloat16 storage, float32 accumulation        */
   WBMM_F16 = 2   /* IEEE half storage, float32 accumulation       */
 } wbmm_dtype;
