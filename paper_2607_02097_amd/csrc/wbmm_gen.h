@@ -1083,6 +1083,195 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
   }
 }
 
+// ---------------------------------------------- 16-bit, many windows
+// The same for 16-bit values: one part per value, and every output tile of a
+// unit accumulated together, so that a fragment of the table (which depends
+// on 2 k - t alone) is read once per unit and serves every (K step, tile) pair
+// that uses it.  The sums run over the K steps in order, as in the staged
+// kernel: the same bits.
+//
+// What bounds it: the rows' way through the vector memory unit, 28 or 14 of
+// every 32 or 16 bytes a lane asks for.  Staged kernel and this one, us: bf16
+// w = 14 B8 C96 100x167 19.5 -> 18.6, w = 13 B16 C200 60x61 22.6 -> 20.8, w = 10
+// B8 C96 100x167 21.1 -> 19.0, w = 7 17.3 -> 15.7; float16 7 x 14 windows B32 C96
+// 56x56 13.7 -> 12.4, 16 x 3 windows B64 C40 48x48 15.6 -> 12.0.  Up to five K
+// steps two workgroups share a compute unit (128 registers); with six and more
+// that spilled (w = 14: 24.1), and one of twice the registers is the better.
+// Five steps hold half of the tiles at a time.
+template <int RP, int S>
+struct GenDirect16 {
+  static constexpr int NF = 4 * S - 2;
+  static constexpr int TP = S == 5 ? S : 2 * S;     // output tiles accumulated together
+  static constexpr int WGS = S <= 5 ? 2 : 1;        // workgroups per compute unit
+  static constexpr int TS_OFF = NF * 1024;          // table copy, then the masks of 0 .. 8 columns
+  static constexpr int MASK_OFF = TS_OFF + 2 * 976;
+  static constexpr size_t LDS = (size_t)MASK_OFF + 9 * 16;
+};
+
+// PADK: the window's rows do not fill the last K step
+template <class Tag, int RP, int S, bool PADK>
+__global__ __launch_bounds__(kGenThreads, (GenDirect16<RP, S>::WGS * 2)) void gen_direct16_kernel(const typename Tag::S *__restrict__ x,
+                                                                      const typename Tag::S *__restrict__ tab,
+                                                                      typename Tag::S *__restrict__ y, GenArgs a) {
+  typedef typename Tag::S E;
+  typedef GenDirect16<RP, S> D;
+  constexpr int KROWS = 32 / RP;  // window rows per K step
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, ln = lane & 15;
+  const uint32_t bid = gen_block();
+  const int64_t c = bid / (uint32_t)a.tiles_per_ch;
+  if (c >= a.C) return;
+  // units of this workgroup (spw rounds of eight), this wave's every eighth
+  const int u0 = (int)(bid - (uint32_t)c * (uint32_t)a.tiles_per_ch) * a.spw * kGenWaves;
+  const int nu = (int)((a.N + 15) / 16);
+  const int u1 = nu - u0 < a.spw * kGenWaves ? nu : u0 + a.spw * kGenWaves;
+
+  // ---- the table, ahead of the first rows
+  const int K2 = (2 * a.ww - 1) * (2 * a.wh - 1);
+  E *Ts = reinterpret_cast<E *>(smem + D::TS_OFF);
+  uint32_t *masks = reinterpret_cast<uint32_t *>(smem + D::MASK_OFF);
+  const E *tc = tab + c * K2;
+  E tv[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int k = tid + i * kGenThreads < K2 ? tid + i * kGenThreads : K2 - 1;
+    tv[i] = tc[a.src == kSrcTableRev ? K2 - 1 - k : k];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
+  // this lane's window of a unit: its first element, rows and columns inside
+  // the image (0 rows: no window)
+  struct Win {
+    int64_t eoff;
+    int rows, cols;
+  };
+  auto window = [&](int u) __attribute__((always_inline)) -> Win {
+    Win w = {0, 0, 0};
+    const uint32_t n = 16u * (uint32_t)u + ln;
+    const uint32_t b = div_by(n, a.dnhw), rem = n - b * a.NHW;
+    const uint32_t wy = div_by(rem, a.dnw), wx = rem - wy * a.NW;
+    const int h0 = (int)wy * a.wh, x0 = (int)wx * a.ww;
+    const bool ok = u < u1 && n < a.N;
+    w.rows = !ok ? 0 : (int)a.H - h0 < a.wh ? (int)a.H - h0 : a.wh;
+    w.cols = (int)a.W - x0 < a.ww ? (int)a.W - x0 : a.ww;
+    w.eoff = (int64_t)b * a.chw + c * a.hw + (int64_t)h0 * a.W + x0;
+    return w;
+  };
+  const int hl = 8 * g / RP, x0 = 8 * g % RP;  // row within a K step, first column
+  const int64_t last = a.numel - 8;
+  typedef const __attribute__((address_space(1))) u32x4u *GP;
+  // (every lane loads, as in gen_load)
+  auto load = [&](const Win &w, u32x4u (&raw)[S]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int r = KROWS * s + hl;
+      int64_t e = w.eoff + (int64_t)r * a.W + x0;
+      e = e < last ? e : last;
+      const uint64_t p = r < w.rows && x0 < w.cols ? reinterpret_cast<uint64_t>(x + e) : reinterpret_cast<uint64_t>(gen_zero);
+      raw[s] = *reinterpret_cast<GP>(p);
+    }
+  };
+  u32x4u raw[S];
+  Win cur = window(u0 + wave);
+  load(cur, raw);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int k = tid + i * kGenThreads;
+    if (k < K2 + 10) Ts[k] = k < K2 ? tv[i] : (E)0;
+  }
+  if (tid < 36) {
+    const int cols = tid >> 2, i = tid & 3;
+    masks[tid] = cols > 2 * i + 1 ? ~0u : cols > 2 * i ? 0xffffu : 0u;
+  }
+  __syncthreads();
+  // ---- its fragments, in lane order
+  for (int ch = tid; ch < D::NF * 64; ch += kGenThreads) {
+    const int l = ch & 63, lg = l >> 4, lo = l & 15;
+    const int dh = (ch / 64 - (2 * S - 1)) * (16 / RP) + 8 * lg / RP - lo / RP, xo = lo % RP, xi = 8 * lg % RP;
+    const bool ok = dh > -a.wh && dh < a.wh && xo < a.ww;
+    const int nv = ok ? a.ww - xi : 0;  // columns inside the window
+    const int base = ok ? (dh + a.wh - 1) * (2 * a.ww - 1) + xi - xo + a.ww - 1 : 0;
+    const uint32_t *q = reinterpret_cast<const uint32_t *>(Ts) + (base >> 1);
+    const uint32_t sh = (uint32_t)(base & 1) * 16u;
+    uint32_t d[5], u[4];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) d[i] = q[i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w = __builtin_amdgcn_alignbit(d[i + 1], d[i], sh);
+      u[i] = nv > 2 * i + 1 ? w : nv > 2 * i ? (w & 0xffffu) : 0u;
+    }
+    *reinterpret_cast<uint4 *>(smem + ch * 16) = make_uint4(u[0], u[1], u[2], u[3]);
+  }
+  __syncthreads();
+
+  const unsigned char *tb = smem + lane * 16;
+  const bool pad = PADK && KROWS * (S - 1) + hl >= a.wh;  // rows past the window: zero coefficients there
+  for (int u = u0 + wave; u < u1; u += kGenWaves) {
+    GFrag xf[S];
+    {
+      const int nv = cur.cols - x0 < 0 ? 0 : cur.cols - x0 > 8 ? 8 : cur.cols - x0;
+      const uint4 m = *reinterpret_cast<const uint4 *>(masks + 4 * nv);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        uint32_t d[4] = {raw[s].x, raw[s].y, raw[s].z, raw[s].w};
+        const int r = KROWS * s + hl;
+        const int64_t over = cur.eoff + (int64_t)r * a.W + x0 - last;
+        if (r < cur.rows && x0 < cur.cols && over > 0) {
+          // within eight elements of the tensor's end: see gen_tail
+#pragma unroll 1
+          for (int k = (int)over; k > 0; --k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[i] = __builtin_amdgcn_alignbit(i < 3 ? d[i + 1] : 0u, d[i], 16);
+        }
+        xf[s] = __builtin_bit_cast(GFrag, make_uint4(d[0] & m.x, d[1] & m.y, d[2] & m.z, d[3] & m.w));
+        asm volatile("" : "+v"(xf[s]));
+      }
+    }
+    const Win w = cur;
+    cur = window(u + kGenWaves);
+    load(cur, raw);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t0 = 0; t0 < 2 * S; t0 += D::TP) {
+      f32x4 acc[D::TP];
+#pragma unroll
+      for (int t = 0; t < D::TP; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int f = 0; f < D::NF; ++f) {
+        const int q = f - (2 * S - 1);  // 2 k - t
+        if (q > 2 * (S - 1) - t0 || q < 1 - t0 - D::TP) continue;
+        const GFrag fr = *reinterpret_cast<const GFrag *>(tb + f * 1024);
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+          const int t = 2 * k - q - t0;
+          if (t < 0 || t >= D::TP) continue;
+          if (PADK && k == S - 1) acc[t] = mma<Tag>(pad ? GFrag{0, 0, 0, 0, 0, 0, 0, 0} : fr, xf[k], acc[t]);
+          else acc[t] = mma<Tag>(fr, xf[k], acc[t]);
+        }
+      }
+      // window ln, positions 16 (t0 + t) + 4 g .. + 3
+#pragma unroll
+      for (int t = 0; t < D::TP; ++t) {
+        const int r = 16 / RP * (t0 + t) + 4 * g / RP, xc = 4 * g % RP;
+        const int nc = r < w.rows ? w.cols - xc : 0;
+        const uint32_t a0 = pack2<Tag>(acc[t][0], acc[t][1]), a1 = pack2<Tag>(acc[t][2], acc[t][3]);
+        E *q = y + w.eoff + (int64_t)r * a.W + xc;
+        if (nc >= 4) {
+          *reinterpret_cast<u32x2u *>(q) = u32x2u{a0, a1};
+        } else if (nc > 0) {
+          if (nc >= 2) *reinterpret_cast<u32u *>(q) = a0;
+          if (nc & 1) q[nc - 1] = (E)((nc == 1 ? a0 : a1) & 0xffffu);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
 // ---------------------------------------------------- table gradient
 // dT = the sums of X^T dY over windows along equal offsets.  K = windows: the
 // position-major fragments of x and dy come from transposing reads of their

@@ -78,6 +78,22 @@ static hipError_t gen_fwd(const void *x, const void *coef, void *y, const Geom &
       return hipGetLastError();
     }
   }
+  if constexpr (Tag::W16) {
+    // 16-bit from the table: the same line of half of the chip's waves (bf16,
+    // w = 14, us: B4 C96 75x124, 1344 units, 9.5 -> 8.7; B1 C64 75x100, 192 units,
+    // 5.0 against 6.5; 5 x 9 windows B4 C64 45x63, 1024 units, 4.8 -> 4.7)
+    if (src < kSrcMat && g.C * cdiv64(a.N, 16) >= 1024) {
+      typedef GenDirect16<RP, S> D;
+      a.stages = (int)cdiv64(a.N, 16 * kGenWaves);
+      gen_plan(g.C, a.stages, (ncu > 0 ? ncu : 256) * D::WGS, 1.0, 1 << 20, &a.spw, &a.tiles_per_ch);
+      const dim3 dgrid = gen_grid(g.C * a.tiles_per_ch);
+      if (wh % (32 / RP))
+        gen_direct16_kernel<Tag, RP, S, true><<<dgrid, dim3(kGenThreads), D::LDS, st>>>((const E *)x, (const E *)coef, (E *)y, a);
+      else
+        gen_direct16_kernel<Tag, RP, S, false><<<dgrid, dim3(kGenThreads), D::LDS, st>>>((const E *)x, (const E *)coef, (E *)y, a);
+      return hipGetLastError();
+    }
+  }
   const dim3 grid = gen_grid(g.C * a.tiles_per_ch), block(kGenThreads);
   constexpr size_t ltab = GenFwd<Tag, RP, S, false>::LDS, lmat = GenFwd<Tag, RP, S, true>::LDS;
   static_assert(ltab <= 160 * 1024 && lmat <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");

@@ -262,6 +262,30 @@ def test_rectangular_errors_and_streams():
     assert torch.equal(got, want)
 
 
+# one unit of 16 windows per wave (1024 units and more) against the staged
+# kernel, which the matrix form takes: the same products in the same order.
+# K steps 1..8, rows that fill the last K step and rows that do not, one round
+# of units per wave and several, cut maps that end inside a row load.
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B", [2, 13])
+@pytest.mark.parametrize("win", [(1, 1), (4, 8), (7, 7), (9, 5), (16, 3), (13, 8), (2, 16), (3, 9), (5, 11), (7, 14),
+                                 (9, 9), (12, 12), (13, 13), (14, 14), (15, 15), (16, 16)], ids=lambda w: "%dx%d" % w)
+def test_units_equal_stages(win, B, dtype):
+    wh, ww = win
+    C, H, Wd = 1030, 2 * wh - wh // 2, 2 * ww + 1
+    g = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randn((B, C, H, Wd), generator=g, device="cuda").to(TORCH_DTYPE[dtype])
+    t = (0.02 * torch.randn((C, (2 * wh - 1) * (2 * ww - 1)), generator=g, device="cuda")).to(TORCH_DTYPE[dtype])
+    # infinities stay where they belong
+    x[0, 3, 0, 0] = x[-1, 5, -1, -1] = float("inf")
+    t[7, 0] = t[9, -1] = float("inf")
+    m = W.wbmm_build_matrix(t, wh, ww)
+    for got, want in ((W.wbmm_rect_forward(x, t, wh, ww), W.wbmm_dense_forward(x, m, wh, ww)),
+                      (W.wbmm_rect_backward_input(x, t, wh, ww), W.wbmm_dense_backward_input(x, m, wh, ww))):
+        assert torch.equal(got.isnan(), want.isnan()), "NaN"
+        assert torch.equal(got.nan_to_num(1.0, 2.0, -2.0), want.nan_to_num(1.0, 2.0, -2.0))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_more_channels_than_one_grid_dimension(dtype):
     """2^23 + 5 channels of one 1 x 2 window: at 512 threads a channel more
