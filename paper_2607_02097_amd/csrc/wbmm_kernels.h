@@ -2772,6 +2772,19 @@ static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const
       return hipGetLastError();
     }
   }
+  // 16-bit rows without fixed offsets (as many windows a map row as are no
+  // power of two, misaligned tensors): the general kernels from 128 windows a
+  // channel on, rows of eight only where units of 16 windows fill half of the
+  // chip's waves.  us: w = 14 B64 C96 84x84 46.8 -> 40.8, B16 C256 42x70 17.8 ->
+  // 14.3; w = 10 B8 C96 120x240 27.6 -> 21.2; w = 7 B8 C96 84x168 17.0 -> 14.3; w = 5
+  // B64 C96 30x30 13.4 -> 11.1; w = 4 7.7 -> 6.6.  With fewer windows the fragments
+  // of a channel are built for too little work (w = 14 B32 C384 14x42, 96
+  // windows, 11.6 against 15.2; w = 6 B4 C64 30x30, 448 units, 3.6 against 3.8).
+  // The same products in the same order: the same bits.
+  if constexpr (Tag::W16 && WIN >= 4) {
+    if (g.N >= 128 && (rp_of(WIN) == 16 || g.C * cdiv64(g.N, 16) >= 1024))
+      return GenEntry<Tag>::forward(x, t, y, g, WIN, WIN, rev ? 1 : 0, st);
+  }
   if (rev)
     wbmm_fwd_kernel<Tag, WIN, true><<<grid, dim3(kFwdThreads), lds, st>>>((const S *)x, (const S *)t, nullptr, (S *)y, a);
   else
@@ -2796,8 +2809,9 @@ static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const
 // * 16-bit windows of 7 and more on maps they do not tile: the row kernel
 //   reads cut and odd rows element by element (w = 14, B8 C96 100x167 40.3 ->
 //   19 us, B1 C64 75x100 8.0 -> 5.0; w = 7 23.9 -> 17.6 and 4.7 -> 4.0).  On
-//   maps they tile its whole-row copies are shorter (B128 C384 14x14 11.0
-//   against 14.5), and for w = 5 the two are equal.  The same products in
+//   maps they tile its whole-row copies are shorter where rows have fixed
+//   offsets (B128 C384 14x14 11.0 against 14.5); for the others see
+//   run_forward_fixed.  The same products in
 //   the same order: the same bits.  (The general kernel needs a tensor of 16
 //   elements.)
 template <class Tag, int WIN>

@@ -286,6 +286,26 @@ def test_units_equal_stages(win, B, dtype):
         assert torch.equal(got.nan_to_num(1.0, 2.0, -2.0), want.nan_to_num(1.0, 2.0, -2.0))
 
 
+# three windows a map row (rows without fixed offsets), 135 windows a channel,
+# channels on either side of the line for rows of eight: the windows one by one
+# as images of their own take the fixed-layout kernels, with the same sums
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("w,C", [(4, 120), (5, 120), (6, 113), (7, 120), (8, 114), (8, 3), (9, 3), (11, 5), (14, 120), (16, 3)])
+def test_rows_without_fixed_offsets(w, C, dtype):
+    td = TORCH_DTYPE[dtype]
+    g = torch.Generator(device="cuda").manual_seed(w)
+    x = torch.randn((15, C, 3 * w, 3 * w), generator=g, device="cuda").to(td)
+    dy = torch.randn(x.shape, generator=g, device="cuda").to(td)
+    t = (0.02 * torch.randn((C, (2 * w - 1) ** 2), generator=g, device="cuda")).to(td)
+
+    def apart(v):
+        return v.reshape(15, C, 3, w, 3, w).permute(0, 2, 4, 1, 3, 5).reshape(135, C, w, w).contiguous()
+    assert torch.equal(apart(W.wbmm_forward(x, t, w)), W.wbmm_forward(apart(x), t, w))
+    dx = W.wbmm_backward_input(dy, t, w)
+    assert torch.equal(apart(dx), W.wbmm_backward_input(apart(dy), t, w))
+    assert torch.equal(W.wbmm_backward(x, dy, t, w)[0], dx)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_more_channels_than_one_grid_dimension(dtype):
     """2^23 + 5 channels of one 1 x 2 window: at 512 threads a channel more
