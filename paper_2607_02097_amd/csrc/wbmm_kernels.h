@@ -2757,8 +2757,6 @@ static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const
     }
   }
   constexpr size_t lds = fwd_lds_bytes<Tag, WIN>();
-  // float32 windows of 13 and more take up to 70 KB (LDS is reached with ds
-  // instructions only)
   static_assert(lds <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
   if constexpr (Tag::ES == 4 || WIN % 2 == 0) {
     set_tiled<WIN, Tag::ES>(g, a, {x, y});
@@ -2811,9 +2809,8 @@ static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const
 //   19 us, B1 C64 75x100 8.0 -> 5.0; w = 7 23.9 -> 17.6 and 4.7 -> 4.0).  On
 //   maps they tile its whole-row copies are shorter where rows have fixed
 //   offsets (B128 C384 14x14 11.0 against 14.5); for the others see
-//   run_forward_fixed.  The same products in
-//   the same order: the same bits.  (The general kernel needs a tensor of 16
-//   elements.)
+//   run_forward_fixed.  The same products in the same order: the same bits.
+//   (The general kernel needs a tensor of 16 elements.)
 template <class Tag, int WIN>
 constexpr bool kGenWindow = !Tag::W16 && rp_of(WIN) == 16;
 
