@@ -1276,10 +1276,18 @@ __global__ __launch_bounds__(kGenThreads, (GenDirect16<RP, S>::WGS * 2)) void ge
 // dT = the sums of X^T dY over windows along equal offsets.  K = windows: the
 // position-major fragments of x and dy come from transposing reads of their
 // window-major stages.  Wave (ph, pg) multiplies input tiles ph S .. + S - 1
-// with a quarter of the output tiles; products of tile pairs with equal
-// difference share an accumulator (S + NPO - 1 of them), so a wave reads
-// S + NPO fragments for S NPO products.  At the end every wave sums the
+// with a quarter of the output tiles.  Rows of sixteen: products of tile pairs
+// with equal difference share an accumulator (S + NPO - 1 of them); rows of
+// eight: one per pair (at most three more).  At the end every wave sums the
 // diagonals of its accumulators, and the waves' sums are added in order.
+//
+// Pads.  A pad position holds zero, and its product with an infinity or NaN
+// is NaN, which must reach no entry of dT.  Pad columns have places of their
+// own in every accumulator and are left out of the diagonals.  Pad rows: with
+// rows of sixteen a tile is one row, and the tiles past the window are not
+// multiplied; with rows of eight half a tile can be a pad row, and a shared
+// accumulator would add it to a row of the window, so each pair has its own
+// and the pad half is left out as the pad columns are.
 //
 // DX (16-bit): the fused backward.  The same stages feed the input gradient
 // dY M^T as in the forward kernel (wave T holds the reversed table's
@@ -1301,14 +1309,16 @@ struct GenDt {
   typedef GenCfg<Tag, RP, S> G;
   static_assert(!DX || Tag::W16, "fused backward: 16-bit");
   static constexpr int NPO = cdiv(G::NT, 4);       // output tiles of a wave (at most)
-  static constexpr int NR = S + NPO - 1;           // accumulators: i - q + NPO - 1
+  static constexpr int R = 16 / RP;                // window rows per tile
+  // accumulators, and the one of input tile i and output tile q of a wave
+  static constexpr int NR = R == 1 ? S + NPO - 1 : S * NPO;
+  __host__ __device__ static constexpr int at(int i, int q) { return R == 1 ? i - q + NPO - 1 : i * NPO + q; }
   static constexpr int KST = G::CW / 32;           // K steps per stage
   static constexpr int NBUF = Tag::W16 ? 2 : 1;    // stages in LDS
   // float32: the smaller partial products in sums of their own where the
   // registers allow
   static constexpr bool LOWACC = !Tag::W16 && S <= 6;
   static constexpr int STAGE = 2 * G::XB;          // x and dy
-  static constexpr int R = 16 / RP;                // window rows per tile
   static constexpr int NBIN = R * R * 2 * RP;      // diagonals of a tile's R x R blocks, padded
   static constexpr int BT = 4;                     // tiles binned at a time
   static constexpr int SCR = kGenWaves * BT * kBinTile * 4;
@@ -1350,7 +1360,10 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
   const uint32_t n0 = (uint32_t)s0 * G::CW;
   const int v = gen_slot_window<G>(a, tid), hi = gen_slot_row<G>(a, tid);
   const int ph = wave >> 2, pg = wave & 3;
-  const int po0 = gen_dt_cut<G::NT>(ph, pg), npo = gen_dt_cut<G::NT>(ph, pg + 1) - po0;
+  // (rows of sixteen: no products of the tiles past the window)
+  const int nto = D::R == 1 ? a.wh : G::NT, po1 = gen_dt_cut<G::NT>(ph, pg + 1);
+  const int po0 = gen_dt_cut<G::NT>(ph, pg), npo = (po1 < nto ? po1 : nto) - po0;
+  const bool xpad = D::R == 1 && ph * S + S - 1 >= a.wh;  // the last input tile is one of them
 
   auto row = [&](int s) __attribute__((always_inline)) -> GRow {
     return s < nst ? gen_row(a, c, n0 + s * G::CW + v, hi) : GRow{0, 0};
@@ -1394,20 +1407,21 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
         for (int q = 0; q < NPO; ++q) bf[q] = dt_frag16<G::LDSW>(gt, q < npo ? po0 + q : po0, lane);
 #pragma unroll
         for (int i = 0; i < S; ++i) {
+          if (i == S - 1 && xpad) continue;
           const GFrag af = dt_frag16<G::LDSW>(xt, ph * S + i, lane);
 #pragma unroll
           for (int q = 0; q < NPO; ++q)
-            if (q < npo) acc[i - q + NPO - 1] = mma<Tag>(af, bf[q], acc[i - q + NPO - 1]);
+            if (q < npo) acc[D::at(i, q)] = mma<Tag>(af, bf[q], acc[D::at(i, q)]);
         }
       }
     } else if (__builtin_amdgcn_readfirstlane(flag[s & 1]) == s) {
       // float32 products of a stage with far rows, from global memory
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-#pragma unroll 1
-        for (int q = 0; q < npo; ++q) {
-          const int i = r + q - (NPO - 1);
-          if (i < 0 || i >= S) continue;
+      for (int i = 0; i < S; ++i) {
+        if (i == S - 1 && xpad) continue;
+#pragma unroll
+        for (int q = 0; q < NPO; ++q) {
+          if (q >= npo) continue;
           const int pa = 16 * (ph * S + i) + ln, pb = 16 * (po0 + q) + ln;
 #pragma unroll 1
           for (int w = 0; w < G::CW; w += 4) {
@@ -1415,7 +1429,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
             const GRow ra = gen_row(a, c, n, pa / RP), rb = gen_row(a, c, n, pb / RP);
             const float av = pa % RP < ra.cols ? x[ra.eoff + pa % RP] : 0.f;
             const float bv = pb % RP < rb.cols ? dy[rb.eoff + pb % RP] : 0.f;
-            acc[r] = mma<TagF32>(av, bv, acc[r]);
+            acc[D::at(i, q)] = mma<TagF32>(av, bv, acc[D::at(i, q)]);
           }
         }
       }
@@ -1439,10 +1453,11 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
             for (int p = 0; p < 3; ++p) af[(i + 1) & 1][p] = dt_frag16<G::LDSW>(xt + p * G::PLANE, ph * S + i + 1, lane);
           }
           __builtin_amdgcn_sched_barrier(0);
+          if (i == S - 1 && xpad) continue;
           const GFrag(&f)[3] = af[i & 1];
 #define WBMM_DT_PART(PA, PB, ACC)                                                          \
-  _Pragma("unroll") for (int q = 0; q < NPO; ++q) if (q < npo) ACC[i - q + NPO - 1] =      \
-      mma_bf16(f[PA], bf[PB][q], ACC[i - q + NPO - 1]);
+  _Pragma("unroll") for (int q = 0; q < NPO; ++q) if (q < npo) ACC[D::at(i, q)] =          \
+      mma_bf16(f[PA], bf[PB][q], ACC[D::at(i, q)]);
           WBMM_DT_PART(2, 0, low)
           WBMM_DT_PART(0, 2, low)
           WBMM_DT_PART(1, 1, low)
@@ -1563,7 +1578,8 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
   // ---- diagonals of the wave's tiles, each R x R blocks of RP x RP: a block
   // is written skewed, element (xi, xo) at column (xo - xi) mod RP of row xi,
   // so that column s holds diagonal dw = -s above row RP - s and RP - s below;
-  // one lane sums one column of one block (pads are zero)
+  // one lane sums one column of one block.  Pad columns, and with rows of
+  // eight pad rows, are written as zero, whatever their products were.
   constexpr int R = D::R;
   float *scr = reinterpret_cast<float *>(smem) + wave * D::BT * kBinTile;
   float *bins = reinterpret_cast<float *>(smem + D::SCR);
@@ -1574,13 +1590,19 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int rr = 4 * g + e;
+      const bool cols = (rr & (RP - 1)) < a.ww && (ln & (RP - 1)) < a.ww;
       float *p = scr + rr * 17 + (ln & ~(RP - 1)) + ((ln - rr) & (RP - 1));
 #pragma unroll
       for (int j = 0; j < D::BT; ++j) {
         if (r0 + j >= NR) continue;
         float t = acc[r0 + j][e];
         if constexpr (D::LOWACC) t += low[r0 + j][e];
-        p[j * kBinTile] = t;
+        bool ok = cols;
+        if constexpr (R == 2) {
+          const int i = (r0 + j) / NPO, q = (r0 + j) % NPO;
+          ok = ok && 2 * (ph * S + i) + rr / RP < a.wh && 2 * (po0 + q) + ln / RP < a.wh;
+        }
+        p[j * kBinTile] = ok ? t : 0.f;
       }
     }
     wave_lds_sync();
@@ -1614,13 +1636,20 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
     float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < kGenWaves; ++w) {
-      const int base = gen_dt_cut<G::NT>(w >> 2, w & 3) - (w >> 2) * S + NPO - 1;
+      const int base = gen_dt_cut<G::NT>(w >> 2, w & 3) - (w >> 2) * S;
 #pragma unroll
       for (int b = 0; b < R * R; ++b) {
         const int pr = dh - (b / R - b % R);  // P R
         if (R == 2 && (pr & 1)) continue;
-        const int r = pr / R + base;
-        if (r >= 0 && r < NR) sum += bins[(w * NR + r) * D::NBIN + b * 2 * RP + RP - 1 + dw];
+        const float *t = bins + w * NR * D::NBIN + b * 2 * RP + RP - 1 + dw;
+        const int r = pr / R + base;  // i - q
+        if constexpr (R == 1) {
+          if (r + NPO - 1 >= 0 && r < S) sum += t[(r + NPO - 1) * D::NBIN];
+        } else {
+#pragma unroll
+          for (int q = 0; q < NPO; ++q)
+            if (r + q >= 0 && r + q < S) sum += t[D::at(r + q, q) * D::NBIN];
+        }
       }
     }
     o[k] = sum;

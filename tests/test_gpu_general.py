@@ -323,3 +323,38 @@ def test_more_channels_than_one_grid_dimension(dtype):
     assert torch.equal(dx[0, :, 0], torch.stack([d0 * t1 + d1 * t0, d0 * t2 + d1 * t1], 1))
     dt = W.wbmm_rect_backward_table(x, dy, 1, 2)
     assert torch.equal(dt, torch.stack([x0 * d1, x0 * d0 + x1 * d1, x1 * d0], 1).float())
+
+
+def pattern(v):
+    """0: finite, 1 and 2: the infinities, 3: NaN."""
+    v = v.float().cpu()
+    return torch.where(v.isnan(), 3, 0) + torch.where(v == float("inf"), 1, 0) + torch.where(v == -float("inf"), 2, 0)
+
+
+# rows of eight and of sixteen that the window fills and does not, odd and even
+# heights; square windows at sizes where both gradients take the general kernel
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(2, 3, 2 * h + 1, 2 * w + 1, h, w) for h, w in (
+    (1, 3), (2, 8), (5, 5), (7, 7), (8, 6), (9, 3), (11, 8), (13, 7), (15, 4), (16, 8), (1, 16), (3, 9), (6, 14),
+    (9, 12), (11, 16), (13, 13), (14, 14), (15, 10), (16, 16))]
+    + [(64, 40, 29, 31, 7, 7), (5, 60, 96, 96, 8, 8), (20, 200, 27, 27, 13, 13), (8, 96, 100, 61, 14, 14)],
+    ids=lambda s: "B%dC%dH%dW%dw%dx%d" % s)
+def test_gradient_infinities_stay_in_their_pairs(shape, dtype):
+    """Infinities and NaN at the corners of windows reach the table entries
+    of the pairs they are in and no others: entry by entry what the matrix
+    gradient, which has no pad positions, folds to."""
+    B, C, H, Wd, wh, ww = shape
+    x, _ = (v.cuda() for v in data(B, C, H, Wd, wh, ww, dtype, seed=1))
+    dy, t = (v.cuda() for v in data(B, C, H, Wd, wh, ww, dtype, seed=2))
+    inf, nan = float("inf"), float("nan")
+    x[1, 0, wh - 1, ww - 1] = inf
+    x[0, 1, 0, 0] = -inf
+    dy[1, 1, wh - 1, 0] = inf
+    dy[0, 2, 0, ww - 1] = nan
+    x[-1, 2, -1, -1] = inf
+    want = pattern(W.wbmm_bin_matrix(W.wbmm_dense_backward_matrix(x, dy, wh, ww), wh, ww))
+    assert want.any() and (wh * ww < 4 or not want[:, (2 * wh - 1) * (2 * ww - 1) // 2 - 1].all())
+    assert torch.equal(pattern(W.wbmm_rect_backward_table(x, dy, wh, ww)), want)
+    if B * C * H * Wd >= 2 ** 21:
+        assert torch.equal(pattern(W.wbmm_backward_table(x, dy, wh)), want)
+        assert torch.equal(pattern(W.wbmm_backward(x, dy, t, wh)[1]), want)
