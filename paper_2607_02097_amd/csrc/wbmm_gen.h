@@ -1316,7 +1316,14 @@ struct GenDt {
   static constexpr int KST = G::CW / 32;           // K steps per stage
   static constexpr int NBUF = Tag::W16 ? 2 : 1;    // stages in LDS
   // float32: the smaller partial products in sums of their own where the
-  // registers allow
+  // registers allow; elsewhere the five of a tile pair and 32 windows are summed
+  // from zero, smallest first, and added once.  All six in one accumulator
+  // rounded six times as often at the sum's full size, and always downwards:
+  // the matrix cores cut the addends that are small beside the largest.  That
+  // is also why the high parts' product is not among the five.  w = 14, error of
+  // dT against 64 bits, one accumulator -> five apart (all six from zero; float32
+  // products): B28 C36 98x98 6.0e-7 -> 1.9e-7 (4.0e-7; 4.0e-7), B1 C1 1500x1500
+  // 8.4e-7 -> 2.7e-7 (1.1e-6; 6.3e-7).
   static constexpr bool LOWACC = !Tag::W16 && S <= 6;
   static constexpr int STAGE = 2 * G::XB;          // x and dy
   static constexpr int NBIN = R * R * 2 * RP;      // diagonals of a tile's R x R blocks, padded
@@ -1455,15 +1462,30 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
           __builtin_amdgcn_sched_barrier(0);
           if (i == S - 1 && xpad) continue;
           const GFrag(&f)[3] = af[i & 1];
-#define WBMM_DT_PART(PA, PB, ACC)                                                          \
-  _Pragma("unroll") for (int q = 0; q < NPO; ++q) if (q < npo) ACC[D::at(i, q)] =          \
-      mma_bf16(f[PA], bf[PB][q], ACC[D::at(i, q)]);
-          WBMM_DT_PART(2, 0, low)
-          WBMM_DT_PART(0, 2, low)
-          WBMM_DT_PART(1, 1, low)
-          WBMM_DT_PART(1, 0, low)
-          WBMM_DT_PART(0, 1, low)
-          WBMM_DT_PART(0, 0, acc)
+#define WBMM_DT_PART(PA, PB, ACC) \
+  _Pragma("unroll") for (int q = 0; q < NPO; ++q) if (q < npo) ACC = mma_bf16(f[PA], bf[PB][q], ACC);
+          if constexpr (D::LOWACC) {
+            WBMM_DT_PART(2, 0, low[D::at(i, q)])
+            WBMM_DT_PART(0, 2, low[D::at(i, q)])
+            WBMM_DT_PART(1, 1, low[D::at(i, q)])
+            WBMM_DT_PART(1, 0, low[D::at(i, q)])
+            WBMM_DT_PART(0, 1, low[D::at(i, q)])
+            WBMM_DT_PART(0, 0, acc[D::at(i, q)])
+          } else {
+#pragma unroll
+            for (int q = 0; q < NPO; ++q) {
+              if (q >= npo) continue;
+              f32x4 t = mma_bf16(f[2], bf[0][q], f32x4{0.f, 0.f, 0.f, 0.f});
+              t = mma_bf16(f[0], bf[2][q], t);
+              t = mma_bf16(f[1], bf[1][q], t);
+              t = mma_bf16(f[1], bf[0][q], t);
+              t = mma_bf16(f[0], bf[1][q], t);
+              f32x4 &r = acc[D::at(i, q)];
+              r = mma_bf16(f[0], bf[0][q], r);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) r[e] += t[e];
+            }
+          }
 #undef WBMM_DT_PART
           __builtin_amdgcn_sched_barrier(0);
         }

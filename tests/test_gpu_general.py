@@ -358,3 +358,47 @@ def test_gradient_infinities_stay_in_their_pairs(shape, dtype):
     if B * C * H * Wd >= 2 ** 21:
         assert torch.equal(pattern(W.wbmm_backward_table(x, dy, wh)), want)
         assert torch.equal(pattern(W.wbmm_backward(x, dy, t, wh)[1]), want)
+
+
+def rounding(adds):
+    """The relative 2-norm error of a float32 sum of random terms added one by
+    one: an addition rounds by at most 2^-23 / sqrt(12) = 2^-24.8 of the partial
+    sum (rms), which after k of n has sqrt(k / n) of the result's size; half as
+    much again for the sums that do not grow so evenly.  (Leaving out any of the
+    six partial products would show as 2^-18 / 3 = 1.3e-6.)"""
+    return 1.5 * 2.0 ** -24.8 * (adds / 2) ** 0.5
+
+
+# table gradients with one and several stages per partial sum, up to six K
+# steps and more, many channels and one; products in units, in stages and from
+# a matrix
+@pytest.mark.parametrize("shape", [(28, 36, 98, 98, 14, 14), (1, 1, 1500, 1500, 13, 13), (1, 2, 1100, 1100, 16, 16),
+                                   (8, 195, 53, 71, 15, 15), (64, 192, 28, 28, 14, 14), (4, 31, 72, 60, 12, 12),
+                                   (64, 96, 56, 56, 7, 7), (9, 16, 65, 80, 16, 8), (1, 3, 40, 50, 9, 14),
+                                   (2, 8, 33, 40, 5, 5)], ids=lambda s: "B%dC%dH%dW%dw%dx%d" % s)
+def test_float32_precision(shape):
+    """float32 results are as good as sums of float32 products rounded once
+    per addition."""
+    B, C, H, Wd, wh, ww = shape
+    x, t = (v.cuda() for v in data(B, C, H, Wd, wh, ww, "f32", seed=wh))
+    dy, _ = (v.cuda() for v in data(B, C, H, Wd, wh, ww, "f32", seed=wh + 100))
+    xw, gw = windows(x.double(), wh, ww).contiguous(), windows(dy.double(), wh, ww).contiguous()
+    idx = index(wh, ww).cuda()
+    m = t.double()[:, idx]
+    ksteps = -(-wh // (4 if ww <= 8 else 2))  # of 32 positions; then the smaller parts' sum
+    windows_, rows = xw.shape[1], 16 + wh
+    want = {"y": unwindows(torch.bmm(xw, m), x.shape, wh, ww),
+            "dx": unwindows(torch.bmm(gw, m.transpose(1, 2).contiguous()), x.shape, wh, ww),
+            "dt": torch.zeros(t.shape, dtype=torch.float64, device="cuda").index_add_(
+                1, idx.flatten(), torch.bmm(xw.transpose(1, 2).contiguous(), gw).flatten(1))}
+    got = {"y": W.wbmm_rect_forward(x, t, wh, ww), "dx": W.wbmm_rect_backward_input(dy, t, wh, ww),
+           "dt": W.wbmm_rect_backward_table(x, dy, wh, ww)}
+    got["y matrix"] = W.wbmm_dense_forward(x, W.wbmm_build_matrix(t, wh, ww), wh, ww)
+    if wh == ww and B * C * H * Wd >= 2 ** 21:
+        got["dt square"] = W.wbmm_backward_table(x, dy, wh)
+    for k, v in got.items():
+        w = want[k.split()[0]]
+        err = float((v.double() - w).norm() / w.norm())
+        bound = rounding(-(-windows_ // 32) + rows if k[:2] == "dt" else ksteps + 2)
+        print(shape, k, "%.1e of %.1e" % (err, bound), flush=True)
+        assert err <= bound, k
