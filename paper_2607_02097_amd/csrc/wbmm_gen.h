@@ -259,7 +259,14 @@ __device__ __attribute__((always_inline)) inline void gen_store(typename Tag::S 
 // bf16 rate is sixteen times the float32 matrix rate, six products cost 3/8 of
 // a float32 one.  Ranges where a part would overflow or vanish (and
 // infinities and NaN) take float32 products instead: a row is "far" when its
-// largest magnitude is at least 2^60, or not zero and below 2^-96.
+// largest magnitude is at least 2^60, or not zero and below 2^-96.  What that
+// costs, every row far, us (ordinary values; the float32 row kernels): forward
+// w = 14 B128 C256 56x56 4390 -> 750 (280; 800), w = 7 B64 C96 56x56 174 -> 62 (38;
+// 45), both gradients w = 14 B128 C192 28x28 2240 -> 325 (156; 273), w = 7 434 ->
+// 136 (82; 144), a cached matrix w = 14 B64 C192 28x28 713 -> 238 (74; 406).
+// Before, every product recomputed its window's address and read both values
+// from global memory; now four values of a row serve every output tile of a
+// wave (forward), or a stage's rows lie in LDS as float32 (gradient).
 constexpr uint32_t kFarHi = (127u + 60u) << 23, kFarLo = (127u - 96u) << 23;
 constexpr uint32_t kFarLoCoef = (127u - 60u) << 23;
 
@@ -543,24 +550,56 @@ __device__ __attribute__((always_inline)) inline void gen_frags_mat32(const GenA
   }
 }
 
-// float32 products of one sub-tile straight from global memory (stages with
-// far rows, far coefficients): slow, and the same for every shape.
+// float32 products of one window per lane and a tile pair (far rows, far
+// coefficients): four columns of one window row per lane at a time, from
+// global memory, and the same four input positions' coefficients from cc, the
+// channel's table or matrix (src as in GenArgs).
 template <int RP, int S>
-__device__ __attribute__((always_inline)) inline f32x4 gen_far_tile(const GenArgs &a, const float *x, const float *coef, int64_t c,
-                                                        uint32_t n, int j, int g) {
-  const int ho = j / RP, xo = j % RP;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-  for (int s = 0; s < 8 * S; ++s) {
-    const int k = 4 * s + g;
-    const int hi = k / RP, xi = k % RP;
-    float bv = 0.f, av = 0.f;
-    if (hi < a.wh && xi < a.ww && ho < a.wh && xo < a.ww) bv = coef[gen_coef<TagF32>(a, c, hi, xi, ho, xo)];
-    const GRow r = gen_row(a, c, n, hi);
-    if (xi < r.cols) av = x[r.eoff + xi];
-    acc = mma<TagF32>(bv, av, acc);
+__device__ __attribute__((always_inline)) inline void gen_far_pair(const GenArgs &a, const float *x, const float *cc,
+                                                                   int src, int64_t c, uint32_t n, int T, int lane,
+                                                                   f32x4 (&acc)[2]) {
+  asm volatile("" : "+v"(lane));  // (what follows from it stays in this branch)
+  const int g = lane >> 4, ln = lane & 15;
+  const int hl = 8 * g / RP, x0 = 8 * g % RP;
+  const int K1 = 2 * a.ww - 1, K2 = K1 * (2 * a.wh - 1), d = a.wh * a.ww;
+  // coefficient of the lane's first input position at window row 0, and the
+  // steps to the next column and row
+  const int col = src == kSrcTable || src == kSrcMatT ? 1 : src == kSrcTableRev ? -1 : d;
+  const int rstep = src == kSrcTable ? K1 : src == kSrcTableRev ? -K1 : a.ww * col;
+  int base[2];
+  bool out[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int j = 32 * T + 16 * h + ln, ho = j / RP, xo = j % RP;
+    out[h] = ho < a.wh && xo < a.ww;
+    const int k = (a.wh - 1 - ho) * K1 + x0 - xo + a.ww - 1, p = ho * a.ww + xo;
+    base[h] = src == kSrcTable ? k : src == kSrcTableRev ? K2 - 1 - k : src == kSrcMat ? x0 * d + p : p * d + x0;
   }
-  return acc;
+#pragma unroll 1
+  for (int q = 0; q < 2 * S; ++q) {
+    const int hi = (q >> 1) * (32 / RP) + hl, xq = 4 * (q & 1);
+    GRow r = gen_row(a, c, n, hi);
+    r.eoff += x0 + xq;
+    r.cols = r.cols - x0 - xq < 0 ? 0 : r.cols - x0 - xq;
+    uint32_t v[4];
+    gen_load<TagF32, 4>(a.numel, x, r, v);
+    float bv[2][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool in = out[h] && hi < a.wh && x0 + xq + i < a.ww;
+        const float f = cc[in ? base[h] + hi * rstep + (xq + i) * col : 0];
+        bv[h][i] = in ? f : 0.f;
+      }
+    gen_tail<TagF32, 4>(a.numel, r, v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float av = i < r.cols ? __builtin_bit_cast(float, v[i]) : 0.f;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc[h] = mma<TagF32>(bv[h][i], av, acc[h]);
+    }
+  }
 }
 
 // Registers and LDS of the forward kernel (MAT: coefficients from a matrix).
@@ -738,10 +777,9 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
           }
         }
       } else {
-        if (far) {
+        if (__builtin_expect(far, 0)) {
           const uint32_t n = n0 + s * G::CW + 16 * u0 + ln;
-          acc[0][0] = gen_far_tile<RP, S>(a, x, coef, c, n, 32 * T + ln, g);
-          acc[0][1] = gen_far_tile<RP, S>(a, x, coef, c, n, 32 * T + 16 + ln, g);
+          gen_far_pair<RP, S>(a, x, coef + c * (MAT ? a.wh * a.ww * a.wh * a.ww : K2), a.src, c, n, T, lane, acc[0]);
         } else {
           // three sums per tile: hi hi, then the partial products of weight
           // 2^-8 (mb) and 2^-16 (lb); the operands of step k + 1 are read
@@ -1020,22 +1058,32 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
         xp[2][s] = __builtin_bit_cast(GFrag, make_uint4(ll[0], ll[1], ll[2], ll[3]));
       }
     }
-    far = cfar || __any(far);
     const Win w = cur;
+    // window ln, positions 16 t + 4 g .. + 3
+    auto store = [&](int t, int g, const float (&v)[4]) __attribute__((always_inline)) {
+      const int pos = 16 * t + 4 * g, r = pos / RP, xc = pos % RP;
+      const int nc = r < w.rows ? w.cols - xc : 0;
+      float *q = y + w.eoff + (int64_t)r * a.W + xc;
+      if (nc >= 4) {
+        *reinterpret_cast<u32x4a *>(q) = u32x4a{__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]),
+                                                __builtin_bit_cast(uint32_t, v[2]), __builtin_bit_cast(uint32_t, v[3])};
+      } else if (nc > 0) {
+        q[0] = v[0];
+        if (nc > 1) q[1] = v[1];
+        if (nc > 2) q[2] = v[2];
+      }
+    };
+    far = cfar || __any(far);
     cur = window(u + kGenWaves);
     load(cur, raw);
     __builtin_amdgcn_sched_barrier(0);
-
     // ---- output tiles 2 T, 2 T + 1
     const unsigned char *tb = tb0;
 #pragma unroll 1
-    for (int T = 0; T < S; ++T, tb -= 2048) {
+    for (int T = far ? S : 0; T < S; ++T, tb -= 2048) {
       f32x4 acc[2], mb[2], lb[2];
       acc[0] = acc[1] = mb[0] = mb[1] = lb[0] = lb[1] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (far) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) acc[h] = gen_far_tile<RP, S>(a, x, tab, c, 16u * (uint32_t)u + ln, 32 * T + 16 * h + ln, g);
-      } else {
+      {
         // (step, tile) by (step, tile); the blocks of the next one are read
         // while this one is multiplied (both tiles' at once would not fit
         // the registers)
@@ -1061,25 +1109,58 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      // window ln, positions 32 T + 16 h + 4 g .. + 3
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int pos = 32 * T + 16 * h + 4 * g, r = pos / RP, xc = pos % RP;
-        const int nc = r < w.rows ? w.cols - xc : 0;
         float v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = acc[h][e] + (mb[h][e] + lb[h][e]);
-        float *q = y + w.eoff + (int64_t)r * a.W + xc;
-        if (nc >= 4) {
-          *reinterpret_cast<u32x4a *>(q) = u32x4a{__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]),
-                                                  __builtin_bit_cast(uint32_t, v[2]), __builtin_bit_cast(uint32_t, v[3])};
-        } else if (nc > 0) {
-          q[0] = v[0];
-          if (nc > 1) q[1] = v[1];
-          if (nc > 2) q[2] = v[2];
-        }
+        store(2 * T + h, g, v);
       }
     }
+    if (far) {
+      // float32 products: four columns of one window row per lane at a time
+      // (from memory again: kept, they would cost the usual path registers),
+      // against the table's entries for them and every output tile.  Input
+      // positions past the window have zero coefficients; outputs past it are
+      // not stored, and what their lanes read (still LDS) does not matter.
+      f32x4 acc[2 * S];
+#pragma unroll
+      for (int t = 0; t < 2 * S; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      int l = lane;
+      asm volatile("" : "+v"(l));  // (what follows from it stays in this branch)
+      const int K1 = 2 * a.ww - 1, hf = 8 * (l >> 4) / RP, xf = 8 * (l >> 4) % RP, lo = l & 15;
+      const float *tl = Ts + (hf - lo / RP + a.wh - 1) * K1 + xf - lo % RP + a.ww - 1;
+#pragma unroll 1
+      for (int q = 0; q < 2 * S; ++q) {
+        const int r = KROWS * (q >> 1) + hf, xq = xf + 4 * (q & 1);
+        GRow f;
+        f.eoff = w.eoff + (int64_t)r * a.W + xq;
+        f.cols = r < w.rows ? w.cols - xq : 0;
+        uint32_t v[4];
+        gen_load<TagF32, 4>(a.numel, x, f, v);
+        gen_tail<TagF32, 4>(a.numel, f, v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = i < f.cols ? v[i] : 0u;
+        const float *tq = tl + KROWS * (q >> 1) * K1 + 4 * (q & 1);
+#pragma unroll
+        for (int t = 0; t < 2 * S; ++t) {
+          float bv[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            bv[i] = tq[i - t * (16 / RP) * K1];
+            bv[i] = r < a.wh && xq + i < a.ww ? bv[i] : 0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[t] = mma<TagF32>(bv[i], __builtin_bit_cast(float, v[i]), acc[t]);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 2 * S; ++t) {
+        const float v[4] = {acc[t][0], acc[t][1], acc[t][2], acc[t][3]};
+        store(t, l >> 4, v);
+      }
+    }
+
   }
 }
 
@@ -1276,18 +1357,21 @@ __global__ __launch_bounds__(kGenThreads, (GenDirect16<RP, S>::WGS * 2)) void ge
 // dT = the sums of X^T dY over windows along equal offsets.  K = windows: the
 // position-major fragments of x and dy come from transposing reads of their
 // window-major stages.  Wave (ph, pg) multiplies input tiles ph S .. + S - 1
-// with a quarter of the output tiles.  Rows of sixteen: products of tile pairs
-// with equal difference share an accumulator (S + NPO - 1 of them); rows of
-// eight: one per pair (at most three more).  At the end every wave sums the
+// with a quarter of the output tiles; products of tile pairs with equal
+// difference share an accumulator (S + NPO - 1 of them; 16-bit rows of eight
+// have one per pair, at most three more).  At the end every wave sums the
 // diagonals of its accumulators, and the waves' sums are added in order.
 //
 // Pads.  A pad position holds zero, and its product with an infinity or NaN
 // is NaN, which must reach no entry of dT.  Pad columns have places of their
-// own in every accumulator and are left out of the diagonals.  Pad rows: with
-// rows of sixteen a tile is one row, and the tiles past the window are not
-// multiplied; with rows of eight half a tile can be a pad row, and a shared
-// accumulator would add it to a row of the window, so each pair has its own
-// and the pad half is left out as the pad columns are.
+// own in every accumulator and are left out of the diagonals.  Pad rows,
+// 16-bit: with rows of sixteen a tile is one row, and the one past a window of
+// odd height (ODD) is not multiplied (by a constant of the kernel: tested in
+// the loops it cost up to 12 %); with rows of eight half a tile can be a pad
+// row, and a shared accumulator would add it to a row of the window, so each
+// pair has its own and the pad half is left out as the pad columns are.
+// float32: infinities and NaN are far rows, and only their products leave pad
+// rows out.
 //
 // DX (16-bit): the fused backward.  The same stages feed the input gradient
 // dY M^T as in the forward kernel (wave T holds the reversed table's
@@ -1304,15 +1388,20 @@ __global__ __launch_bounds__(kGenThreads, (GenDirect16<RP, S>::WGS * 2)) void ge
 // matrix cores and the splitting of the rows, which one LDS buffer per stage
 // leaves beside no products (B128 C192 28x28 w = 14: 85 us, float32 products
 // 122).
-template <class Tag, int RP, int S, bool DX>
+template <class Tag, int RP, int S, bool DX, bool ODD>
 struct GenDt {
   typedef GenCfg<Tag, RP, S> G;
   static_assert(!DX || Tag::W16, "fused backward: 16-bit");
-  static constexpr int NPO = cdiv(G::NT, 4);       // output tiles of a wave (at most)
+  static_assert(!ODD || (Tag::W16 && RP == 16), "the last tile is a pad: 16-bit rows of sixteen");
+  static constexpr int NTW = G::NT - ODD;          // tiles with rows of the window
+  static constexpr int NPO = cdiv(NTW, 4);         // output tiles of a wave (at most)
   static constexpr int R = 16 / RP;                // window rows per tile
-  // accumulators, and the one of input tile i and output tile q of a wave
-  static constexpr int NR = R == 1 ? S + NPO - 1 : S * NPO;
-  __host__ __device__ static constexpr int at(int i, int q) { return R == 1 ? i - q + NPO - 1 : i * NPO + q; }
+  // tile differences i - q + NPO - 1 of a wave's input and output tiles, its
+  // accumulators, and the one of a pair
+  static constexpr int NB = S + NPO - 1;
+  static constexpr bool SHARE = R == 1 || !Tag::W16;
+  static constexpr int NR = SHARE ? NB : S * NPO;
+  __host__ __device__ static constexpr int at(int i, int q) { return SHARE ? i - q + NPO - 1 : i * NPO + q; }
   static constexpr int KST = G::CW / 32;           // K steps per stage
   static constexpr int NBUF = Tag::W16 ? 2 : 1;    // stages in LDS
   // float32: the smaller partial products in sums of their own where the
@@ -1329,7 +1418,7 @@ struct GenDt {
   static constexpr int NBIN = R * R * 2 * RP;      // diagonals of a tile's R x R blocks, padded
   static constexpr int BT = 4;                     // tiles binned at a time
   static constexpr int SCR = kGenWaves * BT * kBinTile * 4;
-  static constexpr int BINS = kGenWaves * NR * NBIN * 4;
+  static constexpr int BINS = kGenWaves * NB * NBIN * 4;
   static constexpr int O_OFF = NBUF * STAGE;       // two result buffers
   static constexpr int END = O_OFF + (DX ? 2 * G::OB : 0);
   static constexpr int MASK_OFF = END > SCR + BINS ? END : SCR + BINS;
@@ -1345,13 +1434,13 @@ __device__ __attribute__((always_inline)) inline int gen_dt_cut(int ph, int pg) 
   return (NT * pg + (ph ? 3 : 0)) >> 2;
 }
 
-template <class Tag, int RP, int S, bool DX>
+template <class Tag, int RP, int S, bool DX, bool ODD>
 __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
     const typename Tag::S *__restrict__ x, const typename Tag::S *__restrict__ dy,
     const typename Tag::S *__restrict__ tab, typename Tag::S *__restrict__ dxo, float *__restrict__ out, GenArgs a) {
   typedef GenCfg<Tag, RP, S> G;
-  typedef GenDt<Tag, RP, S, DX> D;
-  constexpr int NPO = D::NPO, NR = D::NR;
+  typedef GenDt<Tag, RP, S, DX, ODD> D;
+  constexpr int NPO = D::NPO, NR = D::NR, NB = D::NB, R = D::R;
   extern __shared__ __align__(16) unsigned char smem[];
   int *flag = reinterpret_cast<int *>(smem + D::FLAG_OFF);
   uint32_t *masks = reinterpret_cast<uint32_t *>(smem + D::MASK_OFF);
@@ -1367,10 +1456,9 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
   const uint32_t n0 = (uint32_t)s0 * G::CW;
   const int v = gen_slot_window<G>(a, tid), hi = gen_slot_row<G>(a, tid);
   const int ph = wave >> 2, pg = wave & 3;
-  // (rows of sixteen: no products of the tiles past the window)
-  const int nto = D::R == 1 ? a.wh : G::NT, po1 = gen_dt_cut<G::NT>(ph, pg + 1);
-  const int po0 = gen_dt_cut<G::NT>(ph, pg), npo = (po1 < nto ? po1 : nto) - po0;
-  const bool xpad = D::R == 1 && ph * S + S - 1 >= a.wh;  // the last input tile is one of them
+  const int po0 = gen_dt_cut<D::NTW>(ph, pg), po1 = gen_dt_cut<D::NTW>(ph, pg + 1);
+  const int npo = po1 - po0;
+  const bool xpad = ODD && ph == 1;  // this wave's last input tile is past the window
 
   auto row = [&](int s) __attribute__((always_inline)) -> GRow {
     return s < nst ? gen_row(a, c, n0 + s * G::CW + v, hi) : GRow{0, 0};
@@ -1404,7 +1492,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
       if (fx || fg) flag[s & 1] = s;
     }
   };
-  auto products = [&](int s, const unsigned char *st) __attribute__((always_inline)) {
+  auto products = [&](const unsigned char *st) __attribute__((always_inline)) {
     if constexpr (Tag::W16) {
 #pragma unroll
       for (int ks = 0; ks < D::KST; ++ks) {
@@ -1419,25 +1507,6 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
 #pragma unroll
           for (int q = 0; q < NPO; ++q)
             if (q < npo) acc[D::at(i, q)] = mma<Tag>(af, bf[q], acc[D::at(i, q)]);
-        }
-      }
-    } else if (__builtin_amdgcn_readfirstlane(flag[s & 1]) == s) {
-      // float32 products of a stage with far rows, from global memory
-#pragma unroll
-      for (int i = 0; i < S; ++i) {
-        if (i == S - 1 && xpad) continue;
-#pragma unroll
-        for (int q = 0; q < NPO; ++q) {
-          if (q >= npo) continue;
-          const int pa = 16 * (ph * S + i) + ln, pb = 16 * (po0 + q) + ln;
-#pragma unroll 1
-          for (int w = 0; w < G::CW; w += 4) {
-            const uint32_t n = n0 + s * G::CW + w + g;
-            const GRow ra = gen_row(a, c, n, pa / RP), rb = gen_row(a, c, n, pb / RP);
-            const float av = pa % RP < ra.cols ? x[ra.eoff + pa % RP] : 0.f;
-            const float bv = pb % RP < rb.cols ? dy[rb.eoff + pb % RP] : 0.f;
-            acc[D::at(i, q)] = mma<TagF32>(av, bv, acc[D::at(i, q)]);
-          }
         }
       }
     } else {
@@ -1460,7 +1529,6 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
             for (int p = 0; p < 3; ++p) af[(i + 1) & 1][p] = dt_frag16<G::LDSW>(xt + p * G::PLANE, ph * S + i + 1, lane);
           }
           __builtin_amdgcn_sched_barrier(0);
-          if (i == S - 1 && xpad) continue;
           const GFrag(&f)[3] = af[i & 1];
 #define WBMM_DT_PART(PA, PB, ACC) \
   _Pragma("unroll") for (int q = 0; q < NPO; ++q) if (q < npo) ACC = mma_bf16(f[PA], bf[PB][q], ACC);
@@ -1490,6 +1558,73 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+    }
+  };
+
+  // float32 products of a stage with far rows: its rows as they are in the
+  // place of the planes, window-major
+  constexpr int FP = G::KP + 8;  // pitch
+  static_assert(Tag::W16 || 2 * G::CW * FP * 4 <= D::STAGE, "float32 rows within the planes");
+  // (loaded again: kept from the planes' writes on, they cost the usual path
+  // registers)
+  auto far_write = [&](int s) __attribute__((always_inline)) {
+    int vf = v, hf = hi;
+    asm volatile("" : "+v"(vf), "+v"(hf));  // (what follows from them stays in this branch)
+    const GRow r = gen_row(a, c, n0 + s * G::CW + vf, hf);
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+      uint32_t d[G::ND];
+      gen_load<Tag, RP>(a.numel, k ? dy : x, r, d);
+      gen_tail<Tag, RP>(a.numel, r, d);
+      gen_mask<Tag, RP>(masks, r.cols, d);
+      float *p = reinterpret_cast<float *>(smem) + (k * G::CW + vf) * FP + hf * RP;
+      if (hf < G::KR) {
+#pragma unroll
+        for (int i = 0; i < G::ND; i += 4)
+          *reinterpret_cast<uint4 *>(p + i) = make_uint4(d[i], d[i + 1], d[i + 2], d[i + 3]);
+      }
+    }
+  };
+  auto far_products = [&]() __attribute__((always_inline)) {
+    const float *px = reinterpret_cast<const float *>(smem) + g * FP + ln, *pg = px + G::CW * FP;
+    // rows of sixteen: no products of a tile past the window
+    const bool xcut = R == 1 && ph * S + S - 1 >= a.wh;
+    const int ocut = (R == 1 && po1 > a.wh ? a.wh : po1) - po0;
+    // rows of eight: the pairs apart, without their pad rows
+    f32x4 t[R == 1 ? 1 : S * NPO];
+    if constexpr (R == 2) {
+#pragma unroll
+      for (int k = 0; k < S * NPO; ++k) t[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll 1
+    for (int w = 0; w < G::CW; w += 4, px += 4 * FP, pg += 4 * FP) {
+      float av[S], bv[NPO];
+#pragma unroll
+      for (int q = 0; q < NPO; ++q) bv[q] = pg[16 * (q < npo ? po0 + q : 0)];
+#pragma unroll
+      for (int i = 0; i < S; ++i) av[i] = px[16 * (ph * S + i)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < S; ++i) {
+        if (i == S - 1 && xcut) continue;
+#pragma unroll
+        for (int q = 0; q < NPO; ++q) {
+          if (q >= ocut) continue;
+          f32x4 &r = R == 1 ? acc[D::at(i, q)] : t[R == 1 ? 0 : i * NPO + q];
+          r = mma<TagF32>(av[i], bv[q], r);
+        }
+      }
+    }
+    if constexpr (R == 2) {
+#pragma unroll
+      for (int i = 0; i < S; ++i)
+#pragma unroll
+        for (int q = 0; q < NPO; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool ok = 2 * (ph * S + i) + (4 * g + e) / RP < a.wh && 2 * (po0 + q) + ln / RP < a.wh;
+            acc[D::at(i, q)][e] += ok ? t[i * NPO + q][e] : 0.f;
+          }
     }
   };
 
@@ -1570,7 +1705,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
     // stage s + 1 (in d) to LDS, the rows of stage s - 1 out, stage s + 3 into d
     auto stage = [&](int s, Rows &d) __attribute__((always_inline)) {
       const unsigned char *st = smem + (s & 1) * D::STAGE;
-      products(s, st);
+      products(st);
       dx_products(s, st);
       const GRow rnext = d.r;
       write(s + 1, smem + ((s + 1) & 1) * D::STAGE, d);
@@ -1591,8 +1726,15 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
     for (int s = 0; s < nst; ++s) {
       write(s, smem, d0);
       __syncthreads();
+      const int far = flag[s & 1];
       load(s + 1, d0);
-      products(s, smem);
+      if (__builtin_expect(!Tag::W16 && __builtin_amdgcn_readfirstlane(far) == s, 0)) {
+        far_write(s);
+        __syncthreads();
+        far_products();
+      } else {
+        products(smem);
+      }
       __syncthreads();
     }
   }
@@ -1602,12 +1744,11 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
   // so that column s holds diagonal dw = -s above row RP - s and RP - s below;
   // one lane sums one column of one block.  Pad columns, and with rows of
   // eight pad rows, are written as zero, whatever their products were.
-  constexpr int R = D::R;
   float *scr = reinterpret_cast<float *>(smem) + wave * D::BT * kBinTile;
   float *bins = reinterpret_cast<float *>(smem + D::SCR);
-  float *mine = bins + wave * NR * D::NBIN;
+  float *mine = bins + wave * NB * D::NBIN;
 #pragma unroll
-  for (int r0 = 0; r0 < NR; r0 += D::BT) {
+  for (int r0 = 0; r0 < NB; r0 += D::BT) {
     wave_lds_sync();
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1616,15 +1757,20 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
       float *p = scr + rr * 17 + (ln & ~(RP - 1)) + ((ln - rr) & (RP - 1));
 #pragma unroll
       for (int j = 0; j < D::BT; ++j) {
-        if (r0 + j >= NR) continue;
-        float t = acc[r0 + j][e];
-        if constexpr (D::LOWACC) t += low[r0 + j][e];
-        bool ok = cols;
-        if constexpr (R == 2) {
-          const int i = (r0 + j) / NPO, q = (r0 + j) % NPO;
-          ok = ok && 2 * (ph * S + i) + rr / RP < a.wh && 2 * (po0 + q) + ln / RP < a.wh;
+        if (r0 + j >= NB) continue;
+        float t = 0.f;
+        if constexpr (D::SHARE) {
+          t = acc[r0 + j][e];
+          if constexpr (D::LOWACC) t += low[r0 + j][e];
+        } else {
+#pragma unroll
+          for (int q = 0; q < NPO; ++q) {
+            const int i = r0 + j - (NPO - 1) + q;
+            if (i < 0 || i >= S) continue;
+            if (2 * (ph * S + i) + rr / RP < a.wh && 2 * (po0 + q) + ln / RP < a.wh) t += acc[D::at(i, q)][e];
+          }
         }
-        p[j * kBinTile] = ok ? t : 0.f;
+        p[j * kBinTile] = cols ? t : 0.f;
       }
     }
     wave_lds_sync();
@@ -1633,7 +1779,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
     for (int k = 0; k < D::BT * TPT / 64; ++k) {
       const int t = lane + 64 * k;
       const int j = t / TPT, b = t % TPT / RP, sft = t % RP;  // tile, block (ra R + rb), column
-      if (r0 + j < NR) {
+      if (r0 + j < NB) {
         const float *p = scr + j * kBinTile + b / R * RP * 17 + b % R * RP + sft;
         float lo = 0.f, up = 0.f;
 #pragma unroll
@@ -1658,20 +1804,13 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
     float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < kGenWaves; ++w) {
-      const int base = gen_dt_cut<G::NT>(w >> 2, w & 3) - (w >> 2) * S;
+      const int base = gen_dt_cut<D::NTW>(w >> 2, w & 3) - (w >> 2) * S + NPO - 1;
 #pragma unroll
       for (int b = 0; b < R * R; ++b) {
         const int pr = dh - (b / R - b % R);  // P R
         if (R == 2 && (pr & 1)) continue;
-        const float *t = bins + w * NR * D::NBIN + b * 2 * RP + RP - 1 + dw;
-        const int r = pr / R + base;  // i - q
-        if constexpr (R == 1) {
-          if (r + NPO - 1 >= 0 && r < S) sum += t[(r + NPO - 1) * D::NBIN];
-        } else {
-#pragma unroll
-          for (int q = 0; q < NPO; ++q)
-            if (r + q >= 0 && r + q < S) sum += t[D::at(r + q, q) * D::NBIN];
-        }
+        const int r = pr / R + base;
+        if (r >= 0 && r < NB) sum += bins[(w * NB + r) * D::NBIN + b * 2 * RP + RP - 1 + dw];
       }
     }
     o[k] = sum;

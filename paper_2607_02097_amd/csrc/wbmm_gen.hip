@@ -179,13 +179,23 @@ static hipError_t gen_dt(const void *x, const void *dy, const void *t, void *dx,
   gen_plan(g.C, a.stages, ncu > 0 ? ncu : 256, 3.0, max_slabs, &a.spw, &a.tiles_per_ch);
   float *out = a.tiles_per_ch > 1 ? ws : dt;
   const dim3 grid = gen_grid(g.C * a.tiles_per_ch), block(kGenThreads);
-  constexpr size_t lds = GenDt<Tag, RP, S, false>::LDS, flds = GenDt<Tag, RP, S, Tag::W16>::LDS;
-  static_assert(lds <= 160 * 1024 && flds <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
-  if (dx)
-    gen_dt_kernel<Tag, RP, S, Tag::W16><<<grid, block, flds, st>>>((const E *)x, (const E *)dy, (const E *)t, (E *)dx,
-                                                                   out, a);
-  else
-    gen_dt_kernel<Tag, RP, S, false><<<grid, block, lds, st>>>((const E *)x, (const E *)dy, nullptr, nullptr, out, a);
+  auto launch = [&](auto odd) {
+    constexpr bool ODD = decltype(odd)::value;
+    constexpr size_t lds = GenDt<Tag, RP, S, false, ODD>::LDS, flds = GenDt<Tag, RP, S, Tag::W16, ODD>::LDS;
+    static_assert(lds <= 160 * 1024 && flds <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
+    if (dx)
+      gen_dt_kernel<Tag, RP, S, Tag::W16, ODD><<<grid, block, flds, st>>>((const E *)x, (const E *)dy, (const E *)t,
+                                                                          (E *)dx, out, a);
+    else
+      gen_dt_kernel<Tag, RP, S, false, ODD><<<grid, block, lds, st>>>((const E *)x, (const E *)dy, nullptr, nullptr,
+                                                                      out, a);
+  };
+  if constexpr (Tag::W16 && RP == 16) {
+    if (wh & 1) launch(std::true_type{});
+    else launch(std::false_type{});
+  } else {
+    launch(std::false_type{});
+  }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.tiles_per_ch <= 1) return e;
   return launch_dt_sum(ws, dt, g.C * (int64_t)(2 * wh - 1) * (2 * ww - 1), nullptr, nullptr, 0, a.tiles_per_ch, st);

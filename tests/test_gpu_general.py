@@ -402,3 +402,39 @@ def test_float32_precision(shape):
         bound = rounding(-(-windows_ // 32) + rows if k[:2] == "dt" else ksteps + 2)
         print(shape, k, "%.1e of %.1e" % (err, bound), flush=True)
         assert err <= bound, k
+
+
+@pytest.mark.parametrize("kind", ["forward", "forward w7", "backward", "matrix", "rectangular gradient"])
+def test_time_of_values_out_of_range(kind):
+    """Values that take float32 products cost what those cost (the bf16 rate
+    is 16 times theirs and each product takes six bf16 ones, so 2.7 times where
+    the matrix cores are the bound), not much more: at most five times."""
+    B, C, H, Wd, wh, ww = {"forward": (32, 256, 56, 56, 14, 14), "forward w7": (128, 192, 56, 56, 7, 7),
+                           "backward": (128, 192, 28, 28, 14, 14), "matrix": (64, 192, 28, 28, 14, 14),
+                           "rectangular gradient": (64, 192, 56, 56, 7, 14)}[kind]
+    x, t = (v.cuda() for v in data(B, C, H, Wd, wh, ww, "f32", seed=1))
+    m = W.wbmm_build_matrix(t, wh, ww) if kind == "matrix" else None
+
+    def once(x):
+        if kind == "backward":
+            return W.wbmm_backward(x, x.flip(0), t, wh)
+        if kind == "matrix":
+            return W.wbmm_dense_forward(x, m, wh, ww)
+        if kind == "rectangular gradient":
+            return W.wbmm_rect_backward_table(x, x, wh, ww)
+        return W.wbmm_forward(x, t, wh)
+
+    def time(x):
+        once(x)
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            once(x)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+    plain, far = time(x), time(x * 2.0 ** -100)
+    print(kind, "%.0f us, out of range %.0f us" % (1e3 * plain, 1e3 * far), flush=True)
+    assert far <= 5 * plain
