@@ -31,8 +31,8 @@
  *   accumulation; every output element is rounded once (nearest-even) from
  *   its float32 sum.  float32 inputs are multiplied at float32 precision,
  *   with float32 products or as three bfloat16 parts whose partial products
- *   reach 2^-24 of each product; values outside the parts' range, infinities
- *   and NaN take float32 products.
+ *   reach 2^-24 of each product; values of 2^60 and more and infinities, and
+ *   those below 2^-96 but zero, take float32 products, alone or beside others.
  * - Work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
  *   default stream).  Calls are asynchronous: nothing is synchronised, and the
  *   caller must keep every buffer alive until the stream has passed the work.

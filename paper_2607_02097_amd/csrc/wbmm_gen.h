@@ -258,8 +258,10 @@ __device__ __attribute__((always_inline)) inline void gen_store(typename Tag::S 
 // others in a second one: what is left out is below 2^-24 of the product.  The
 // bf16 rate is sixteen times the float32 matrix rate, six products cost 3/8 of
 // a float32 one.  Ranges where a part would overflow or vanish (and
-// infinities and NaN) take float32 products instead: a row is "far" when its
-// largest magnitude is at least 2^60, or not zero and below 2^-96.  What that
+// infinities and NaN) take float32 products instead: a row is "far" when one of
+// its magnitudes is at least 2^60, or not zero and below 2^-96 (from 2^-103 on
+// every bit of the lowest part lies above bf16's smallest normal value; a tiny
+// value beside ordinary ones can decide an output alone).  What that
 // costs, every row far, us (ordinary values; the float32 row kernels): forward
 // w = 14 B128 C256 56x56 4390 -> 750 (280; 800), w = 7 B64 C96 56x56 174 -> 62 (38;
 // 45), both gradients w = 14 B128 C192 28x28 2240 -> 325 (156; 273), w = 7 434 ->
@@ -269,6 +271,18 @@ __device__ __attribute__((always_inline)) inline void gen_store(typename Tag::S 
 // wave (forward), or a stage's rows lie in LDS as float32 (gradient).
 constexpr uint32_t kFarHi = (127u + 60u) << 23, kFarLo = (127u - 96u) << 23;
 constexpr uint32_t kFarLoCoef = (127u - 60u) << 23;
+
+// Magnitudes (float bits without the sign, doubled) of the values seen: the
+// largest, and the smallest but zero, less one (an instruction each a value).
+struct FarRange {
+  uint32_t mx = 0, mn = ~0u;
+  __device__ __attribute__((always_inline)) void add(uint32_t bits) {
+    const uint32_t m = bits << 1, n = m - 1;
+    mx = m > mx ? m : mx;
+    mn = n < mn ? n : mn;
+  }
+  __device__ __attribute__((always_inline)) bool far() const { return mx >= 2 * kFarHi || mn < 2 * kFarLo - 1; }
+};
 
 // Two values -> the dwords of their three planes.
 __device__ __attribute__((always_inline)) inline void split3(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
@@ -292,13 +306,10 @@ __device__ __attribute__((always_inline)) inline bool gen_write(unsigned char *x
     for (int i = 0; i < G::ND; i += 4)
       *reinterpret_cast<uint4 *>(p + 4 * i) = make_uint4(d[i], d[i + 1], d[i + 2], d[i + 3]);
   } else {
-    uint32_t mx = 0;
+    FarRange mag;
 #pragma unroll
-    for (int i = 0; i < G::ND; ++i) {
-      const uint32_t m = d[i] & 0x7fffffffu;
-      mx = m > mx ? m : mx;
-    }
-    far = mx >= kFarHi || (mx != 0 && mx < kFarLo);
+    for (int i = 0; i < G::ND; ++i) mag.add(d[i]);
+    far = mag.far();
 #pragma unroll
     for (int i = 0; i < RP; i += 8) {
       uint32_t h[4], m[4], l[4];
@@ -336,15 +347,15 @@ __device__ __attribute__((always_inline)) inline int64_t gen_coef(const GenArgs 
 // [x_out][x_in] (zero past the window), from the table copy Ts (reversed for
 // the input gradient): a fragment is then one 16-byte read at a per-lane
 // base plus a constant.  float32: three planes, the lowest at tblow.  Returns
-// the largest magnitude the thread saw (float32).
+// the magnitudes that the thread saw (float32).
 template <class Tag, int RP, int S>
-__device__ __attribute__((always_inline)) inline uint32_t gen_build_tb(const GenArgs &a, const typename Tag::S *Ts,
+__device__ __attribute__((always_inline)) inline FarRange gen_build_tb(const GenArgs &a, const typename Tag::S *Ts,
                                                                        unsigned char *tb, unsigned char *tblow,
                                                                        int tid) {
   typedef GenCfg<Tag, RP, S> G;
   constexpr int CPR = RP / 8;  // 8-element chunks per block row
   const int K1 = 2 * a.ww - 1;
-  uint32_t mx = 0;
+  FarRange mag;
   for (int ch = tid; ch < G::NBLK * RP * CPR; ch += kGenThreads) {
     const int row = ch / CPR, xi0 = (ch % CPR) * 8;
     const int dh = row / RP - (G::KR - 1), xo = row % RP;
@@ -370,9 +381,8 @@ __device__ __attribute__((always_inline)) inline uint32_t gen_build_tb(const Gen
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float f0 = nv > 2 * k ? Ts[base + 2 * k] : 0.f, f1 = nv > 2 * k + 1 ? Ts[base + 2 * k + 1] : 0.f;
-        const uint32_t m0 = __builtin_bit_cast(uint32_t, f0) & 0x7fffffffu, m1 = __builtin_bit_cast(uint32_t, f1) & 0x7fffffffu;
-        mx = m0 > mx ? m0 : mx;
-        mx = m1 > mx ? m1 : mx;
+        mag.add(__builtin_bit_cast(uint32_t, f0));
+        mag.add(__builtin_bit_cast(uint32_t, f1));
         split3(f0, f1, h[k], m[k], l[k]);
       }
       *reinterpret_cast<uint4 *>(p) = make_uint4(h[0], h[1], h[2], h[3]);
@@ -380,7 +390,7 @@ __device__ __attribute__((always_inline)) inline uint32_t gen_build_tb(const Gen
       *reinterpret_cast<uint4 *>(tblow + off) = make_uint4(l[0], l[1], l[2], l[3]);
     }
   }
-  return mx;
+  return mag;
 }
 
 // Byte offset in the blocks of lane's part of the fragment of tile pair T at
@@ -500,7 +510,7 @@ __device__ __attribute__((always_inline)) inline void gen_frags_mat16(const GenA
 template <int RP, int S>
 __device__ __attribute__((always_inline)) inline void gen_frags_mat32(const GenArgs &a, const float *coef, int64_t c,
                                                                       int T, int lane, GFrag (&fr)[3][2][S],
-                                                                      uint32_t &mx) {
+                                                                      FarRange &mag) {
   const int g = lane >> 4, ln = lane & 15;
   const int d = a.wh * a.ww;
   const float *cm = coef + c * d * d;
@@ -536,7 +546,7 @@ __device__ __attribute__((always_inline)) inline void gen_frags_mat32(const GenA
         // (the finished value, not its parts, is what stays in registers)
         asm volatile("" : "+v"(u));
         v[e] = __builtin_bit_cast(float, u);
-        mx = (u & 0x7fffffffu) > mx ? (u & 0x7fffffffu) : mx;
+        mag.add(u);
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) split3(v[2 * k], v[2 * k + 1], hh[k], mm[k], ll[k]);
@@ -695,23 +705,23 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
   __syncthreads();
   const int T = wave % S, sg = wave / S;  // tile pair, sub-tile group
   GFrag fr[F::NPR][2][S];
-  uint32_t cmx = 0;  // largest coefficient magnitude seen (float32)
+  FarRange cmag;  // coefficients seen (float32)
   if constexpr (MAT) {
     constexpr int ROOM = F::LOW_OFF - G::XB;
     if constexpr (Tag::W16) {
       if (a.src == kSrcMat) gen_frags_mat16<Tag, RP, S, ROOM, false>(a, coef, c, T, tid, masks, xbuf + G::XB, fr);
       else gen_frags_mat16<Tag, RP, S, ROOM, true>(a, coef, c, T, tid, masks, xbuf + G::XB, fr);
     } else
-      gen_frags_mat32<RP, S>(a, coef, c, T, lane, fr, cmx);
+      gen_frags_mat32<RP, S>(a, coef, c, T, lane, fr, cmag);
   } else {
-    cmx = gen_build_tb<Tag, RP, S>(a, Ts, xbuf + G::XB, F::LOW ? smem + F::LOW_OFF : xbuf + G::XB + 2 * G::TBB, tid);
+    cmag = gen_build_tb<Tag, RP, S>(a, Ts, xbuf + G::XB, F::LOW ? smem + F::LOW_OFF : xbuf + G::XB + 2 * G::TBB, tid);
   }
   if constexpr (!Tag::W16) {
-    // far coefficients: a huge one, or none of normal size though not all
-    // are zero
-    if (__any(cmx >= kFarHi) && lane == 0) flag[2] = 1;
-    if (__any(cmx != 0) && lane == 0) flag[3] = 1;
-    if (__any(cmx >= kFarLoCoef) && lane == 0) flag[4] = 1;
+    // far coefficients: a huge or a tiny one, or none of normal size though
+    // not all are zero
+    if (__any(cmag.far()) && lane == 0) flag[2] = 1;
+    if (__any(cmag.mx != 0) && lane == 0) flag[3] = 1;
+    if (__any(cmag.mx >= 2 * kFarLoCoef) && lane == 0) flag[4] = 1;
   }
   __syncthreads();
   if constexpr (!MAT) gen_frags_tb<Tag, RP, S>(a, xbuf + G::XB, T, lane, fr);
@@ -954,7 +964,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
   if (tid < 72) masks[tid] = tid / 8 > tid % 8 ? ~0u : 0u;
   if (tid < 3) flag[tid] = 0;
   __syncthreads();
-  uint32_t cmx = 0;
+  FarRange cmag;
   for (int ch = tid; ch < D::NF * 64; ch += kGenThreads) {
     const int l = ch & 63, lg = l >> 4, lo = l & 15;
     const int dh = (ch / 64 - (2 * S - 1)) * (16 / RP) + 8 * lg / RP - lo / RP, xo = lo % RP, xi = 8 * lg % RP;
@@ -965,9 +975,8 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float f0 = nv > 2 * k ? t[2 * k] : 0.f, f1 = nv > 2 * k + 1 ? t[2 * k + 1] : 0.f;
-      const uint32_t m0 = __builtin_bit_cast(uint32_t, f0) & 0x7fffffffu, m1 = __builtin_bit_cast(uint32_t, f1) & 0x7fffffffu;
-      cmx = m0 > cmx ? m0 : cmx;
-      cmx = m1 > cmx ? m1 : cmx;
+      cmag.add(__builtin_bit_cast(uint32_t, f0));
+      cmag.add(__builtin_bit_cast(uint32_t, f1));
       split3(f0, f1, hh[k], mm[k], ll[k]);
     }
     unsigned char *p = smem + ch * 16;
@@ -975,9 +984,9 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
     *reinterpret_cast<uint4 *>(p + D::PL) = make_uint4(mm[0], mm[1], mm[2], mm[3]);
     *reinterpret_cast<uint4 *>(p + 2 * D::PL) = make_uint4(ll[0], ll[1], ll[2], ll[3]);
   }
-  if (__any(cmx >= kFarHi) && lane == 0) flag[0] = 1;
-  if (__any(cmx != 0) && lane == 0) flag[1] = 1;
-  if (__any(cmx >= kFarLoCoef) && lane == 0) flag[2] = 1;
+  if (__any(cmag.far()) && lane == 0) flag[0] = 1;
+  if (__any(cmag.mx != 0) && lane == 0) flag[1] = 1;
+  if (__any(cmag.mx >= 2 * kFarLoCoef) && lane == 0) flag[2] = 1;
   __syncthreads();
   const bool cfar = flag[0] || (flag[1] && !flag[2]);
 
@@ -1041,15 +1050,21 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
 #pragma unroll
             for (int i = 0; i < 8; ++i) raw[s][i] = i < 7 ? raw[s][i + 1] : 0u;
         }
-        uint32_t mx = 0;
+        // (the largest as floats, a third fewer instructions than FarRange; it
+        // may leave out NaN, which the parts carry to the same outputs)
+        float mx = 0.f;
+        uint32_t mn = ~0u;
         uint32_t hh[4], mm[4], ll[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          raw[s][i] &= m[i];
-          const uint32_t v = raw[s][i] & 0x7fffffffu;
-          mx = v > mx ? v : mx;
+        for (int i = 0; i < 8; ++i) raw[s][i] &= m[i];
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+          asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(mx) : "v"(raw[s][i]), "v"(raw[s][i + 1]));
+          const uint32_t n0 = (raw[s][i] << 1) - 1, n1 = (raw[s][i + 1] << 1) - 1;
+          mn = n0 < mn ? n0 : mn;
+          mn = n1 < mn ? n1 : mn;
         }
-        far |= mx >= kFarHi || (mx != 0 && mx < kFarLo);
+        far |= !(mx < __builtin_bit_cast(float, kFarHi)) || mn < 2 * kFarLo - 1;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           split3(__builtin_bit_cast(float, raw[s][2 * i]), __builtin_bit_cast(float, raw[s][2 * i + 1]), hh[i], mm[i], ll[i]);

@@ -404,6 +404,72 @@ def test_float32_precision(shape):
         assert err <= bound, k
 
 
+# the direct kernels (many channels; rows of eight: always), the staged kernel,
+# the matrix form and the table gradient
+@pytest.mark.parametrize("shape", [(3, 2, 28, 42, 14, 14), (3, 1024, 28, 42, 14, 14), (7, 3, 21, 30, 7, 7),
+                                   (2, 5, 40, 50, 16, 9), (9, 4, 70, 65, 11, 8)], ids=lambda s: "B%dC%dH%dW%dw%dx%d" % s)
+def test_float32_tiny_beside_ordinary(shape):
+    """A value far below the others of its row or table keeps float32's
+    precision where it decides an output alone: coefficients that are zero for
+    every other position of its row, inputs that are zero wherever the other
+    coefficients apply."""
+    B, C, H, Wd, wh, ww = shape
+    x, t = (v.cuda() for v in data(B, C, H, Wd, wh, ww, "f32", seed=3))
+    k = (2 * wh - 1) * (2 * ww - 1)
+    mid = k // 2
+    x = x + torch.where(x < 0, -0.5, 0.5)  # (no result becomes denormal)
+    eps = 2.0 ** -21  # one product: three roundings and what the parts leave out, 2^-24 each
+    for e in (-100, -110, -118):
+        # every second column tiny, the table's centre alone: y = x T_0
+        xs = x.clone()
+        xs[..., ::2] *= 2.0 ** e
+        only = torch.zeros_like(t)
+        only[:, mid] = 1.0 + t[:, mid]
+        want = xs.double() * only[:, mid].double()[None, :, None, None]
+        m = W.wbmm_build_matrix(only, wh, ww)
+        for name, y in (("forward", W.wbmm_rect_forward(xs, only, wh, ww)),
+                        ("input gradient", W.wbmm_rect_backward_input(xs, only, wh, ww)),
+                        ("matrix", W.wbmm_dense_forward(xs, m, wh, ww)),
+                        ("matrix^T", W.wbmm_dense_backward_input(xs, m, wh, ww))):
+            worst = float(((y.double() - want).abs() / want.abs()).max())
+            print(shape, e, name, "%.1e" % worst, flush=True)
+            assert worst <= eps, name
+        # a tiny centre beside ordinary entries, inputs in one position a window
+        ts = t.clone()
+        ts[:, mid] = (1.0 + t[:, mid]) * 2.0 ** e
+        xo = torch.zeros_like(x)
+        xo[:, :, ::wh, ::ww] = x[:, :, ::wh, ::ww]
+        want = xo[:, :, ::wh, ::ww].double() * ts[:, mid].double()[None, :, None, None]
+        m = W.wbmm_build_matrix(ts, wh, ww)
+        for name, y in (("table", W.wbmm_rect_forward(xo, ts, wh, ww)),
+                        ("table reversed", W.wbmm_rect_backward_input(xo, ts, wh, ww)),
+                        ("table's matrix", W.wbmm_dense_forward(xo, m, wh, ww)),
+                        ("table's matrix^T", W.wbmm_dense_backward_input(xo, m, wh, ww))):
+            y = y[:, :, ::wh, ::ww].double()
+            worst = float(((y - want).abs() / want.abs()).max())
+            print(shape, e, name, "%.1e" % worst, flush=True)
+            assert worst <= eps, name
+        # small inputs and a small centre: their product is still a float32
+        if e == -110:
+            ts[:, mid] = (1.0 + t[:, mid]) * 2.0 ** -62
+            y = W.wbmm_rect_forward(xo * 2.0 ** -62, ts, wh, ww)[:, :, ::wh, ::ww].double()
+            want = (xo * 2.0 ** -62)[:, :, ::wh, ::ww].double() * ts[:, mid].double()[None, :, None, None]
+            worst = float(((y - want).abs() / want.abs()).max())
+            print(shape, "both small %.1e" % worst, flush=True)
+            assert worst <= eps, "both small"
+        # dT of a tiny column and one dY beside it: the centre is one product
+        # (the other columns of x are ordinary and meet zeros there)
+        xg, dy = torch.zeros_like(x), torch.zeros_like(x)
+        xg[0, :, 0] = x[0, :, 0]
+        xg[0, :, 0, 0] *= 2.0 ** e
+        dy[0, :, 0, 0] = x[0, :, 1, 1]
+        want = xg[0, :, 0, 0].double() * dy[0, :, 0, 0].double()
+        dt = W.wbmm_rect_backward_table(xg, dy, wh, ww)[:, mid].double()
+        assert float(((dt - want).abs() / want.abs()).max()) <= eps, "table gradient"
+        dt = W.wbmm_rect_backward_table(dy, xg, wh, ww)[:, mid].double()
+        assert float(((dt - want).abs() / want.abs()).max()) <= eps, "table gradient, dY"
+
+
 @pytest.mark.parametrize("kind", ["forward", "forward w7", "backward", "matrix", "rectangular gradient"])
 def test_time_of_values_out_of_range(kind):
     """Values that take float32 products cost what those cost (the bf16 rate
