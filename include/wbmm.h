@@ -114,7 +114,8 @@ size_t wbmm_backward_table_workspace_bytes(int64_t B, int64_t C, int64_t H,
  * concurrently must not share one.
  *
  * The reduction has a fixed order (slab partials are summed in slab order):
- * the result is bitwise reproducible for a given shape. */
+ * the result is bitwise reproducible for a given shape (16-bit: and x and dy
+ * at addresses alike in being multiples of four). */
 wbmm_status wbmm_backward_table(const void *x, const void *dy, float *dtable,
                                 void *workspace, size_t workspace_bytes,
                                 int64_t B, int64_t C, int64_t H, int64_t W,

@@ -3050,6 +3050,16 @@ static hipError_t run_backward_fused(const void *x, const void *dy, const void *
   a.tile = (int)p.slab_windows;
   a.tiles_per_ch = (int)p.slabs;
   set_tiled<WIN, Tag::ES>(g, a, {x, dy, dx});
+  if (Tag::W16 && !a.tiled) {
+    // dx alone at an address that is no multiple of four: two launches, so
+    // that dT's kernel, and with it the order of its sums, does not depend on dx
+    KArgs b = a;
+    set_tiled<WIN, Tag::ES>(g, b, {x, dy});
+    if (b.tiled) {
+      const hipError_t e = run_forward<Tag, WIN>(dy, t, dx, g, true, st);
+      return e != hipSuccess ? e : run_dtable<Tag, WIN>(x, dy, dt, ws, g, st);
+    }
+  }
   if (Tag::W16 && gen_grad<Tag, WIN>(g, a.tiled != 0))
     return GenEntry<Tag>::backward(x, dy, t, dx, dt, ws, g, WIN, WIN, p.slabs, st);
   if constexpr (Tag::ES == 4 || WIN % 2 == 0) {

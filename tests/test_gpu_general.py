@@ -470,6 +470,26 @@ def test_float32_tiny_beside_ordinary(shape):
         assert float(((dt - want).abs() / want.abs()).max()) <= eps, "table gradient, dY"
 
 
+@pytest.mark.parametrize("odd", ["x", "dy", "dx"])
+@pytest.mark.parametrize("shape", [(32, 96, 56, 56, 14), (16, 192, 28, 28, 14), (64, 96, 32, 32, 8)],
+                         ids=lambda s: "B%dC%dH%dW%dw%d" % s)
+def test_gradients_at_odd_addresses(shape, odd):
+    """16-bit tensors at addresses that are no multiple of four, on maps with
+    fixed-offset rows: one call for both gradients equals the separate ones."""
+    B, C, H, Wd, w = shape
+    x, t = (v.cuda() for v in data(B, C, H, Wd, w, w, "bf16", seed=1))
+    dy, _ = (v.cuda() for v in data(B, C, H, Wd, w, w, "bf16", seed=2))
+    base = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")
+    moved = base[1:].view(x.shape)
+    dx = None
+    if odd == "dx":
+        dx = moved
+    else:
+        x, dy = (moved.copy_(x), dy) if odd == "x" else (x, moved.copy_(dy))
+    dx, dt = W.wbmm_backward(x, dy, t, w, dx=dx)
+    assert torch.equal(dt, W.wbmm_backward_table(x, dy, w))
+    assert torch.equal(dx, W.wbmm_backward_input(dy, t, w))
+
 @pytest.mark.parametrize("kind", ["forward", "forward w7", "backward", "matrix", "rectangular gradient"])
 def test_time_of_values_out_of_range(kind):
     """Values that take float32 products cost what those cost (the bf16 rate
