@@ -2,30 +2,9 @@
 // every row pitch and K-step count.
 // Compiled with -DWBMM_INST_TAG=<TagF32|TagBF16|TagF16>.
 #include "wbmm_gen.h"
+#include "wbmm_plan.h"
 
 namespace wbmm {
-
-// Workgroups per channel: consecutive stages of one channel per workgroup,
-// as many workgroups as the chip holds at a time (slots) or a few rounds of
-// them, whichever leaves the fewest stages in a row; a workgroup's prologue
-// (coefficients, first rows) costs about ov stages.
-static void gen_plan(int64_t C, int64_t stages, int64_t slots, double ov, int64_t max_parts, int *spw, int *parts) {
-  double best = 1e300;
-  int64_t bp = 1;
-  for (int64_t p = 1; p <= stages && p <= max_parts; ++p) {
-    const int64_t per = cdiv64(stages, p);
-    const int64_t rounds = cdiv64(C * cdiv64(stages, per), slots);
-    const double cost = (double)rounds * ((double)per + ov);
-    if (cost < best - 1e-9) {
-      best = cost;
-      bp = p;
-    }
-    if (C * p > 8 * slots) break;
-  }
-  const int64_t per = cdiv64(stages, bp);
-  *spw = (int)per;
-  *parts = (int)cdiv64(stages, per);
-}
 
 static GenArgs gen_args(const Geom &g, int wh, int ww) {
   GenArgs a;
@@ -58,11 +37,7 @@ static hipError_t gen_fwd(const void *x, const void *coef, void *y, const Geom &
   typedef GenCfg<Tag, RP, S> G;
   GenArgs a = gen_args(g, wh, ww);
   a.src = src;
-  a.stages = (int)cdiv64(a.N, G::CW);
-  gen_lanes<G>(a);
   const int ncu = compute_units();
-  const int wgs = src >= kSrcMat ? GenFwd<Tag, RP, S, true>::WGS : GenFwd<Tag, RP, S, false>::WGS;
-  gen_plan(g.C, a.stages, (int64_t)(ncu > 0 ? ncu : 256) * wgs, 1.5, 1 << 20, &a.spw, &a.tiles_per_ch);
   if constexpr (!Tag::W16) {
     // float32 from the table: one unit of 16 windows per wave where they fill
     // half of the chip's 2048 waves (w = 14, us: B16 C96 56x56, 1536 units, 24.8
@@ -94,6 +69,10 @@ static hipError_t gen_fwd(const void *x, const void *coef, void *y, const Geom &
       return hipGetLastError();
     }
   }
+  a.stages = (int)cdiv64(a.N, G::CW);
+  gen_lanes<G>(a);
+  const int wgs = src >= kSrcMat ? GenFwd<Tag, RP, S, true>::WGS : GenFwd<Tag, RP, S, false>::WGS;
+  gen_plan(g.C, a.stages, (int64_t)(ncu > 0 ? ncu : 256) * wgs, 1.5, 1 << 20, &a.spw, &a.tiles_per_ch);
   const dim3 grid = gen_grid(g.C * a.tiles_per_ch), block(kGenThreads);
   constexpr size_t ltab = GenFwd<Tag, RP, S, false>::LDS, lmat = GenFwd<Tag, RP, S, true>::LDS;
   static_assert(ltab <= 160 * 1024 && lmat <= 160 * 1024, "workgroup LDS above the 160 KB of a compute unit");
