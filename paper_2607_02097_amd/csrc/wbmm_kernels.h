@@ -2734,6 +2734,17 @@ static bool img_layout(const Geom &g, const void *x, const void *y, ImgArgs &ia)
   return true;
 }
 
+// Maps as wide as a window of 9 and more, enough of them for the general
+// kernels' units: a window's rows lie together, and the row kernel's whole-row
+// copies are the shorter way (us, row kernel and units: w = 11 B56 C779 58x11 46
+// and 75, w = 15 B71 C98 52x15 13 and 25, w = 9 B63 C189 43x9 10.4 and 19.9, w = 14
+// B28 C148 79x14 9.0 and 11.4; 0.83 of the units' time over 305 shapes of w = 9 to
+// 16, but 1.02 over 166 of w = 4 to 8).
+template <int WIN>
+static bool one_column(const Geom &g) {
+  return rp_of(WIN) == 16 && g.W == WIN && g.C * cdiv64(g.N, 16) >= 1024;
+}
+
 template <class Tag, int WIN>
 static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const Geom &g, bool rev,
                                     hipStream_t st) {
@@ -2780,7 +2791,7 @@ static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const
   // windows, 11.6 against 15.2; w = 6 B4 C64 30x30, 448 units, 3.6 against 3.8).
   // The same products in the same order: the same bits.
   if constexpr (Tag::W16 && WIN >= 4) {
-    if (g.N >= 128 && (rp_of(WIN) == 16 || g.C * cdiv64(g.N, 16) >= 1024))
+    if (g.N >= 128 && (rp_of(WIN) == 16 || g.C * cdiv64(g.N, 16) >= 1024) && !one_column<WIN>(g))
       return GenEntry<Tag>::forward(x, t, y, g, WIN, WIN, rev ? 1 : 0, st);
   }
   if (rev)
@@ -2810,7 +2821,15 @@ static hipError_t run_forward_fixed(const void *x, const void *t, void *y, const
 //   maps they tile its whole-row copies are shorter where rows have fixed
 //   offsets (B128 C384 14x14 11.0 against 14.5); for the others see
 //   run_forward_fixed.  The same products in the same order: the same bits.
-//   (The general kernel needs a tensor of 16 elements.)
+//   (The general kernel needs a tensor of 16 elements.)  Not with few windows
+//   for many channels, where its prologue, once a channel, is most of the work
+//   and the row kernel has more workgroups a compute unit (us, row kernel and
+//   general): up to 4 windows of more than 256 channels (w = 14 B1 C293 8x14 4.7
+//   and 5.8, w = 8 B4 C1771 7x5 4.4 and 6.6), up to 8 of more than 512 (w = 15 B1
+//   C1938 4x99 18 and 42), and one to three units of 16 windows a channel for
+//   the unit kernel's eight waves (w = 15 B2 C574 16x120 10.0 and 18.4, w = 14 B12
+//   C655 20x11 11.9 and 17.1; 3000 units: w = 16 B15 C723 14x51 27 and 20).  Nor
+//   where one_column holds.
 template <class Tag, int WIN>
 constexpr bool kGenWindow = !Tag::W16 && rp_of(WIN) == 16;
 
@@ -2818,7 +2837,9 @@ template <class Tag, int WIN>
 static bool gen_map(const Geom &g) {
   const int64_t numel = g.B * g.C * g.H * g.W;
   if constexpr (Tag::W16) {
-    return WIN >= 7 && (g.H % WIN != 0 || g.W % WIN != 0) && numel >= 16;
+    const int64_t units = g.C * cdiv64(g.N, 16);
+    const bool few = (g.C > 256 && g.N <= 4) || (g.C > 512 && (g.N <= 8 || (units >= 1024 && units < 2048)));
+    return WIN >= 7 && (g.H % WIN != 0 || g.W % WIN != 0) && numel >= 16 && !few && !one_column<WIN>(g);
   } else {
     KArgs a = make_args(g);
     set_tiled<WIN, Tag::ES>(g, a, {});

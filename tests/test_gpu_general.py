@@ -490,6 +490,24 @@ def test_gradients_at_odd_addresses(shape, odd):
     assert torch.equal(dt, W.wbmm_backward_table(x, dy, w))
     assert torch.equal(dx, W.wbmm_backward_input(dy, t, w))
 
+# channels and windows on either side of the lines between the row kernel and
+# the general ones, on cut maps and on maps as wide as a window
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [(4, 256, 8, 14, 14), (4, 257, 8, 14, 14), (5, 257, 8, 14, 14), (1, 700, 20, 30, 15),
+                                   (8, 512, 5, 9, 9), (8, 513, 5, 9, 9), (9, 513, 5, 9, 9), (16, 1030, 5, 3, 7),
+                                   (17, 1030, 5, 3, 7), (33, 600, 7, 8, 13), (33, 683, 7, 8, 13), (15, 114, 79, 14, 14),
+                                   (10, 200, 44, 11, 11), (60, 300, 9, 9, 9), (16, 200, 63, 8, 8)],
+                         ids=lambda s: "B%dC%dH%dW%dw%d" % s)
+def test_channel_counts_change_no_bit(shape, dtype):
+    B, C, H, Wd, w = shape
+    x, t = (v.cuda() for v in data(B, C, H, Wd, w, w, dtype, seed=w))
+    for f in (W.wbmm_forward, W.wbmm_backward_input):
+        y = f(x, t, w)
+        for lo in (0, C - 20):
+            part = slice(lo, lo + 20)
+            assert torch.equal(y[:, part], f(x[:, part].contiguous(), t[part].contiguous(), w))
+
+
 @pytest.mark.parametrize("kind", ["forward", "forward w7", "backward", "matrix", "rectangular gradient"])
 def test_time_of_values_out_of_range(kind):
     """Values that take float32 products cost what those cost (the bf16 rate
