@@ -3004,13 +3004,32 @@ static hipError_t sum_slabs(const float *part, float *dt, int64_t n, const float
 //   elements at windows up to 8, from 4 M above (fused backward, us: w = 7
 //   B64 C96 56x56 47 -> 29, B64 C192 14x14 11.3 -> 9.5; w = 14 B8 C96 100x167
 //   69 -> 35; w = 5 B64 C96 40x40 41 -> 26; but w = 14 B4 C96 50x84, 1.6 M, 11.5
-//   against 12.5 and w = 9 B128 C384 9x9, 4.0 M, 17.3 against 23.9).
+//   against 12.5 and w = 9 B128 C384 9x9, 4.0 M, 17.3 against 23.9).  On maps
+//   that windows of 9 and more tile, where rows are only addressed one by one:
+//   w = 10, with six of sixteen columns padding, only where the workgroups, one
+//   a compute unit, leave less than a tenth of the chip idle (B36 C108 30x60 19.1
+//   against 24.3, B78 C17 100x60 29.6 -> 23.4; 37 shapes of 89 to 99 % 1.04 to
+//   1.11 -> 1, 14 below 73 % 0.91).  With more than 256 channels, whose workgroups
+//   come in rounds, windows of 13 and more: odd ones from 33 windows on (w = 15
+//   B34 C620 30x15, 68 windows, 50 -> 40; but B3 C864 30x75, 30, 22 against 34),
+//   even ones where the rounds are 70 % full (w = 14 B4 C470 112x154 64 -> 57; B4
+//   C260 56x154 29 against 35); w = 9, 11 and 12 lose (140 shapes: 0.91, 0.95 and
+//   0.82; w = 9 B8 C612 72x36 42 against 49, w = 12 B18 C353 60x36 32 against 39).
 // The same for the fused backward and the table gradient alone, so that they
 // agree bit for bit.
 template <class Tag, int WIN>
 static bool gen_grad(const Geom &g, bool tiled) {
   const int64_t numel = g.B * g.C * g.H * g.W;
   if (!Tag::W16) return (WIN >= 13 && numel >= (int64_t)1 << 21) || ((WIN == 7 || WIN == 8) && gen_map<Tag, WIN>(g));
+  if (rp_of(WIN) == 16 && g.H % WIN == 0 && g.W % WIN == 0) {
+    const int64_t stages = cdiv64(g.N, 32);
+    if (g.C <= 256) {
+      const int64_t idle = 256 * cdiv64(stages, 256 / g.C) - g.C * stages;  // stages not run, of 256 units'
+      if (WIN == 10 && 10 * idle > 256 * cdiv64(stages, 256 / g.C)) return false;
+    } else if (WIN < 13 || (WIN % 2 ? g.N <= 32 : 10 * g.C < 7 * 256 * cdiv64(g.C, 256))) {
+      return false;
+    }
+  }
   return !tiled && numel >= (int64_t)1 << (rp_of(WIN) == 8 ? 21 : 22);
 }
 

@@ -508,6 +508,15 @@ def test_channel_counts_change_no_bit(shape, dtype):
             assert torch.equal(y[:, part], f(x[:, part].contiguous(), t[part].contiguous(), w))
 
 
+# on either side of the lines between the general gradient kernel and the
+# four-wave ones, on tiled maps without fixed-offset rows
+@pytest.mark.parametrize("shape", [(36, 108, 30, 60, 10), (78, 17, 100, 60, 10), (12, 612, 18, 36, 9), (20, 257, 33, 33, 11),
+                                   (20, 256, 33, 33, 11), (8, 600, 30, 30, 15), (9, 600, 30, 30, 15), (14, 260, 28, 42, 14),
+                                   (10, 420, 28, 42, 14)], ids=lambda s: "B%dC%dH%dW%dw%d" % s)
+def test_gradients_on_tiled_maps(shape):
+    test_general_gradients(shape, "bf16")
+
+
 @pytest.mark.parametrize("kind", ["forward", "forward w7", "backward", "matrix", "rectangular gradient"])
 def test_time_of_values_out_of_range(kind):
     """Values that take float32 products cost what those cost (the bf16 rate
