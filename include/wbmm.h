@@ -126,11 +126,15 @@ wbmm_status wbmm_backward_table(const void *x, const void *dy, float *dtable,
 size_t wbmm_backward_workspace_bytes(int64_t B, int64_t C, int64_t H, int64_t W,
                                      int w, wbmm_dtype dtype);
 
-/* Both gradients in one pass (the input gradient of wbmm_backward_input and
+/* Both gradients in one call (the input gradient of wbmm_backward_input and
  * the table gradient of wbmm_backward_table, the chain rule on Alg. 1 and
  * Theorem 3.2 for the training mode of Sec. "Inference Caching Mechanism",
- * where gradients flow through the table): every window of x and dy is
- * read once.  Results equal those of the two separate calls bit for bit.
+ * where gradients flow through the table).  In one pass, which reads every
+ * window of x and dy once, but for float32 windows of 9 and more, float32 maps
+ * of 2 M elements and more that the general kernels take, and a 16-bit dx that
+ * alone is not 4-byte aligned: there dy is read twice, by the input gradient's
+ * and the table gradient's kernel.  Results equal those of the two separate
+ * calls bit for bit.
  * x, dy, dx: [B,C,H,W] in dtype; table: [C,(2w-1)^2] in dtype; dtable: float32
  * [C,(2w-1)^2], overwritten.  dx and dtable must not overlap any input, each
  * other or the workspace.  workspace / workspace_bytes: as for

@@ -15,10 +15,9 @@ namespace wbmm {
 
 struct DenseArgs {
   int64_t B, C, H, W;
-  int wh, ww, d, kp;  // kp: d padded to the matrix-core K step
+  int wh, ww, d;
   int NH, NW;
-  int64_t N;          // windows per channel
-  int tiles_per_ch;
+  int64_t N;  // windows per channel
 };
 
 // Element offset of window position p of window n (channel c), or -1 when
@@ -146,15 +145,13 @@ __global__ __launch_bounds__(256) void dense_bin_kernel(const float *__restrict_
 
 // ------------------------------------------------------------ launchers
 
-static DenseArgs dense_args(const Geom &g, int wh, int ww, int ks) {
+static DenseArgs dense_args(const Geom &g, int wh, int ww) {
   DenseArgs a;
   a.B = g.B; a.C = g.C; a.H = g.H; a.W = g.W;
   a.wh = wh; a.ww = ww; a.d = wh * ww;
-  a.kp = (a.d + ks - 1) / ks * ks;
   a.NH = (int)((g.H + wh - 1) / wh);
   a.NW = (int)((g.W + ww - 1) / ww);
   a.N = g.B * (int64_t)a.NH * a.NW;
-  a.tiles_per_ch = 0;
   return a;
 }
 
@@ -172,7 +169,7 @@ template <class Tag>
 static hipError_t run_dense_dm(const void *x, const void *dy, float *dm, const Geom &g, int wh, int ww,
                                hipStream_t st) {
   typedef DenseDmCfg<Tag> G;
-  DenseArgs a = dense_args(g, wh, ww, Tag::KS);
+  DenseArgs a = dense_args(g, wh, ww);
   const int nblk = (a.d + G::BP - 1) / G::BP;
   typedef typename Tag::S S;
   dense_dm_kernel<Tag><<<dim3((unsigned)(g.C * nblk * nblk)), dim3(256), G::LDS, st>>>(
