@@ -58,23 +58,23 @@ def parse():
 # on (sha256 of the kernel header's code without comments and blank lines);
 # otherwise reported as null.
 TRAFFIC = {
-    ("bf16_b128_c384_14_w14", "bwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 60216855},
-    ("bf16_b128_c384_14_w14", "dt"): {"source": "47e7e6b98c7e5ae3", "bytes": 40341305},
-    ("bf16_b128_c384_14_w14", "dx"): {"source": "47e7e6b98c7e5ae3", "bytes": 39188661},
-    ("bf16_b128_c384_14_w14", "fwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 39195930},
-    ("bf16_b16_c64_112_hier7", "hbwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 79881155},
-    ("bf16_b16_c64_112_hier7", "hfwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 51753543},
-    ("bf16_b16_c64_112_w14", "bwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 78627821},
-    ("bf16_b16_c64_112_w14", "dt"): {"source": "47e7e6b98c7e5ae3", "bytes": 52797814},
-    ("bf16_b16_c64_112_w14", "dx"): {"source": "47e7e6b98c7e5ae3", "bytes": 51579920},
-    ("bf16_b16_c64_112_w14", "fwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 51625552},
-    ("bf16_b64_c192_28_hier7", "hbwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 60623699},
-    ("bf16_b64_c192_28_hier7", "hfwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 39823680},
-    ("bf16_b64_c192_28_w14", "bwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 59373612},
-    ("bf16_b64_c192_28_w14", "dt"): {"source": "47e7e6b98c7e5ae3", "bytes": 39781561},
-    ("bf16_b64_c192_28_w14", "dx"): {"source": "47e7e6b98c7e5ae3", "bytes": 39380701},
-    ("bf16_b64_c192_28_w14", "fwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 39351965},
-    ("bf16_b64_c96_56_w7", "fwd"): {"source": "47e7e6b98c7e5ae3", "bytes": 77249018},
+    ("bf16_b128_c384_14_w14", "bwd"): {"source": "faa545b1172465f5", "bytes": 60217303},
+    ("bf16_b128_c384_14_w14", "dt"): {"source": "faa545b1172465f5", "bytes": 40341305},
+    ("bf16_b128_c384_14_w14", "dx"): {"source": "faa545b1172465f5", "bytes": 39187510},
+    ("bf16_b128_c384_14_w14", "fwd"): {"source": "faa545b1172465f5", "bytes": 39195547},
+    ("bf16_b16_c64_112_hier7", "hbwd"): {"source": "faa545b1172465f5", "bytes": 79881347},
+    ("bf16_b16_c64_112_hier7", "hfwd"): {"source": "faa545b1172465f5", "bytes": 51711495},
+    ("bf16_b16_c64_112_w14", "bwd"): {"source": "faa545b1172465f5", "bytes": 78627549},
+    ("bf16_b16_c64_112_w14", "dt"): {"source": "faa545b1172465f5", "bytes": 52797942},
+    ("bf16_b16_c64_112_w14", "dx"): {"source": "faa545b1172465f5", "bytes": 51601136},
+    ("bf16_b16_c64_112_w14", "fwd"): {"source": "faa545b1172465f5", "bytes": 51584112},
+    ("bf16_b64_c192_28_hier7", "hbwd"): {"source": "faa545b1172465f5", "bytes": 60605289},
+    ("bf16_b64_c192_28_hier7", "hfwd"): {"source": "faa545b1172465f5", "bytes": 39885920},
+    ("bf16_b64_c192_28_w14", "bwd"): {"source": "faa545b1172465f5", "bytes": 59373740},
+    ("bf16_b64_c192_28_w14", "dt"): {"source": "faa545b1172465f5", "bytes": 39781689},
+    ("bf16_b64_c192_28_w14", "dx"): {"source": "faa545b1172465f5", "bytes": 39419229},
+    ("bf16_b64_c192_28_w14", "fwd"): {"source": "faa545b1172465f5", "bytes": 39216301},
+    ("bf16_b64_c96_56_w7", "fwd"): {"source": "faa545b1172465f5", "bytes": 77301397},
 }
 
 
