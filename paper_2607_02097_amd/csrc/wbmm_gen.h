@@ -283,6 +283,22 @@ struct FarRange {
   }
   __device__ __attribute__((always_inline)) bool far() const { return mx >= 2 * kFarHi || mn < 2 * kFarLo - 1; }
 };
+// The same with the largest as a float, a third fewer instructions, for the
+// products Y = X M: NaN may be left out, which the parts carry to the same
+// outputs.
+struct FarRangeFwd {
+  float mx = 0.f;
+  uint32_t mn = ~0u;
+  __device__ __attribute__((always_inline)) void add(uint32_t a, uint32_t b) {
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(mx) : "v"(a), "v"(b));
+    const uint32_t m = (a << 1) - 1, n = (b << 1) - 1;
+    mn = m < mn ? m : mn;
+    mn = n < mn ? n : mn;
+  }
+  __device__ __attribute__((always_inline)) bool far() const {
+    return !(mx < __builtin_bit_cast(float, kFarHi)) || mn < 2 * kFarLo - 1;
+  }
+};
 
 // Two values -> the dwords of their three planes.
 __device__ __attribute__((always_inline)) inline void split3(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
@@ -294,8 +310,8 @@ __device__ __attribute__((always_inline)) inline void split3(float a, float b, u
 }
 
 // A padded row -> LDS (window-major planes); float32: returns whether the row
-// is far.
-template <class Tag, int RP, int S>
+// is far (FWD: see FarRangeFwd).
+template <class Tag, int RP, int S, bool FWD>
 __device__ __attribute__((always_inline)) inline bool gen_write(unsigned char *xb, int v, int hi,
                                                                 const uint32_t (&d)[RP * Tag::ES / 4]) {
   typedef GenCfg<Tag, RP, S> G;
@@ -306,10 +322,17 @@ __device__ __attribute__((always_inline)) inline bool gen_write(unsigned char *x
     for (int i = 0; i < G::ND; i += 4)
       *reinterpret_cast<uint4 *>(p + 4 * i) = make_uint4(d[i], d[i + 1], d[i + 2], d[i + 3]);
   } else {
-    FarRange mag;
+    if constexpr (FWD) {
+      FarRangeFwd mag;
 #pragma unroll
-    for (int i = 0; i < G::ND; ++i) mag.add(d[i]);
-    far = mag.far();
+      for (int i = 0; i < G::ND; i += 2) mag.add(d[i], d[i + 1]);
+      far = mag.far();
+    } else {
+      FarRange mag;
+#pragma unroll
+      for (int i = 0; i < G::ND; ++i) mag.add(d[i]);
+      far = mag.far();
+    }
 #pragma unroll
     for (int i = 0; i < RP; i += 8) {
       uint32_t h[4], m[4], l[4];
@@ -346,16 +369,14 @@ __device__ __attribute__((always_inline)) inline int64_t gen_coef(const GenArgs 
 // Toeplitz blocks in LDS, block dh = hi - ho from -(KR - 1) to KR - 1 as
 // [x_out][x_in] (zero past the window), from the table copy Ts (reversed for
 // the input gradient): a fragment is then one 16-byte read at a per-lane
-// base plus a constant.  float32: three planes, the lowest at tblow.  Returns
-// the magnitudes that the thread saw (float32).
+// base plus a constant.  float32: three planes, the lowest at tblow.
 template <class Tag, int RP, int S>
-__device__ __attribute__((always_inline)) inline FarRange gen_build_tb(const GenArgs &a, const typename Tag::S *Ts,
-                                                                       unsigned char *tb, unsigned char *tblow,
-                                                                       int tid) {
+__device__ __attribute__((always_inline)) inline void gen_build_tb(const GenArgs &a, const typename Tag::S *Ts,
+                                                                   unsigned char *tb, unsigned char *tblow,
+                                                                   int tid) {
   typedef GenCfg<Tag, RP, S> G;
   constexpr int CPR = RP / 8;  // 8-element chunks per block row
   const int K1 = 2 * a.ww - 1;
-  FarRange mag;
   for (int ch = tid; ch < G::NBLK * RP * CPR; ch += kGenThreads) {
     const int row = ch / CPR, xi0 = (ch % CPR) * 8;
     const int dh = row / RP - (G::KR - 1), xo = row % RP;
@@ -381,8 +402,6 @@ __device__ __attribute__((always_inline)) inline FarRange gen_build_tb(const Gen
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float f0 = nv > 2 * k ? Ts[base + 2 * k] : 0.f, f1 = nv > 2 * k + 1 ? Ts[base + 2 * k + 1] : 0.f;
-        mag.add(__builtin_bit_cast(uint32_t, f0));
-        mag.add(__builtin_bit_cast(uint32_t, f1));
         split3(f0, f1, h[k], m[k], l[k]);
       }
       *reinterpret_cast<uint4 *>(p) = make_uint4(h[0], h[1], h[2], h[3]);
@@ -390,7 +409,6 @@ __device__ __attribute__((always_inline)) inline FarRange gen_build_tb(const Gen
       *reinterpret_cast<uint4 *>(tblow + off) = make_uint4(l[0], l[1], l[2], l[3]);
     }
   }
-  return mag;
 }
 
 // Byte offset in the blocks of lane's part of the fragment of tile pair T at
@@ -693,10 +711,12 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
   if constexpr (DEEP) gen_load<Tag, RP>(a.numel, x, row(1), d1);
   __builtin_amdgcn_sched_barrier(0);
   E *Ts = reinterpret_cast<E *>(obuf);
+  FarRange cmag;  // coefficients seen (float32)
   if constexpr (!MAT) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int k = tid + i * kGenThreads;
+      if constexpr (!Tag::W16) cmag.add(__builtin_bit_cast(uint32_t, tv[i]));
       if (k < K2 + 10) Ts[k] = k < K2 ? tv[i] : (E)0;
     }
   }
@@ -705,7 +725,6 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
   __syncthreads();
   const int T = wave % S, sg = wave / S;  // tile pair, sub-tile group
   GFrag fr[F::NPR][2][S];
-  FarRange cmag;  // coefficients seen (float32)
   if constexpr (MAT) {
     constexpr int ROOM = F::LOW_OFF - G::XB;
     if constexpr (Tag::W16) {
@@ -714,7 +733,7 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
     } else
       gen_frags_mat32<RP, S>(a, coef, c, T, lane, fr, cmag);
   } else {
-    cmag = gen_build_tb<Tag, RP, S>(a, Ts, xbuf + G::XB, F::LOW ? smem + F::LOW_OFF : xbuf + G::XB + 2 * G::TBB, tid);
+    gen_build_tb<Tag, RP, S>(a, Ts, xbuf + G::XB, F::LOW ? smem + F::LOW_OFF : xbuf + G::XB + 2 * G::TBB, tid);
   }
   if constexpr (!Tag::W16) {
     // far coefficients: a huge or a tiny one, or none of normal size though
@@ -734,7 +753,7 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
 #pragma unroll
     for (int i = 0; i < G::ND; ++i) asm volatile("" : "+v"(d[i]));  // (the rows arrive here, on every path)
     if (hi < G::KR) {
-      if (gen_write<Tag, RP, S>(xbuf + (s & 1) * G::XB, v, hi, d)) flag[s & 1] = s;
+      if (gen_write<Tag, RP, S, true>(xbuf + (s & 1) * G::XB, v, hi, d)) flag[s & 1] = s;
     }
   };
   write(0, d0);
@@ -959,12 +978,15 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
   uint32_t *masks = reinterpret_cast<uint32_t *>(smem + D::MASK_OFF);
   int *flag = reinterpret_cast<int *>(smem + D::FLAG_OFF);
   const float *tc = tab + c * K2;
-  for (int k = tid; k < K2 + 10; k += kGenThreads)
-    Ts[k] = k < K2 ? tc[a.src == kSrcTableRev ? K2 - 1 - k : k] : 0.f;
+  FarRange cmag;
+  for (int k = tid; k < K2 + 10; k += kGenThreads) {
+    const float f = k < K2 ? tc[a.src == kSrcTableRev ? K2 - 1 - k : k] : 0.f;
+    cmag.add(__builtin_bit_cast(uint32_t, f));
+    Ts[k] = f;
+  }
   if (tid < 72) masks[tid] = tid / 8 > tid % 8 ? ~0u : 0u;
   if (tid < 3) flag[tid] = 0;
   __syncthreads();
-  FarRange cmag;
   for (int ch = tid; ch < D::NF * 64; ch += kGenThreads) {
     const int l = ch & 63, lg = l >> 4, lo = l & 15;
     const int dh = (ch / 64 - (2 * S - 1)) * (16 / RP) + 8 * lg / RP - lo / RP, xo = lo % RP, xi = 8 * lg % RP;
@@ -975,8 +997,6 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float f0 = nv > 2 * k ? t[2 * k] : 0.f, f1 = nv > 2 * k + 1 ? t[2 * k + 1] : 0.f;
-      cmag.add(__builtin_bit_cast(uint32_t, f0));
-      cmag.add(__builtin_bit_cast(uint32_t, f1));
       split3(f0, f1, hh[k], mm[k], ll[k]);
     }
     unsigned char *p = smem + ch * 16;
@@ -1050,21 +1070,13 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_direct_kernel(const float 
 #pragma unroll
             for (int i = 0; i < 8; ++i) raw[s][i] = i < 7 ? raw[s][i + 1] : 0u;
         }
-        // (the largest as floats, a third fewer instructions than FarRange; it
-        // may leave out NaN, which the parts carry to the same outputs)
-        float mx = 0.f;
-        uint32_t mn = ~0u;
+        FarRangeFwd mag;
         uint32_t hh[4], mm[4], ll[4];
 #pragma unroll
         for (int i = 0; i < 8; ++i) raw[s][i] &= m[i];
 #pragma unroll
-        for (int i = 0; i < 8; i += 2) {
-          asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(mx) : "v"(raw[s][i]), "v"(raw[s][i + 1]));
-          const uint32_t n0 = (raw[s][i] << 1) - 1, n1 = (raw[s][i + 1] << 1) - 1;
-          mn = n0 < mn ? n0 : mn;
-          mn = n1 < mn ? n1 : mn;
-        }
-        far |= !(mx < __builtin_bit_cast(float, kFarHi)) || mn < 2 * kFarLo - 1;
+        for (int i = 0; i < 8; i += 2) mag.add(raw[s][i], raw[s][i + 1]);
+        far |= mag.far();
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           split3(__builtin_bit_cast(float, raw[s][2 * i]), __builtin_bit_cast(float, raw[s][2 * i + 1]), hh[i], mm[i], ll[i]);
@@ -1503,7 +1515,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void gen_dt_kernel(
 #pragma unroll
     for (int i = 0; i < G::ND; ++i) asm volatile("" : "+v"(d.x[i]), "+v"(d.g[i]));  // (the rows arrive here, on every path)
     if (hi < G::KR) {
-      const bool fx = gen_write<Tag, RP, S>(st, v, hi, d.x), fg = gen_write<Tag, RP, S>(st + G::XB, v, hi, d.g);
+      const bool fx = gen_write<Tag, RP, S, false>(st, v, hi, d.x), fg = gen_write<Tag, RP, S, false>(st + G::XB, v, hi, d.g);
       if (fx || fg) flag[s & 1] = s;
     }
   };
