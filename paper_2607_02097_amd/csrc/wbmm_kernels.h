@@ -3146,7 +3146,10 @@ static hipError_t run_backward(const void *x, const void *dy, const void *t, voi
   if (!Tag::W16 && (kGenWindow<Tag, WIN> || gen_map<Tag, WIN>(g))) {
     // dY is read twice, which costs less than the fused kernels' float32
     // products (w = 14, B128 C192 28x28: 279 us fused, 148 as two launches;
-    // w = 7 B32 C256 37x53 100 and 78)
+    // w = 7 B32 C256 37x53 100 and 78).  Below 2 M elements it costs more (w =
+    // 14 B1 C8 28x28 12 fused, 16 as two), but dX must equal
+    // wbmm_backward_input's, whose kernel is the more precise and takes 9 us
+    // there where the float32 products took 33.
     const hipError_t e = run_forward<Tag, WIN>(dy, t, dx, g, true, st);
     return e != hipSuccess ? e : run_dtable<Tag, WIN>(x, dy, dt, ws, g, st);
   }
