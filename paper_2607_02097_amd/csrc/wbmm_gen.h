@@ -806,7 +806,7 @@ __global__ __launch_bounds__(kGenThreads, (2 * GenFwd<Tag, RP, S, MAT>::WGS)) vo
           }
         }
       } else {
-        if (__builtin_expect(far, 0)) {
+        if (far) {
           const uint32_t n = n0 + s * G::CW + 16 * u0 + ln;
           gen_far_pair<RP, S>(a, x, coef + c * (MAT ? a.wh * a.ww * a.wh * a.ww : K2), a.src, c, n, T, lane, acc[0]);
         } else {
